@@ -698,6 +698,7 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
     it.count = 0;
     bool big = false;
     unsigned a = 0, r = 0, mp = 0, in = 0, up = 0;
+    long long tiles[BATCH_MAX], rows[BATCH_MAX];
     int max_sweeps = 0;
     for (; i < count && it.count < BATCH_MAX; ++i) {
       if (!batchable(i)) continue;
@@ -712,7 +713,8 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
       const Geometry g = plan_columns(p.n, p.m, WIDE, Q);
       agg.first[it.count] = a; a += (unsigned)(g.tiles * g.groups);
       red.first[it.count] = r; r += (unsigned)cdiv(p.m, SWG / reduce_parts(g.groups, fold_threads(g.groups)));
-      map.first[it.count] = mp; mp += (unsigned)(g.tiles * g.map_groups);
+      tiles[it.count] = g.tiles;
+      rows[it.count] = p.n;
       ini.first[it.count] = in; in += (unsigned)cdiv(p.m, WG);
       upd.first[it.count] = up; up += (unsigned)cdiv(p.m, UPD_COLS);
       plan_l11(p.n, p.m, (int)sizeof(T), &plan.sweeps[it.count], &plan.handoff[it.count]);
@@ -721,6 +723,9 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
       ++it.count;
     }
     if (it.count == 0) break;
+    BatchMapPlan mplan;
+    plan_batch_map(it.count, tiles, rows, &mplan);
+    for (int k = 0; k < it.count; ++k) { map.first[k] = mp; mp += (unsigned)(tiles[k] * mplan.groups[k]); }
     agg.first[it.count] = a; red.first[it.count] = r; map.first[it.count] = mp;
     ini.first[it.count] = in; upd.first[it.count] = up;
     mark(stream);
@@ -741,8 +746,8 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
       launch((l11_finish_batch_kernel<T>), dim3(up), dim3(FIN_WG), stream, it, upd, plan);
     }
     mark(stream);
-    if (big) launch((colmap_batch_kernel<Q, T, SEARCH_CACHE_BIG>), dim3(mp), dim3(WG), stream, it, map, outer);
-    else launch((colmap_batch_kernel<Q, T, SEARCH_CACHE>), dim3(mp), dim3(WG), stream, it, map, outer);
+    if (big) launch((colmap_batch_kernel<Q, T, SEARCH_CACHE_BIG>), dim3(mp), dim3(WG), stream, it, map, mplan, outer);
+    else launch((colmap_batch_kernel<Q, T, SEARCH_CACHE>), dim3(mp), dim3(WG), stream, it, map, mplan, outer);
     mark(stream);
   }
   int st = launch_status();
