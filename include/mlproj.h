@@ -135,7 +135,7 @@ int mlproj_trace_end(void);
  * rows, or up to 4096 rows when the matrix has at most 4M elements; else 3 at 4096, 6 at 16384,
  * 12 beyond 131072): the finishing pass costs more per column the taller the matrix.  With the
  * default, a matrix of at most 4096 rows and 64M elements (32M in 16-bit storage) whose rows are
- * 16-byte aligned is not swept at all: one kernel keeps 16 whole columns per workgroup in
+ * at least 16 bytes long is not swept at all: one kernel keeps 16 whole columns per workgroup in
  * registers (a stripe whose columns are all dropped is zeroed with most of it unread), finds their
  * thresholds there and maps from the same registers (fp32: also up to 8192 rows, 8 columns per
  * workgroup, while there are no more such stripes than compute units); any forced value keeps
@@ -242,8 +242,8 @@ int bilevel_proj_pq(int outer_norm, int variant, const float* Y /* device, n*m *
  * projection): Alg. 1 unchanged, computed on the widened values; only X is rounded to the
  * storage format.  v_out and u_out stay fp32.  mask_out[j] = 1 when column j is kept
  * (u_j > 0, decided in fp64) and 0 when the projection zeroes it.  Y and X must be aligned to
- * the element size; the 16-byte accesses need 16-byte aligned pointers and m a multiple of
- * 16 / element size, other inputs take an element-wise path.  X may alias Y.  The workspace
+ * the element size; rows of any length are read and written in 16-byte pieces (shorter ones element
+ * by element), fastest when they are 64-byte aligned.  X may alias Y.  The workspace
  * size is mlproj_workspace_bytes(variant, n, m, 1) for every storage type.                  */
 int bilevel_proj_stored(int storage, int outer_norm, int variant,
                         const void* Y /* device, n*m elements */, void* X /* device, n*m elements */,

@@ -30,8 +30,7 @@ struct BatchItem {
   unsigned char* mask_out;
   long long n, m;
   double eta;
-  int wide;   // rows are 16-byte aligned: the wide form of LaneCols
-  int x_vec;  // ... and so is X: 16-byte stores
+  int wide;   // the wide form of LaneCols (see wide_rows)
   int whole;  // one-kernel form: X overlaps Y, one workgroup does the whole matrix
 };
 
@@ -118,12 +117,12 @@ __global__ __launch_bounds__(WG) void colmap_batch_kernel(BatchItems it, BatchGr
   const T* Y = static_cast<const T*>(b.Y);
   T* X = static_cast<T*>(b.X);
   const double eta = Q == Q1 ? -1.0 : b.eta;   // l1,1: tau comes from the record, not from a search here
-  if (b.wide && b.x_vec)
-    colmap_body<Q, T, WIDE, false, true, SC>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid);
+  if (b.wide && b.m % WIDE == 0)
+    colmap_body<Q, T, WIDE, MAP_EVEN, SC>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid);
   else if (b.wide)
-    colmap_body<Q, T, WIDE, false, false, SC>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid);
+    colmap_body<Q, T, WIDE, MAP_RAGGED, SC>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid);
   else
-    colmap_body<Q, T, WIDE, true, false, SC>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid);
+    colmap_body<Q, T, WIDE, MAP_STRIDED, SC>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid);
 }
 
 // Matrices of at most 128 KiB each: the one-kernel form of tiny.h for all of them in one launch
@@ -233,8 +232,12 @@ __global__ __launch_bounds__(LH_WG, lh_min_waves(NV, PACKED)) void l11_held_batc
   const Geometry g = plan_columns(b.n, b.m, WIDE, Q1);
   const Ws ws = bind(b.ws, layout_for(g, b.m, Q1));
   const long long stripes = (long long)(gr.first[p + 1] - gr.first[p]);
-  l11_held_body<T, NV, LH_SEARCH_CACHE>(static_cast<const T*>(b.Y), static_cast<T*>(b.X), b.n, b.m, ws, b.u_out,
-                                        b.mask_out, b.eta, outer, stripe_of_workgroup(bid, stripes));
+if (lh_even_rows(b.X, b.m, (int)sizeof(T)))
+    l11_held_body<T, NV, LH_SEARCH_CACHE, LH_COLS, true>(static_cast<const T*>(b.Y), static_cast<T*>(b.X), b.n, b.m, ws, b.u_out,
+                                                        b.mask_out, b.eta, outer, stripe_of_workgroup(bid, stripes));
+  else
+    l11_held_body<T, NV, LH_SEARCH_CACHE, LH_COLS, false>(static_cast<const T*>(b.Y), static_cast<T*>(b.X), b.n, b.m, ws, b.u_out,
+                                                        b.mask_out, b.eta, outer, stripe_of_workgroup(bid, stripes));
 }
 
 }  // namespace mlproj

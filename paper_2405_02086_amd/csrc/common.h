@@ -238,92 +238,138 @@ struct alignas(sizeof(T) * VEC) Pack {
   T e[VEC];
 };
 
+// 16 bytes at any element's address, as one access: the rows of a matrix whose row length is not a
+// multiple of 16 bytes start anywhere, and this GPU's 16-byte loads and stores need no alignment
+// (the runtime runs it in unaligned access mode).
+template <int ALIGN> struct Wide16;
+template <> struct Wide16<4> { typedef unsigned type __attribute__((ext_vector_type(4), aligned(4))); };
+template <> struct Wide16<2> { typedef unsigned type __attribute__((ext_vector_type(4), aligned(2))); };
+
+template <typename T, int VEC>
+__device__ __forceinline__ Pack<T, VEC> load_pack(const T* p) {
+  Pack<T, VEC> t;
+  if constexpr (VEC > 1) {
+    const typename Wide16<sizeof(T)>::type w = *reinterpret_cast<const typename Wide16<sizeof(T)>::type*>(p);
+    __builtin_memcpy(&t, &w, 16);
+  } else {
+    t.e[0] = *p;
+  }
+  return t;
+}
+
 template <int VEC, typename T>
 __device__ __forceinline__ void load_row(const T* p, float (&x)[VEC]) {
-  const Pack<T, VEC> t = *reinterpret_cast<const Pack<T, VEC>*>(p);
+  const Pack<T, VEC> t = load_pack<T, VEC>(p);
 #pragma unroll
   for (int k = 0; k < VEC; ++k) x[k] = (float)t.e[k];
 }
 
 template <typename T>
-__device__ __forceinline__ void store_one_nt(T* p, float x) {
+__device__ __forceinline__ void store_one_nt(T* p, T x) {
   if constexpr (sizeof(T) == 4) {
     __builtin_nontemporal_store(x, p);
   } else {
-    const T t = (T)x;
     unsigned short bits;
-    __builtin_memcpy(&bits, &t, 2);
+    __builtin_memcpy(&bits, &x, 2);
     __builtin_nontemporal_store(bits, reinterpret_cast<unsigned short*>(p));
   }
 }
 
 // X is written once and never read again by this call: a non-temporal store keeps it from
-// displacing Y in the caches between the two passes over Y.  WIDE = one 16-byte store
-// (X 16-byte aligned), otherwise element by element.
-template <int VEC, bool WIDE = (VEC > 1), typename T>
-__device__ __forceinline__ void store_row_nt(T* p, const float (&x)[VEC]) {
-  if constexpr (VEC > 1 && WIDE) {
-    typedef unsigned vu4 __attribute__((ext_vector_type(4)));
-    Pack<T, VEC> t;
-#pragma unroll
-    for (int k = 0; k < VEC; ++k) t.e[k] = (T)x[k];
-    vu4 w;
-    __builtin_memcpy(&w, &t, 16);
-    __builtin_nontemporal_store(w, reinterpret_cast<vu4*>(p));
-  } else {
-#pragma unroll
-    for (int k = 0; k < VEC; ++k) store_one_nt(p + k, x[k]);
-  }
+// displacing Y in the caches between the two passes over Y.  (NT = false: an ordinary store, for runs
+// that leave cache lines partly written which a neighbour is about to complete.)
+// A product of fp64, rounded to fp32 and then to the storage type.  The fp32 value is made opaque: the
+// compiler is free to round fp64 straight to 16 bits instead and does so depending on the code around
+// it, so that two kernels would differ in the last bit (and that conversion takes a dozen
+// instructions: 4096 x 4096, l1,2, fp16 40 against 23 us).
+template <typename T>
+__device__ __forceinline__ T round_to(double x) {
+  float f = (float)x;
+  if constexpr (sizeof(T) == 2) asm("" : "+v"(f));
+  return (T)f;
 }
 
-// The columns of a tile that one lane owns, and how it reaches them in a row.
-//   wide    : VEC consecutive columns, one 16-byte access per row; needs 16-byte aligned
-//             rows (base aligned, row length a multiple of VEC);
-//   strided : columns lane, lane + 64, lane + 128, ... of the tile, one element per access,
-//             for any alignment and row length.  A wavefront's access is still one coalesced
-//             run of 64 elements and a lane has the same bytes in flight as in the wide form.
-template <typename T, int VEC, bool STRIDED>
-struct LaneCols {
-  long long first;      // the first owned column
-  bool ok[VEC];         // which owned columns exist (column < m)
-  long long from[VEC];  // strided: the column to read for slot k (an existing one, see load)
-  __device__ __forceinline__ LaneCols(long long tile0, int lane, long long m) {
-    first = STRIDED ? tile0 + lane : tile0 + (long long)lane * VEC;
+template <bool NT = true, typename T, int VEC>
+__device__ __forceinline__ void store_pack(T* p, const Pack<T, VEC>& t) {
+  if constexpr (VEC > 1) {
+    typename Wide16<sizeof(T)>::type w;
+    __builtin_memcpy(&w, &t, 16);
+    if constexpr (NT) __builtin_nontemporal_store(w, reinterpret_cast<typename Wide16<sizeof(T)>::type*>(p));
+    else *reinterpret_cast<typename Wide16<sizeof(T)>::type*>(p) = w;
+  } else {
+    store_one_nt(p, t.e[0]);
+  }
+}
+template <int VEC, bool NT = true, typename T>
+__device__ __forceinline__ void store_row(T* p, const float (&x)[VEC]) {
+  Pack<T, VEC> t;
 #pragma unroll
-    for (int k = 0; k < VEC; ++k) {
-      ok[k] = col(k) < m;
-      from[k] = ok[k] ? col(k) : first;
+  for (int k = 0; k < VEC; ++k) t.e[k] = (T)x[k];
+  store_pack<NT>(p, t);
+}
+template <int VEC, typename T>
+__device__ __forceinline__ void store_row_nt(T* p, const float (&x)[VEC]) { store_row<VEC, true>(p, x); }
+
+// The columns of a tile that one lane owns, and how it reaches them in a row.
+//   wide    : VEC consecutive columns, one 16-byte access per row, wherever the row starts.  The
+//             lane whose columns would run past the end of the row (m not a multiple of VEC) reads
+//             the row's last 16 bytes instead: its first slots then shadow columns of its
+//             neighbour, and are neither kept nor stored.  Needs m >= VEC.
+//   strided : columns lane, lane + 64, lane + 128, ... of the tile, one element per access, for
+//             rows shorter than one 16-byte access.  A slot whose column does not exist reads the
+//             lane's first column instead, so that no load is conditional (a conditional load
+//             brings its wait with it); what such a slot computes is never stored or read.
+// ALL_WHOLE: m is known to be a multiple of VEC (wide form), so a lane owns all its slots or none.
+template <typename T, int VEC, bool STRIDED, bool ALL_WHOLE = false>
+struct LaneCols {
+  long long tile;       // first column of the tile
+  long long first;      // column of slot 0
+  bool some;            // the lane owns a column
+  bool whole;           // ... and every slot is an owned one
+  bool ok[VEC];         // which slots are owned columns
+  long long from[STRIDED ? VEC : 1];  // strided: the column to read for slot k (an existing one, see load)
+  __device__ __forceinline__ LaneCols(long long tile0, int lane, long long m) {
+    tile = tile0;
+    if constexpr (STRIDED) {
+      first = tile0 + lane;
+      some = first < m;
+      whole = false;
+#pragma unroll
+      for (int k = 0; k < VEC; ++k) {
+        ok[k] = col(k) < m;
+        from[k] = ok[k] ? col(k) : first;
+      }
+    } else {
+      const long long mine = tile0 + (long long)lane * VEC;
+      some = mine < m;
+      whole = ALL_WHOLE || mine + VEC <= m;
+      first = whole ? mine : m - VEC;
+#pragma unroll
+      for (int k = 0; k < VEC; ++k) ok[k] = some && (ALL_WHOLE || first + k >= mine);
     }
   }
   __device__ __forceinline__ long long col(int k) const {
     return STRIDED ? first + (long long)k * WAVE : first + k;
   }
-  // position of owned column k inside the tile
-  static __device__ __forceinline__ int slot(int lane, int k) {
-    return STRIDED ? lane + k * WAVE : lane * VEC + k;
-  }
-  __device__ __forceinline__ bool any() const { return ok[0]; }  // owned columns ascend with k
+  // position of owned column k inside the tile (owned slots only)
+  __device__ __forceinline__ int slot(int k) const { return (int)(col(k) - tile); }
+  __device__ __forceinline__ bool any() const { return some; }
   // The lane's elements of the row that starts at `row`, as stored.  Call only when any().
-  // Strided: a slot whose column does not exist reads the lane's first column instead, so
-  // that no load is conditional (a conditional load brings its wait with it); what such a slot
-  // computes is never stored or read.
   __device__ __forceinline__ void load(const T* row, Pack<T, VEC>& dst) const {
     if constexpr (STRIDED) {
 #pragma unroll
       for (int k = 0; k < VEC; ++k) dst.e[k] = row[from[k]];
     } else {
-      dst = *reinterpret_cast<const Pack<T, VEC>*>(row + first);
+      dst = load_pack<T, VEC>(row + first);
     }
   }
-  // XWIDE: one 16-byte store (wide form and X 16-byte aligned), else element by element
-  template <bool XWIDE>
-  __device__ __forceinline__ void store_nt(T* row, const float (&x)[VEC]) const {
-    if constexpr (STRIDED) {
+  __device__ __forceinline__ void store_nt(T* row, const Pack<T, VEC>& x) const {
+    if (ALL_WHOLE || (!STRIDED && whole)) {
+      store_pack(row + first, x);
+    } else {
 #pragma unroll
       for (int k = 0; k < VEC; ++k)
-        if (ok[k]) store_one_nt(row + col(k), x[k]);
-    } else {
-      store_row_nt<VEC, XWIDE>(row + first, x);
+        if (ok[k]) store_one_nt(row + col(k), x.e[k]);
     }
   }
 };

@@ -181,7 +181,7 @@ __global__ __launch_bounds__(WG) void held_clear_kernel(unsigned* __restrict__ p
 }
 
 // posts: HELD_MAX_WGS words, cleared to HELD_ABSENT.  d0 slabs of len elements; the plan's grid.
-template <typename T, bool XVEC>
+template <typename T>
 __global__ __launch_bounds__(HELD_WG) void held_slab_kernel(const T* Y, T* X, long long d0, long long len,
                                                             HeldPlan hp, double eta, Ws ws, unsigned* posts,
                                                             float* __restrict__ v_out, float* __restrict__ u_out,
@@ -282,7 +282,7 @@ __global__ __launch_bounds__(HELD_WG) void held_slab_kernel(const T* Y, T* X, lo
         const float y = (float)d[k].e[e];
         f[e] = copysignf(fminf(fabsf(y), u), y);
       }
-      store_row_nt<VEC, XVEC>(hb.at(X, k), f);
+      store_row_nt<VEC>(hb.at(X, k), f);
     }
   }
 }

@@ -128,9 +128,10 @@ __device__ __forceinline__ void l11_sweep_body(const T* __restrict__ Y, long lon
   }
 #pragma unroll
   for (int k = 0; k < VEC; ++k) {
-    sm_sum[wave][lc.slot(lane, k)] = sum[k];
-    sm_cnt[wave][lc.slot(lane, k)] = cnt[k];
-    sm_cnt2[wave][lc.slot(lane, k)] = cnt2[k];
+    if (!lc.ok[k]) continue;
+    sm_sum[wave][lc.slot(k)] = sum[k];
+    sm_cnt[wave][lc.slot(k)] = cnt[k];
+    sm_cnt2[wave][lc.slot(k)] = cnt2[k];
   }
   __syncthreads();
   for (int col = threadIdx.x; col < TILE_W; col += WG) {
@@ -225,7 +226,7 @@ __device__ __forceinline__ void l11_filter_body(const T* __restrict__ Y, long lo
         for (int k = 0; k < VEC; ++k) {
           const float a = fabsf(y[k]);
           if (a >= clo[k] && !(a >= chi[k])) {
-            const int c = lc.slot(lane, k);
+            const int c = lc.slot(k);
             const unsigned slot = atomicAdd(&staged_cnt[c], 1u);
             if (slot < (unsigned)CAPW) {
               staged[slot][c] = a;
@@ -264,8 +265,9 @@ __device__ __forceinline__ void l11_filter_body(const T* __restrict__ Y, long lo
   }
 #pragma unroll
   for (int k = 0; k < VEC; ++k) {
-    sm_sum[wave][lc.slot(lane, k)] = sum[k];
-    sm_cnt[wave][lc.slot(lane, k)] = cnt[k];
+    if (!lc.ok[k]) continue;
+    sm_sum[wave][lc.slot(k)] = sum[k];
+    sm_cnt[wave][lc.slot(k)] = cnt[k];
   }
   __syncthreads();
   for (int c = threadIdx.x; c < TILE_W; c += WG) {

@@ -112,7 +112,8 @@ __global__ __launch_bounds__(WG) void colagg_grid_kernel(const T* __restrict__ Y
   }
   // the column sums, folded over the four wavefronts exactly as colagg_body does
 #pragma unroll
-  for (int k = 0; k < VEC; ++k) sm[wave][lc.slot(lane, k)] = acc[k];
+  for (int k = 0; k < VEC; ++k)
+    if (lc.ok[k]) sm[wave][lc.slot(k)] = acc[k];
   __syncthreads();
   const size_t cell0 = ((size_t)t * g.groups + grp) * TILE_W;
   for (int c = threadIdx.x; c < TILE_W; c += WG) {
@@ -128,7 +129,7 @@ __global__ __launch_bounds__(WG) void colagg_grid_kernel(const T* __restrict__ Y
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < VEC; ++k)
-      smf[wave][lc.slot(lane, k)] = q < GRID_PTS ? S[k][q] : (float)K[k][q - GRID_PTS];
+      if (lc.ok[k]) smf[wave][lc.slot(k)] = q < GRID_PTS ? S[k][q] : (float)K[k][q - GRID_PTS];
     __syncthreads();
     for (int c = threadIdx.x; c < TILE_W; c += WG) {
       float a = smf[0][c];

@@ -58,6 +58,11 @@ static inline bool lh_narrow_fits(long long n) {
   return (n + LhShape<float, LH_COLS_NARROW>::RL - 1) / LhShape<float, LH_COLS_NARROW>::RL * 4 <= 128;
 }
 
+// Whether every stripe of X begins and ends on a 64-byte sector.
+__host__ __device__ static inline bool lh_even_rows(const void* X, long long m, int elem_bytes) {
+  return (reinterpret_cast<uintptr_t>(X) | (unsigned long long)(m * elem_bytes)) % 64 == 0;
+}
+
 struct LhLds {
   double s[LH_FOLD_ROWS][LH_COLS];
   unsigned k[LH_FOLD_ROWS][LH_COLS];
@@ -93,7 +98,9 @@ __device__ __forceinline__ float lh_row_max(float x) {
 // itself (SC values of v per thread), workgroup 0 files the result record; SC = 0: a search
 // kernel ran before and the record is read.  X may alias Y (a thread reads and writes the same
 // elements only).
-template <typename T, int NV, int SC, int COLS = LH_COLS>
+// EVEN: every stripe's runs lie on whole 64-byte sectors of X (lh_even_rows); otherwise rows may start
+// anywhere.  (Two builds: with the ragged form's tests and stores beside it the even one lost 1 to 2 %.)
+template <typename T, int NV, int SC, int COLS, bool EVEN>
 __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, long long m, const Ws& ws,
                                               float* __restrict__ u_out, unsigned char* __restrict__ mask_out,
                                               double seed_eta, int outer, long long bid) {
@@ -107,9 +114,18 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
   const int wave = tid / WAVE;
   const int cw = tid % CW;            // which 16-byte piece of the stripe's run
   const int rl = tid / CW;            // row lane
-  const long long col0 = bid * COLS + (long long)cw * VEC;
-  const bool lane_ok = col0 < m;      // (m is a multiple of VEC: a lane's columns exist together)
-  const long long col0c = lane_ok ? col0 : m - VEC;   // a lane past the end shadows the last columns
+  // The stripe is COLS whole columns.  Ragged rows: the last stripe ends with the row and overlaps the
+  // stripe before it (in a row shorter than a stripe the last lanes overlap their neighbours instead;
+  // m >= VEC).  What a column gives does not depend on who computes it, so the overlap is loaded and
+  // summed like the rest, by both with the same values, and only its owner stores it and publishes
+  // its threshold.  Even rows: a lane past the end shadows the last columns and stores nothing.
+  const long long own0 = bid * COLS;                 // first column the workgroup owns
+  const long long s0 = EVEN || own0 + COLS <= m ? own0 : (m < COLS ? 0 : m - COLS);   // first column of the stripe
+  const long long want = s0 + (long long)cw * VEC;
+  const long long col0c = want + VEC <= m ? want : m - VEC;   // the lane's columns: col0c .. col0c + VEC - 1
+  const int lc = EVEN ? cw * VEC : (int)(col0c - s0);         // ... and their place in the stripe
+  const long long mine0 = want > own0 ? want : own0;
+  const int skip = mine0 - col0c < VEC ? (int)(mine0 - col0c) : VEC;   // leading columns somebody else owns
   // Byte offsets of the thread's elements from the start of the matrix, in 32 bits (the host
   // sends at most lh_max_elems<T>() elements here): one address register per access instead of two.
   const unsigned off0 = (unsigned)(((long long)rl * m + col0c) * (long long)sizeof(T));
@@ -122,8 +138,8 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
   auto request_rows = [&](auto first, auto last) {   // (compile-time bounds: raw[] must stay in registers)
 #pragma unroll
     for (int u = decltype(first)::value; u < decltype(last)::value; ++u) {
-      const unsigned off = rl + u * RL < n ? off0 + (unsigned)u * step : off_last;
-      raw[u] = *reinterpret_cast<const Pack<T, VEC>*>(ybytes + off);
+      const unsigned off = rl + u * RL < (int)n ? off0 + (unsigned)u * step : off_last;
+      raw[u] = load_pack<T, VEC>(reinterpret_cast<const T*>(ybytes + off));
     }
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -135,10 +151,58 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
   using RN = std::integral_constant<int, ROWS>;
   auto request_stripe = [&]() { request_rows(R0(), RN()); };
 
+  // Stores the lane's own columns of its rows: value(u, k) for row u, column k.  Even rows are streamed
+  // past the caches.  Ragged runs end in two partly written sectors each, which the neighbouring
+  // stripes (on the same XCD, see stripe_of_workgroup) complete: ordinary stores, so that the L2 can
+  // merge them (2001 x 3003: 38 against 48 us).  (There the offset and the row are made opaque in
+  // each branch: formed ahead of both, the addresses and row tests of all rows would sit in registers
+  // beside the held data, which then spill.)
+  auto store_rows = [&](auto value) {
+    const int rows = (int)n;
+    if constexpr (EVEN) {
+      if (skip != 0) return;
+#pragma unroll
+      for (int u = 0; u < ROWS; ++u) {
+        if (rl + u * RL < rows) {
+          float f[VEC];
+#pragma unroll
+          for (int k = 0; k < VEC; ++k) f[k] = value(u, k);
+          store_row<VEC, true>(reinterpret_cast<T*>(reinterpret_cast<char*>(X) + (off0 + (unsigned)u * step)), f);
+        }
+      }
+    } else {
+      unsigned at = off0;
+      int row = rl;
+      if (skip == 0) {
+        asm volatile("" : "+v"(at), "+v"(row));
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+          if (row + u * RL < rows) {
+            float f[VEC];
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) f[k] = value(u, k);
+            store_row<VEC, false>(reinterpret_cast<T*>(reinterpret_cast<char*>(X) + (at + (unsigned)u * step)), f);
+          }
+        }
+      } else {
+        asm volatile("" : "+v"(at), "+v"(row));
+#pragma unroll
+        for (int u = 0; u < ROWS; ++u) {
+          if (row + u * RL < rows) {
+            T* p = reinterpret_cast<T*>(reinterpret_cast<char*>(X) + (at + (unsigned)u * step));
+#pragma unroll
+            for (int k = 0; k < VEC; ++k)
+              if (k >= skip) store_one_nt(p + k, (T)value(u, k));
+          }
+        }
+      }
+    }
+  };
+
   // The owner of column c of the stripe: thread c.
-  const bool owner = tid < COLS;
-  const long long j = bid * COLS + tid;
-  const long long jj = (owner && j < m) ? j : 0;
+  const long long j = s0 + tid;
+  const bool owner = tid < COLS && j >= own0 && j < m;
+  const long long jj = owner ? j : 0;
   double vj = 0.0;
 
   Top top;
@@ -172,41 +236,32 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
   unsigned kprev = NO_COUNT;
   if (owner) {
     if constexpr (SC > 0) vj = ws.v[jj];
-    uj = j < m ? radius_of(ws, jj, vj, top) : 0.0;
-    mine = j < m && !inside && uj > 0.0;
+    uj = radius_of(ws, jj, vj, top);
+    mine = !inside && uj > 0.0;
     open = mine;
-    if (j < m) {
-      if (u_out) u_out[j] = (float)uj;
-      if (mask_out) mask_out[j] = uj > 0.0 ? 1 : 0;
-    }
+    if (u_out) u_out[j] = (float)uj;
+    if (mask_out) mask_out[j] = uj > 0.0 ? 1 : 0;
   }
   if constexpr (SC == 0) {
     // The search ran ahead, so the radii are known early: a stripe whose columns are all dropped
     // (the sparse results the projection is used for) is zeroed, and three quarters of it are
     // never read (the first quarter was requested with the radii, so that a stripe that is
     // needed does not wait twice).
-    const bool need = inside || __syncthreads_or((owner && j < m && uj > 0.0) ? 1 : 0) != 0;
+    const bool need = inside || __syncthreads_or((owner && uj > 0.0) ? 1 : 0) != 0;
     if (!need) {
-      if (lane_ok) {
-        float zero[VEC];
-#pragma unroll
-        for (int k = 0; k < VEC; ++k) zero[k] = 0.0f;
-#pragma unroll
-        for (int u = 0; u < ROWS; ++u)
-          if (rl + u * RL < n) store_row_nt<VEC, true>(reinterpret_cast<T*>(reinterpret_cast<char*>(X) + (off0 + (unsigned)u * step)), zero);
-      }
+      store_rows([](int, int) { return 0.0f; });
       return;
     }
     request_rows(RE(), RN());
   }
   // (the starting guess only now: with the search ahead, the rest of the stripe is on its way)
   // a dropped column maps to zero: threshold +inf; inside the ball nothing moves: threshold 0
-  if (owner) t = mine ? l11_guess(vj, uj, n, lb) : (inside ? 0.0 : HUGE_VAL);
+  t = mine ? l11_guess(vj, uj, n, lb) : (inside ? 0.0 : HUGE_VAL);   // (the same for a column somebody else owns)
 
   float held[ROWS][VEC];
 #pragma unroll
   for (int u = 0; u < ROWS; ++u) {
-    const bool row_ok = rl + (long long)u * RL < n;
+    const bool row_ok = rl + u * RL < (int)n;
 #pragma unroll
     for (int k = 0; k < VEC; ++k) held[u][k] = row_ok ? (float)raw[u].e[k] : 0.0f;   // |0| is never above a threshold
   }
@@ -226,7 +281,7 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
       for (int k = 0; k < VEC; ++k) hm[k] = lh_row_max<CW>(hm[k]);
       if ((lane & 15) < CW) {
 #pragma unroll
-        for (int k = 0; k < VEC; ++k) lds.s[wave * 4 + lane / 16][cw * VEC + k] = (double)hm[k];
+        for (int k = 0; k < VEC; ++k) lds.s[wave * 4 + lane / 16][lc + k] = (double)hm[k];
       }
       __syncthreads();
       // (the fold over the partial rows: the 64 lanes of the first wavefront take a quarter of the
@@ -238,7 +293,7 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
         amax = fmax(amax, __shfl_xor(amax, 16));
         amax = fmax(amax, __shfl_xor(amax, 32));
       }
-      if (owner) {
+      if (tid < COLS) {
         if (mine) {
           if (amax - uj > lb) lb = amax - uj;
           if (t <= lb || t >= amax) {   // the guess is no better than the bound, or beyond every entry
@@ -253,7 +308,7 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
     for (;;) {
       float ct[VEC];
 #pragma unroll
-      for (int k = 0; k < VEC; ++k) ct[k] = lds.ct[cw * VEC + k];
+      for (int k = 0; k < VEC; ++k) ct[k] = lds.ct[lc + k];
       double s[VEC];
       unsigned cnt[VEC];
 #pragma unroll
@@ -277,8 +332,8 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
       if ((lane & 15) < CW) {
 #pragma unroll
         for (int k = 0; k < VEC; ++k) {
-          lds.s[wave * 4 + lane / 16][cw * VEC + k] = s[k];
-          lds.k[wave * 4 + lane / 16][cw * VEC + k] = cnt[k];
+          lds.s[wave * 4 + lane / 16][lc + k] = s[k];
+          lds.k[wave * 4 + lane / 16][lc + k] = cnt[k];
         }
       }
       __syncthreads();
@@ -315,7 +370,7 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
       if (!__syncthreads_or((owner && open) ? 1 : 0)) break;
     }
   }
-  if (owner) {
+  if (tid < COLS) {
     const float th = (float)t;
     lds.th[tid] = th;
     lds.tl[tid] = t < HUGE_VAL ? (float)(t - (double)th) : 0.0f;
@@ -325,24 +380,13 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
     }
   }
   __syncthreads();
-  if (!lane_ok) return;
   float th[VEC], tl[VEC];
 #pragma unroll
   for (int k = 0; k < VEC; ++k) {
-    th[k] = lds.th[cw * VEC + k];
-    tl[k] = lds.tl[cw * VEC + k];
+    th[k] = lds.th[lc + k];
+    tl[k] = lds.tl[lc + k];
   }
-  char* const xbytes = reinterpret_cast<char*>(X);
-#pragma unroll
-  for (int u = 0; u < ROWS; ++u) {
-    if (rl + u * RL < n) {
-      float f[VEC];
-#pragma unroll
-      for (int k = 0; k < VEC; ++k)
-        f[k] = copysignf(fmaxf((fabsf(held[u][k]) - th[k]) - tl[k], 0.0f), held[u][k]);
-      store_row_nt<VEC, true>(reinterpret_cast<T*>(xbytes + (off0 + (unsigned)u * step)), f);
-    }
-  }
+  store_rows([&](int u, int k) { return copysignf(fmaxf((fabsf(held[u][k]) - th[k]) - tl[k], 0.0f), held[u][k]); });
 }
 
 // Registers: 32 values per thread leave room for two workgroups per CU, 128 for one.  64 fit two
@@ -352,11 +396,11 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
 // PACKED picks the two-per-CU build.
 constexpr int lh_min_waves(int nv, bool packed) { return nv <= 32 ? 4 : nv <= 64 ? (packed ? 4 : 2) : 2; }
 
-template <typename T, int NV, int SC, bool PACKED = false, int COLS = LH_COLS>
+template <typename T, int NV, int SC, bool EVEN, bool PACKED = false, int COLS = LH_COLS>
 __global__ __launch_bounds__(LH_WG, lh_min_waves(NV, PACKED)) void l11_held_kernel(
     const T* Y, T* X, long long n, long long m, Ws ws, float* __restrict__ u_out,
     unsigned char* __restrict__ mask_out, double seed_eta, int outer) {
-  l11_held_body<T, NV, SC, COLS>(Y, X, n, m, ws, u_out, mask_out, seed_eta, outer,
+  l11_held_body<T, NV, SC, COLS, EVEN>(Y, X, n, m, ws, u_out, mask_out, seed_eta, outer,
                                  stripe_of_workgroup(blockIdx.x, gridDim.x));
 }
 

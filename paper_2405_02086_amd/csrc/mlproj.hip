@@ -65,6 +65,16 @@ static int pick_vec(const void* Y, long long row_len, int elem_bytes = 4) {
   return (row_len % wide == 0 && aligned(Y, 16)) ? wide : 1;
 }
 
+// Whether the column kernels read a row in 16-byte pieces (the wide form of LaneCols) or element by
+// element.  The wide form takes any address; on rows of a fraction of a tile, most of whose lanes
+// are idle, the ragged lane's extra stores outweigh the wider loads unless the elements are 16-bit
+// (70000 rows, l1,inf, element by element / wide, us: fp32 33 columns 25.6 / 28.7, 130 31.9 / 33.1,
+// 200 34.7 / 34.8; bf16 33 columns 34.2 / 51.1, 201 41.0 / 35.4, 403 46.0 / 41.1; and 5001 x 8195
+// bf16 61 / 54).  16-byte aligned rows were always wide.
+static bool wide_rows(const void* Y, long long m, int elem_bytes) {
+  return pick_vec(Y, m, elem_bytes) > 1 || m >= (elem_bytes == 4 ? WAVE * 4 : WAVE);
+}
+
 static int workspace_bytes_impl(int variant, long long d0, long long d1, long long d2,
                                 size_t* out) {
   if (!out) return MLPROJ_ERR_NULL_POINTER;
@@ -267,11 +277,8 @@ static int run_bilevel(const T* Y, T* X, long long n, long long m, float eta,
     return st;
   if (!aligned(Y, sizeof(T)) || (X && !aligned(X, sizeof(T)))) return MLPROJ_ERR_ALIGNMENT;
   if (!aligned(workspace, 256)) return MLPROJ_ERR_WORKSPACE;
-  // Every lane owns WIDE columns; rows that are not 16-byte aligned are read element-wise
-  // (the strided form of LaneCols), and a misaligned X alone only narrows the stores.  The
-  // geometry depends on n and m only, so the two stages of a split call agree on it.
-  const bool wide = pick_vec(Y, m, (int)sizeof(T)) == WIDE;
-  const bool x_vec = !X || aligned(X, 16);
+  // (the geometry depends on n and m only, so the two stages of a split call agree on it)
+  const bool wide = wide_rows(Y, m, (int)sizeof(T));
   const Geometry g = plan_columns(n, m, WIDE, Q);
   if (g.tiles * g.groups > MAX_GRID) return MLPROJ_ERR_TOO_LARGE;
   const Layout L = layout_for(g, m, Q);
@@ -298,7 +305,7 @@ static int run_bilevel(const T* Y, T* X, long long n, long long m, float eta,
     // from Y, a single one when they overlap)
     TinyPlan tp;
     const bool apart = X && (X + n * m <= Y || Y + n * m <= X);
-    if (mode == MODE_PROJECT && stages == STAGE_ALL && wide && x_vec && !weights && tiny_plan(n, m, WIDE, &tp)) {
+    if (mode == MODE_PROJECT && stages == STAGE_ALL && !weights && tiny_plan(n, m, WIDE, &tp)) {
       mark(stream);
       launch((tiny_kernel<Q, T, WIDE>), dim3(apart ? (unsigned)tp.slots : 1u), dim3(TINY_WG), stream, Y, X, n, m,
                          (double)eta, outer, tp.cw, ws, v_out, u_out, mask_out, apart ? 0 : 1);
@@ -306,7 +313,7 @@ static int run_bilevel(const T* Y, T* X, long long n, long long m, float eta,
       return launch_status();
     }
   }
-  // l1,1 on at most 4096 rows (16-byte aligned rows, the whole call at once): after the aggregate
+  // l1,1 on at most 4096 rows (of at least 16 bytes, the whole call at once): after the aggregate
   // pass one kernel holds 16 whole columns per workgroup in registers, runs the inner searches
   // there, and maps and stores from the same registers (l11held.h)
   int held_values = 0;
@@ -314,14 +321,15 @@ static int run_bilevel(const T* Y, T* X, long long n, long long m, float eta,
   if constexpr (Q == Q1) {
     // (measured: ahead of the lock-step sweeps up to 64M elements, 57 against 97 us at 4096 x 4096,
     // 108 against 146 at 4096 x 8192, 219 against 227 at 4096 x 16384, and far ahead where most
-    // columns are dropped, whose stripes are not even read; behind at 128M.  A forced sweep count,
-    // the test hook, keeps the sweeps.)
-    if (mode == MODE_PROJECT && stages == STAGE_ALL && wide && x_vec &&
+    // columns are dropped, whose stripes are not even read; behind at 128M.  Rows that are not
+    // 16-byte aligned: 38 against 65 us at 2001 x 3003, 21 against 27 at 1001 x 333.  A forced sweep
+    // count, the test hook, keeps the sweeps.)
+    if (mode == MODE_PROJECT && stages == STAGE_ALL && m >= WIDE &&
         n * m <= lh_max_elems<T>() && g_l11_sweeps.load(std::memory_order_relaxed) == 0)
       held_values = lh_values_for<T>(n);
     // (fp32 up to 8192 rows: stripes of 8 columns)
     if constexpr (sizeof(T) == 4) {
-      if (held_values == 0 && mode == MODE_PROJECT && stages == STAGE_ALL && wide && x_vec && n * m <= lh_max_elems<T>() &&
+      if (held_values == 0 && mode == MODE_PROJECT && stages == STAGE_ALL && m >= WIDE && n * m <= lh_max_elems<T>() &&
           g_l11_sweeps.load(std::memory_order_relaxed) == 0 && l11_narrow_stripes_fit(n, m)) {
         held_values = 128;
         held_cols = LH_COLS_NARROW;
@@ -388,25 +396,34 @@ static int run_bilevel(const T* Y, T* X, long long n, long long m, float eta,
         const double seed_eta = seeded ? (double)eta : -1.0;
         // (64 values per thread: two workgroups per CU when there are more stripes than CUs)
         const bool packed = held_values == 64 && cdiv(m, LH_COLS) > compute_units();
+        const bool even = lh_even_rows(X, m, (int)sizeof(T));
+        auto go = [&](auto values, auto sc, auto packed_build, auto cols) {
+          constexpr int NV = decltype(values)::value, SC = decltype(sc)::value, COLS = decltype(cols)::value;
+          constexpr bool PACKED = decltype(packed_build)::value;
+          if (even) launch((l11_held_kernel<T, NV, SC, true, PACKED, COLS>), hgrid, hblock, stream, Y, X, n, m, ws, u_out, mask_out, seed_eta, outer);
+          else launch((l11_held_kernel<T, NV, SC, false, PACKED, COLS>), hgrid, hblock, stream, Y, X, n, m, ws, u_out, mask_out, seed_eta, outer);
+        };
+        auto go_search = [&](auto values, auto packed_build, auto cols) {
+          if (seeded) go(values, std::integral_constant<int, LH_SEARCH_CACHE>(), packed_build, cols);
+          else go(values, std::integral_constant<int, 0>(), packed_build, cols);
+        };
+        using Stripe = std::integral_constant<int, LH_COLS>;
         bool narrow_done = false;
         if constexpr (sizeof(T) == 4) {
           if (held_cols == LH_COLS_NARROW) {
-            if (seeded) launch((l11_held_kernel<T, 128, LH_SEARCH_CACHE, false, LH_COLS_NARROW>), hgrid, hblock, stream, Y, X, n, m, ws, u_out, mask_out, seed_eta, outer);
-            else launch((l11_held_kernel<T, 128, 0, false, LH_COLS_NARROW>), hgrid, hblock, stream, Y, X, n, m, ws, u_out, mask_out, seed_eta, outer);
+            go_search(std::integral_constant<int, 128>(), std::false_type(), std::integral_constant<int, LH_COLS_NARROW>());
             narrow_done = true;
           }
         }
         if (narrow_done) {
-        } else if (seeded) {
-          if (held_values == 32) launch((l11_held_kernel<T, 32, LH_SEARCH_CACHE>), hgrid, hblock, stream, Y, X, n, m, ws, u_out, mask_out, seed_eta, outer);
-          else if (packed) launch((l11_held_kernel<T, 64, LH_SEARCH_CACHE, true>), hgrid, hblock, stream, Y, X, n, m, ws, u_out, mask_out, seed_eta, outer);
-          else if (held_values == 64) launch((l11_held_kernel<T, 64, LH_SEARCH_CACHE>), hgrid, hblock, stream, Y, X, n, m, ws, u_out, mask_out, seed_eta, outer);
-          else launch((l11_held_kernel<T, 128, LH_SEARCH_CACHE>), hgrid, hblock, stream, Y, X, n, m, ws, u_out, mask_out, seed_eta, outer);
+        } else if (held_values == 32) {
+          go_search(std::integral_constant<int, 32>(), std::false_type(), Stripe());
+        } else if (packed) {
+          go_search(std::integral_constant<int, 64>(), std::true_type(), Stripe());
+        } else if (held_values == 64) {
+          go_search(std::integral_constant<int, 64>(), std::false_type(), Stripe());
         } else {
-          if (held_values == 32) launch((l11_held_kernel<T, 32, 0>), hgrid, hblock, stream, Y, X, n, m, ws, u_out, mask_out, seed_eta, outer);
-          else if (packed) launch((l11_held_kernel<T, 64, 0, true>), hgrid, hblock, stream, Y, X, n, m, ws, u_out, mask_out, seed_eta, outer);
-          else if (held_values == 64) launch((l11_held_kernel<T, 64, 0>), hgrid, hblock, stream, Y, X, n, m, ws, u_out, mask_out, seed_eta, outer);
-          else launch((l11_held_kernel<T, 128, 0>), hgrid, hblock, stream, Y, X, n, m, ws, u_out, mask_out, seed_eta, outer);
+          go_search(std::integral_constant<int, 128>(), std::false_type(), Stripe());
         }
         mark(stream);
         return launch_status();
@@ -475,18 +492,17 @@ static int run_bilevel(const T* Y, T* X, long long n, long long m, float eta,
   }
   if (stages & STAGE_APPLY) {
     mark(stream);
-    if (fuse_big && wide && x_vec)
-      launch((colmap_kernel<Q, T, WIDE, false, true, SEARCH_CACHE_BIG>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
-    else if (fuse_big && wide)
-      launch((colmap_kernel<Q, T, WIDE, false, false, SEARCH_CACHE_BIG>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
+    const bool even = wide && m % WIDE == 0;
+    if (fuse_big && even)   // (more than 4096 columns: wide whatever the alignment)
+      launch((colmap_kernel<Q, T, WIDE, MAP_EVEN, SEARCH_CACHE_BIG>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
     else if (fuse_big)
-      launch((colmap_kernel<Q, T, WIDE, true, false, SEARCH_CACHE_BIG>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
-    else if (wide && x_vec)
-      launch((colmap_kernel<Q, T, WIDE, false, true>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
+      launch((colmap_kernel<Q, T, WIDE, MAP_RAGGED, SEARCH_CACHE_BIG>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
+    else if (even)
+      launch((colmap_kernel<Q, T, WIDE, MAP_EVEN>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
     else if (wide)
-      launch((colmap_kernel<Q, T, WIDE, false, false>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
+      launch((colmap_kernel<Q, T, WIDE, MAP_RAGGED>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
     else
-      launch((colmap_kernel<Q, T, WIDE, true, false>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
+      launch((colmap_kernel<Q, T, WIDE, MAP_STRIDED>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
   }
   mark(stream);
   return launch_status();
@@ -526,7 +542,6 @@ static int run_trilevel(const T* Y, T* X, long long d0, long long d1, long long 
   if (!aligned(workspace, 256)) return MLPROJ_ERR_WORKSPACE;
   const long long len = d1 * d2;
   const int vec = pick_vec(Y, len, (int)sizeof(T));
-  const bool x_vec = aligned(X, 16);
   const Geometry g = plan_slabs(d0, len, vec);
   if (g.tiles * g.groups > MAX_GRID) return MLPROJ_ERR_TOO_LARGE;
   const Layout L = layout_for(g, d0, MLPROJ_L1INFINF);
@@ -544,10 +559,7 @@ static int run_trilevel(const T* Y, T* X, long long d0, long long d1, long long 
       mark(stream);
       launch(held_clear_kernel, dim3(1), dim3(WG), stream, ws.posts);
       mark(stream);
-      if (x_vec)
-        launch((held_slab_kernel<T, true>), dim3((unsigned)hp.nwg), dim3(HELD_WG), stream, Y, X, d0, len, hp, (double)eta, ws, ws.posts, v_out, u_out, mask_out, patience);
-      else
-        launch((held_slab_kernel<T, false>), dim3((unsigned)hp.nwg), dim3(HELD_WG), stream, Y, X, d0, len, hp, (double)eta, ws, ws.posts, v_out, u_out, mask_out, patience);
+      launch((held_slab_kernel<T>), dim3((unsigned)hp.nwg), dim3(HELD_WG), stream, Y, X, d0, len, hp, (double)eta, ws, ws.posts, v_out, u_out, mask_out, patience);
       mark(stream);
       return launch_status();
     }
@@ -568,12 +580,10 @@ static int run_trilevel(const T* Y, T* X, long long d0, long long d1, long long 
     launch_search(ws, d0, (double)eta, MODE_PROJECT, MLPROJ_OUTER_L1, nullptr, stream);
   }
   mark(stream);
-  if (vec == WIDE && x_vec)
-    launch((slabmap_kernel<T, WIDE, true>), grid, block, stream, Y, X, d0, len, g, ws, u_out, mask_out, fused_eta);
-  else if (vec == WIDE)
-    launch((slabmap_kernel<T, WIDE, false>), grid, block, stream, Y, X, d0, len, g, ws, u_out, mask_out, fused_eta);
+  if (vec == WIDE)
+    launch((slabmap_kernel<T, WIDE>), grid, block, stream, Y, X, d0, len, g, ws, u_out, mask_out, fused_eta);
   else
-    launch((slabmap_kernel<T, 1, false>), grid, block, stream, Y, X, d0, len, g, ws, u_out, mask_out, fused_eta);
+    launch((slabmap_kernel<T, 1>), grid, block, stream, Y, X, d0, len, g, ws, u_out, mask_out, fused_eta);
   mark(stream);
   return launch_status();
 }
@@ -605,7 +615,7 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
     if (!tiny_built<Q, T>()) return false;
     const mlproj_problem& p = pr[i];
     TinyPlan tp;
-    return pick_vec(p.Y, p.m, (int)sizeof(T)) == WIDE && aligned(p.X, 16) && tiny_plan(p.n, p.m, WIDE, &tp);
+    return tiny_plan(p.n, p.m, WIDE, &tp);
   };
   // l1,1 problems that a single call sends through the columns-in-registers kernel (see
   // run_bilevel) take the same kernel here, so that a batch gives the bits of its single calls:
@@ -614,7 +624,7 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
   auto held_values = [&](int i) {
     if constexpr (Q != Q1) return 0;
     const mlproj_problem& p = pr[i];
-    if (pick_vec(p.Y, p.m, (int)sizeof(T)) != WIDE || !aligned(p.X, 16) || p.n * p.m > lh_max_elems<T>() ||
+    if (p.m < WIDE || p.n * p.m > lh_max_elems<T>() ||
         g_l11_sweeps.load(std::memory_order_relaxed) != 0)
       return 0;
     const int wide_stripes = lh_values_for<T>(p.n);
@@ -637,7 +647,7 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
         b.Y = p.Y; b.X = p.X; b.ws = p.workspace;
         b.v_out = p.v_out; b.u_out = p.u_out; b.mask_out = p.mask_out;
         b.n = p.n; b.m = p.m; b.eta = (double)p.eta;
-        b.wide = 1; b.x_vec = 1;
+        b.wide = 1;
         b.whole = apart(k) ? 0 : 1;
         TinyPlan tp;
         tiny_plan(p.n, p.m, WIDE, &tp);
@@ -666,7 +676,7 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
         b.Y = p.Y; b.X = p.X; b.ws = p.workspace;
         b.v_out = p.v_out; b.u_out = p.u_out; b.mask_out = p.mask_out;
         b.n = p.n; b.m = p.m; b.eta = (double)p.eta;
-        b.wide = 1; b.x_vec = 1; b.whole = 0;
+        b.wide = 1; b.whole = 0;
         const Geometry g = plan_columns(p.n, p.m, WIDE, Q);
         agg.first[it.count] = a; a += (unsigned)(g.tiles * g.groups);
         red.first[it.count] = r; r += (unsigned)cdiv(p.m, SWG / reduce_parts(g.groups, fold_threads(g.groups)));
@@ -707,8 +717,7 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
       b.Y = p.Y; b.X = p.X; b.ws = p.workspace;
       b.v_out = p.v_out; b.u_out = p.u_out; b.mask_out = p.mask_out;
       b.n = p.n; b.m = p.m; b.eta = (double)p.eta;
-      b.wide = pick_vec(p.Y, p.m, (int)sizeof(T)) == WIDE ? 1 : 0;
-      b.x_vec = aligned(p.X, 16) ? 1 : 0;
+      b.wide = wide_rows(p.Y, p.m, (int)sizeof(T)) ? 1 : 0;
       b.whole = 0;
       const Geometry g = plan_columns(p.n, p.m, WIDE, Q);
       agg.first[it.count] = a; a += (unsigned)(g.tiles * g.groups);

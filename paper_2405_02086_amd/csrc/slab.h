@@ -44,7 +44,7 @@ __global__ __launch_bounds__(WG) void slabagg_kernel(const T* __restrict__ Y, lo
 
 // X_abc = sign(Y_abc) min(|Y_abc|, u_a).  The appendix form clips each fibre to
 // U2_ab = min(V_ab, u_a); since |Y_abc| <= V_ab the two clips give the same value.
-template <typename T, int VEC, bool XVEC>
+template <typename T, int VEC>
 __global__ __launch_bounds__(WG) void slabmap_kernel(const T* Y, T* X, long long d0,
                                                      long long len, Geometry g, Ws ws,
                                                      float* __restrict__ u_out,
@@ -81,7 +81,7 @@ __global__ __launch_bounds__(WG) void slabmap_kernel(const T* Y, T* X, long long
     for (int r = 0; r < 4; ++r) {
 #pragma unroll
       for (int k = 0; k < VEC; ++k) x[r][k] = copysignf(fminf(fabsf(x[r][k]), u), x[r][k]);
-      store_row_nt<VEC, XVEC>(q + i + r * STEP, x[r]);
+      store_row_nt<VEC>(q + i + r * STEP, x[r]);
     }
   }
   for (; i < hi; i += STEP) {
@@ -89,7 +89,7 @@ __global__ __launch_bounds__(WG) void slabmap_kernel(const T* Y, T* X, long long
     load_row<VEC>(p + i, x);
 #pragma unroll
     for (int k = 0; k < VEC; ++k) x[k] = copysignf(fminf(fabsf(x[k]), u), x[k]);
-    store_row_nt<VEC, XVEC>(q + i, x);
+    store_row_nt<VEC>(q + i, x);
   }
 }
 

@@ -48,8 +48,8 @@ struct TinyPlan {
 
 // Whether an n x m matrix with `vec` elements per 16-byte chunk fits, and how.
 __host__ __device__ static inline bool tiny_plan(long long n, long long m, int vec, TinyPlan* p) {
-  if (m % vec != 0 || m > FUSED_SEARCH_MAX) return false;
-  const long long cpr = m / vec;
+  if (m < vec || m > FUSED_SEARCH_MAX) return false;
+  const long long cpr = cdiv(m, vec);
   if (cpr > TINY_WG) return false;
   int cw = 1;
   while (cw < cpr) cw *= 2;
@@ -81,16 +81,21 @@ __device__ __forceinline__ void tiny_body(const T* Y, T* X, long long n,
   const int rl = TINY_WG / cw;
   const int tc = threadIdx.x % cw;
   const int tr = threadIdx.x / cw;
-  const long long cpr = m / VEC;
+  const long long cpr = cdiv(m, VEC);
   const bool col_ok = tc < cpr;
-  const long long at = (col_ok ? tc : cpr - 1) * VEC;   // a lane without a chunk shadows the last one
+  // The chunk that would run past the end of the row is the row's last 16 bytes instead: its first
+  // `shadow` elements are its neighbour's, aggregated there, and stored by both with the same
+  // values (every element is in registers before the first store).  A lane without a chunk
+  // shadows that last one.
+  const long long at = ((long long)tc + 1) * VEC <= m ? (long long)tc * VEC : m - VEC;
+  const int shadow = col_ok ? (int)(tc * VEC - at) : VEC;
   const int width = cw * VEC;
 
   Pack<T, VEC> raw[TINY_SLOTS];
 #pragma unroll
   for (int k = 0; k < TINY_SLOTS; ++k) {
     const long long row = tr + (long long)k * rl;
-    raw[k] = *reinterpret_cast<const Pack<T, VEC>*>(Y + (row < n ? row : n - 1) * m + at);
+    raw[k] = load_pack<T, VEC>(Y + (row < n ? row : n - 1) * m + at);
   }
   __builtin_amdgcn_sched_barrier(0);
   Acc acc[VEC];
@@ -104,7 +109,8 @@ __device__ __forceinline__ void tiny_body(const T* Y, T* X, long long n,
     }
   }
 #pragma unroll
-  for (int e = 0; e < VEC; ++e) sm_part[tr * width + tc * VEC + e] = acc[e];
+  for (int e = 0; e < VEC; ++e)
+    if (e >= shadow) sm_part[tr * width + at + e] = acc[e];
   __syncthreads();
   for (int c = threadIdx.x; c < width; c += TINY_WG) {
     Acc a = sm_part[c];
@@ -131,7 +137,7 @@ __device__ __forceinline__ void tiny_body(const T* Y, T* X, long long n,
   double par[VEC];   // q = 2: scale u_j / v_j
 #pragma unroll
   for (int e = 0; e < VEC; ++e) {
-    const double vj = (double)sm_v[tc * VEC + e];
+    const double vj = (double)sm_v[at + e];
     const double uj = radius(vj, top);
     uf[e] = (float)uj;
     par[e] = (Q == Q2 && vj > 0.0) ? uj / vj : 0.0;
@@ -143,14 +149,14 @@ __device__ __forceinline__ void tiny_body(const T* Y, T* X, long long n,
     if (whole || k == (int)bid) {
       const long long row = tr + (long long)k * rl;
       if (row < n) {
-        float f[VEC];
+        Pack<T, VEC> f;
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
           const float y = (float)raw[k].e[e];
-          if constexpr (Q == QINF) f[e] = copysignf(fminf(fabsf(y), uf[e]), y);
-          else f[e] = (float)((double)y * par[e]);
+          if constexpr (Q == QINF) f.e[e] = (T)copysignf(fminf(fabsf(y), uf[e]), y);
+          else f.e[e] = round_to<T>((double)y * par[e]);
         }
-        store_row_nt<VEC>(X + row * m + at, f);
+        store_pack(X + row * m + at, f);
       }
     }
   }

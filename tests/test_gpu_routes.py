@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 from oracle import mlproj_oracle as orc
-from test_gpu_parity import ATOL, QNAME, RTOL, STORE_DTYPES, check_stored, eta_for, stored_input, mp  # noqa: F401
+from test_gpu_parity import ATOL, QNAME, RTOL, STORE_DTYPES, check_stored, eta_for, run_stored, stored_input, mp  # noqa: F401
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -24,3 +24,36 @@ def test_batch_map_grid_is_planned_for_the_launch(mp, q, shapes):
         assert torch.equal(mp.bilevel_proj_stored(Y, eta, q), X)
     ref = orc.bilevel(Yd[0].cpu().numpy(), float(np.float32(etas[0])), q)
     np.testing.assert_allclose(Xs[0].cpu().numpy(), ref["X"], rtol=RTOL, atol=ATOL)
+
+
+# Row lengths around the 16-byte pieces, the tiles (256 fp32, 512 16-bit columns) and the 16- and 8-column stripes;
+# heights around the rows a workgroup holds.  At most 128 KiB takes the one-kernel form (q = inf, 2).
+RAGGED = [("f32", (5, 5)), ("f32", (7, 4)), ("f32", (100, 77)), ("f32", (300, 257)), ("f32", (129, 259)), ("f32", (1025, 511)),
+          ("f32", (4096, 9)), ("f32", (2049, 31)), ("f32", (1, 70001)), ("f32", (40, 5003)), ("f32", (4097, 15)),
+          ("f32", (8192, 7)), ("f32", (6000, 1001)), ("f32", (9000, 301)), ("f32", (33, 17)),
+          ("bf16", (9, 9)), ("bf16", (200, 65)), ("bf16", (700, 513)), ("bf16", (2047, 135)), ("bf16", (65, 4103)),
+          ("f16", (40, 1031)), ("f16", (5000, 71)), ("f16", (300, 15))]
+
+
+@pytest.mark.parametrize("q", ["inf", 1, 2])
+@pytest.mark.parametrize("storage,shape", RAGGED)
+def test_rows_of_any_length_and_address(mp, q, storage, shape):
+    """Rows that start anywhere, read and written in 16-byte pieces: out of place, in place, with Y and X off their
+    16-byte boundaries by different amounts."""
+    Y = stored_input(shape, storage, 7)
+    eta = eta_for(Y, q, 0.2)
+    ref = orc.bilevel_stored(Y, eta, q, storage)
+    for kw in ({}, {"inplace": True}, {"offset": 1, "x_offset": 3}, {"offset": 2, "inplace": True}):
+        check_stored(run_stored(mp, Y, eta, q, storage, **kw), ref, q, storage)
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+@pytest.mark.parametrize("q", ["inf", 1, 2])
+def test_batch_of_ragged_rows_gives_the_bits_of_the_single_calls(mp, q, storage):
+    dev = torch.device("cuda:0")
+    dt = getattr(torch, STORE_DTYPES[storage])
+    shapes = [(100, 77), (300, 257), (2049, 31), (33, 17), (700, 1001), (64, 64), (3, 3), (40, 5003)]
+    Yd = [torch.from_numpy(stored_input(sh, storage, i)).to(dev).to(dt) for i, sh in enumerate(shapes)]
+    etas = [eta_for(Y.float().cpu().numpy(), q, 0.2) for Y in Yd]
+    for Y, eta, X in zip(Yd, etas, mp.bilevel_proj_batch(Yd, etas, q)):
+        assert torch.equal(mp.bilevel_proj_stored(Y, eta, q), X)
