@@ -57,3 +57,15 @@ def test_batch_of_ragged_rows_gives_the_bits_of_the_single_calls(mp, q, storage)
     etas = [eta_for(Y.float().cpu().numpy(), q, 0.2) for Y in Yd]
     for Y, eta, X in zip(Yd, etas, mp.bilevel_proj_batch(Yd, etas, q)):
         assert torch.equal(mp.bilevel_proj_stored(Y, eta, q), X)
+
+
+@pytest.mark.parametrize("q", ["inf", 2])
+@pytest.mark.parametrize("m", [4097, 6144, 6145, 8192, 8200, 14337, 16384])
+def test_search_over_part_of_its_register_slots(mp, q, m):
+    """The threshold search of 4097 to 16384 columns works through its slots in chunks of 2048 columns; many rounds
+    (a radius that keeps a handful of columns) and few."""
+    rng = np.random.default_rng(m)
+    Y = rng.random((37, m), dtype=np.float32)
+    for frac in (1e-5, 0.3):
+        eta = eta_for(Y, q, frac)
+        check_stored(run_stored(mp, Y, eta, q, "f32"), orc.bilevel_stored(Y, eta, q, "f32"), q, "f32")
