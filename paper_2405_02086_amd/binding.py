@@ -8,16 +8,17 @@ import ctypes
 import os
 import struct
 import subprocess
+import tempfile
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libmlproj.so")
-SRC_PATH = os.path.join(_HERE, "csrc", "mlproj.hip")
+SRC_PATHS = [os.path.join(_HERE, "csrc", name) for name in ("mlproj.hip", "heldmulti.hip")]
 
 L1INF, L11, L12, L1INFINF = 0, 1, 2, 3
 _VARIANTS = {"l1inf": L1INF, "l11": L11, "l12": L12, "tri": L1INFINF}
 
 HIPCC_FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-shared", "-fPIC",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     # keep the compiler from forming packed-fp32 VALU ops
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
@@ -31,15 +32,26 @@ class MlprojError(RuntimeError):
 
 
 def build(verbose=False):
-    """Compile csrc/mlproj.hip (one translation unit that includes csrc/*.h) for gfx950 into
-    libmlproj.so next to this file."""
+    """Compile the translation units csrc/*.hip (with the csrc/*.h they include) for gfx950, side by
+    side, and link them into libmlproj.so next to this file."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc] + HIPCC_FLAGS + ["-o", LIB_PATH, SRC_PATH]
-    proc = subprocess.run(cmd, capture_output=True, text=True)
-    if verbose or proc.returncode != 0:
-        print(" ".join(cmd))
-        print(proc.stdout + proc.stderr)
-    if proc.returncode != 0:
+    with tempfile.TemporaryDirectory() as tmp:
+        objects = [os.path.join(tmp, "%d.o" % i) for i in range(len(SRC_PATHS))]
+        commands = [[hipcc] + HIPCC_FLAGS + ["-c", "-o", o, src] for o, src in zip(objects, SRC_PATHS)]
+        running = [subprocess.Popen(c, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True) for c in commands]
+        said = [p.communicate()[0] for p in running]
+        link = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH] + objects
+        failed = any(p.returncode != 0 for p in running)
+        if not failed:
+            done = subprocess.run(link, capture_output=True, text=True)
+            commands.append(link)
+            said.append(done.stdout + done.stderr)
+            failed = done.returncode != 0
+        if verbose or failed:
+            for c, out in zip(commands, said):
+                print(" ".join(c))
+                print(out)
+    if failed:
         raise RuntimeError("hipcc failed building libmlproj.so")
     global _lib
     _lib = None

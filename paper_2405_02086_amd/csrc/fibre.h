@@ -25,13 +25,6 @@ __device__ __forceinline__ Pack<T, VEC> load_chunk(const T* p) {
   return *reinterpret_cast<const Pack<T, VEC>*>(p);
 }
 
-template <int Q>
-__device__ __forceinline__ void accumulate_d(double& a, double y) {
-  if constexpr (Q == QINF) a = fmax(a, fabs(y));
-  else if constexpr (Q == Q1) a += fabs(y);
-  else a = fma(y, y, a);
-}
-
 constexpr int FIB_UNROLL = 4;  // fibres a segment works on at once (x2 chunks each: loads in flight)
 
 // V[f] = || fibre f ||_q for nf contiguous fibres of len elements (len = nvec * VEC).

@@ -176,7 +176,7 @@ __device__ __forceinline__ void held_help(int piece, const T* __restrict__ Y, co
   held_fold_and_post(piece, mx, posts, true, sm_w);
 }
 
-__global__ __launch_bounds__(WG) void held_clear_kernel(unsigned* __restrict__ posts) {
+static __global__ __launch_bounds__(WG) void held_clear_kernel(unsigned* __restrict__ posts) {
   posts[threadIdx.x] = HELD_ABSENT;    // (HELD_MAX_WGS = WG words)
 }
 

@@ -1,0 +1,391 @@
+// mlproj: the kernels of the one-pass multi-level projection (see heldmulti.h for the design).
+#include "heldmulti.h"
+
+#include "common.h"
+#include "reduce.h"
+#include "search.h"
+
+namespace mlproj {
+
+__global__ __launch_bounds__(WG) void hm_clear_kernel(unsigned long long* __restrict__ posts, int n) {
+  const int i = blockIdx.x * WG + threadIdx.x;
+  if (i < n) posts[i] = HM_ABSENT;
+}
+
+// The chunks of one fibre that a lane holds.  Every load is unconditional (a chunk that does not exist
+// reads the fibre's first one, and is blanked); the elements a ragged last chunk shares with the one
+// before it are blanked there too: 0 adds nothing to a norm and is never above a threshold.
+template <typename T, int SEG, int KPF>
+struct HmLane {
+  static constexpr int VEC = 16 / (int)sizeof(T);
+  int sl;
+  __device__ __forceinline__ int at(const HmPlan& p, int k) const {   // element offset in the fibre
+    const int i = sl + k * SEG;
+    return i >= p.nvec ? 0 : (i == p.nvec - 1 ? p.len - VEC : i * VEC);
+  }
+  __device__ __forceinline__ int blank(const HmPlan& p, int k) const {   // leading elements that do not count
+    const int i = sl + k * SEG;
+    return i >= p.nvec ? VEC : (i == p.nvec - 1 ? p.dup : 0);
+  }
+  __device__ __forceinline__ void load(const HmPlan& p, const T* fibre, Pack<T, VEC> (&x)[KPF]) const {
+#pragma unroll
+    for (int k = 0; k < KPF; ++k) x[k] = load_pack<T, VEC>(fibre + at(p, k));
+  }
+  __device__ __forceinline__ void blank_out(const HmPlan& p, Pack<T, VEC> (&x)[KPF]) const {
+    if (p.nvec == KPF * SEG && p.dup == 0) return;   // (the same for the whole grid)
+#pragma unroll
+    for (int k = 0; k < KPF; ++k) {
+      const int b = blank(p, k);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) x[k].e[e] = e < b ? (T)0.0f : x[k].e[e];
+    }
+  }
+};
+
+// || fibre ||_q, the same in every lane of the segment for q = inf, lane 0's taken otherwise.
+template <int Q, typename T, int SEG, int KPF>
+__device__ __forceinline__ double hm_fibre_norm(const Pack<T, 16 / (int)sizeof(T)> (&x)[KPF]) {
+  constexpr int VEC = 16 / (int)sizeof(T);
+  if constexpr (Q == QINF) {
+    float a = 0.0f;
+#pragma unroll
+    for (int k = 0; k < KPF; ++k)
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) a = fmaxf(a, fabsf((float)x[k].e[e]));
+    return seg_max<SEG>((double)a);
+  } else {
+    double a = 0.0;
+#pragma unroll
+    for (int k = 0; k < KPF; ++k)
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) accumulate_d<Q>(a, (double)(float)x[k].e[e]);
+    const double s = seg_sum<SEG>(a);
+    return Q == Q2 ? sqrt(s) : s;
+  }
+}
+
+// The q2-norm of d1 fibre norms in LDS, by one wavefront, always in this order.
+__device__ __forceinline__ double hm_slab_norm(const double* v, int d1, int q2) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  double a = 0.0;
+  for (int i = lane; i < d1; i += WAVE) {
+    const double x = v[i];
+    a = q2 == QINF ? fmax(a, x) : q2 == Q1 ? a + x : fma(x, x, a);
+  }
+  if (q2 == QINF) return wave_max(a);
+  a = wave_sum(a);
+  return q2 == Q2 ? sqrt(a) : a;
+}
+
+// The radii of a slab's d1 fibres, by one wavefront: its fibre norms v (q2-norm nv) projected onto the
+// q2-ball of radius r (the map of fibre.h, see fibre_map_cached_kernel for the starting point).
+__device__ __forceinline__ void hm_slab_radii(const double* v, double* out, int d1, int q2, double nv, double r) {
+  const int lane = threadIdx.x & (WAVE - 1);
+  double par = 0.0;
+  if (q2 == Q2) {
+    par = nv > r ? r / nv : 1.0;
+  } else if (q2 == Q1 && nv > r) {
+    if (!(r > 0.0)) {
+      par = HUGE_VAL;
+    } else {
+      const double floor_t = (nv - r) / (double)d1;
+      const float guess = -0.75f * (float)(nv / (double)d1) * __logf((float)(r / nv));
+      bool first = (double)guess > floor_t;
+      par = first ? (double)guess : floor_t;
+      unsigned kprev = 0xffffffffu;
+      for (;;) {
+        double s = 0.0;
+        unsigned c = 0;
+        for (int i = lane; i < d1; i += WAVE) {
+          const double x = v[i];
+          if (x > par) { s += x; ++c; }
+        }
+        s = wave_sum(s);
+        c = wave_sum_u(c);
+        if (first) {
+          kprev = c > 0u ? c : 0xffffffffu;
+          par = c > 0u ? fmax((s - r) / (double)c, floor_t) : floor_t;
+          first = false;
+        } else if (c == 0u || c == kprev) {
+          break;
+        } else {
+          kprev = c;
+          const double t = (s - r) / (double)c;
+          if (t > par) par = t;
+        }
+      }
+    }
+  }
+  for (int i = lane; i < d1; i += WAVE) {
+    const double x = v[i];
+    out[i] = q2 == QINF ? fmin(x, r) : q2 == Q2 ? x * par : fmax(x - par, 0.0);
+  }
+}
+
+// (Keeps the widening of 16-bit elements where they are used: shared between the phases, or hoisted out
+// of a search, it doubles the registers of the held data.)
+template <typename T, int VEC, int KPF>
+__device__ __forceinline__ void hm_keep_stored(Pack<T, VEC> (&x)[KPF]) {
+  if constexpr (sizeof(T) == 2) {
+#pragma unroll
+    for (int k = 0; k < KPF; ++k) {
+      unsigned w[4];
+      __builtin_memcpy(w, &x[k], 16);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(w[i]));
+      __builtin_memcpy(&x[k], w, 16);
+    }
+  }
+}
+
+// above() of l11.h for t >= 0 (an infinite t gives a NaN: nothing is above it).
+__device__ __forceinline__ float hm_above(double t) {
+  const float f = (float)t;
+  return (double)f <= t ? __uint_as_float(__float_as_uint(f) + 1u) : f;
+}
+
+template <int Q, typename T, int SEG, int KPF>
+__global__ __launch_bounds__(HM_WG) void held_multi_kernel(const void* Yv, void* Xv, HmPlan p, int q2, double eta, int outer, Ws ws,
+                                                           unsigned long long* posts, float* __restrict__ v_out,
+                                                           float* __restrict__ u_out, unsigned patience) {
+  constexpr int VEC = 16 / (int)sizeof(T);
+  const T* const Y = static_cast<const T*>(Yv);
+  T* const X = static_cast<T*>(Xv);
+  constexpr int ROUNDS = hm_slots((int)sizeof(T)) / KPF;
+  constexpr int NSEG = HM_WG / SEG;
+  static_assert(NSEG * ROUNDS <= HM_MAX_FIBRES, "norms and radii of every held fibre fit their LDS arrays");
+  __shared__ double sm_v[HM_MAX_FIBRES];   // fibre norms
+  __shared__ double sm_r[HM_MAX_FIBRES];   // ... their radii (a helper's scratch before that)
+  __shared__ double sm_w[HM_MAX_SLABS];    // slab norms, of the whole tensor
+  __shared__ PairScratch<HM_WAVES> bs;
+  __shared__ unsigned char sm_missing[HM_MAX_WGS];
+  __shared__ unsigned sm_any;
+  const int tid = threadIdx.x;
+  const int wave = tid / WAVE, lane = tid & (WAVE - 1);
+  const int seg = tid / SEG;
+  const HmLane<T, SEG, KPF> hl{tid % SEG};
+  const int wg = blockIdx.x;
+  const int slab0 = wg * p.spw;
+  const int slabs = p.d0 - slab0 < p.spw ? p.d0 - slab0 : p.spw;
+  const int fibres = slabs * p.d1;
+  const long long origin = (long long)slab0 * p.d1 * p.len;
+
+  // 1. the share, into registers (a fibre that does not exist reads the last one)
+  Pack<T, VEC> d[ROUNDS][KPF];
+#pragma unroll
+  for (int j = 0; j < ROUNDS; ++j) {
+    if (j < p.rounds) {
+      const int f = j * NSEG + seg;
+      hl.load(p, Y + origin + (long long)(f < fibres ? f : fibres - 1) * p.len, d[j]);
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+
+  // 2. the norms of its fibres and slabs; the slabs' are posted
+#pragma unroll
+  for (int j = 0; j < ROUNDS; ++j) {
+    if (j < p.rounds) {
+      hl.blank_out(p, d[j]);
+      const double v = hm_fibre_norm<Q, T, SEG, KPF>(d[j]);
+      const int f = j * NSEG + seg;
+      if (hl.sl == 0 && f < fibres) sm_v[f] = v;
+    }
+  }
+  __syncthreads();
+  for (int s = wave; s < slabs; s += HM_WAVES) {
+    const double w = hm_slab_norm(sm_v + s * p.d1, p.d1, q2);
+    if (lane == 0)
+      __hip_atomic_exchange(posts + slab0 + s, (unsigned long long)__double_as_longlong(w), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+
+  // 3. everybody's slab norms
+  constexpr int WORDS = HM_MAX_SLABS / HM_WG;
+  unsigned taken = 0u;      // which of this thread's words are in sm_w
+  bool complete = false;
+  for (int round = 0; round < HELD_MAX_ROUNDS && !complete; ++round) {
+    if (tid == 0) sm_any = 0u;
+    if (tid < HM_MAX_WGS) sm_missing[tid] = 0;
+    __syncthreads();
+    for (unsigned spins = 0;; ++spins) {
+      bool all = true;
+#pragma unroll
+      for (int i = 0; i < WORDS; ++i) {
+        const int a = tid + i * HM_WG;
+        if (a < p.d0 && !(taken & (1u << i))) {
+          const unsigned long long x = __hip_atomic_load(posts + a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (x != HM_ABSENT) {
+            sm_w[a] = __longlong_as_double((long long)x);
+            taken |= 1u << i;
+          } else {
+            all = false;
+          }
+        }
+      }
+      if (__all(all) || spins >= patience) break;
+      __builtin_amdgcn_s_sleep(8);
+    }
+#pragma unroll
+    for (int i = 0; i < WORDS; ++i) {
+      const int a = tid + i * HM_WG;
+      if (a < p.d0 && !(taken & (1u << i))) {
+        sm_missing[a / p.spw] = 1;
+        sm_any = 1u;
+      }
+    }
+    __syncthreads();
+    complete = sm_any == 0u;
+    if (!complete) {
+      for (int i = 1; i <= p.nwg; ++i) {
+        const int g = (wg + i) % p.nwg;
+        if (!sm_missing[g]) continue;   // (uniform: an LDS flag)
+        // the share of workgroup g, its fibres and slabs normed in its own order
+        const int g_slab0 = g * p.spw;
+        const int g_slabs = p.d0 - g_slab0 < p.spw ? p.d0 - g_slab0 : p.spw;
+        const int g_fibres = g_slabs * p.d1;
+        const T* share = Y + (long long)g_slab0 * p.d1 * p.len;
+        for (int j = 0; j < p.rounds; ++j) {
+          const int f = j * NSEG + seg;
+          Pack<T, VEC> x[KPF];
+          hl.load(p, share + (long long)(f < g_fibres ? f : g_fibres - 1) * p.len, x);
+          hl.blank_out(p, x);
+          const double v = hm_fibre_norm<Q, T, SEG, KPF>(x);
+          if (hl.sl == 0 && f < g_fibres) sm_r[f] = v;
+        }
+        __syncthreads();   // (every thread's reads of Y are behind it: see held.h for why the look comes after)
+        for (int s = wave; s < g_slabs; s += HM_WAVES) {
+          const double w = hm_slab_norm(sm_r + s * p.d1, p.d1, q2);
+          unsigned long long* q = posts + g_slab0 + s;
+          if (lane == 0 && __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == HM_ABSENT)
+            __hip_atomic_exchange(q, (unsigned long long)__double_as_longlong(w), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+      }
+    }
+    __syncthreads();
+  }
+
+  // 4. tau, by every workgroup for itself
+  SearchOut o = search_block<WG, HM_MAX_SLABS / WG, HM_WG, double>(sm_w, p.d0, eta, MODE_PROJECT, outer, bs);
+  if (!complete) o.tau = __longlong_as_double(0x7ff8000000000000LL);   // never reached: make it loud
+  const Top top = top_of(o);
+  if (wg == 0) {
+    if (tid == 0) write_result(ws, o, nullptr);
+    for (int a = tid; a < p.d0; a += HM_WG) {
+      if (v_out) v_out[a] = (float)sm_w[a];
+      if (u_out) u_out[a] = (float)radius(sm_w[a], top);
+    }
+  }
+
+  // 5. the radii of the fibres
+  for (int s = wave; s < slabs; s += HM_WAVES) {
+    const double w = sm_w[slab0 + s];
+    hm_slab_radii(sm_v + s * p.d1, sm_r + s * p.d1, p.d1, q2, w, radius(w, top));
+  }
+  __syncthreads();
+
+  // 6. the fibres, from the registers
+#pragma unroll
+  for (int j = 0; j < ROUNDS; ++j) {
+    if (j < p.rounds) {
+      const int f = j * NSEG + seg;
+      const int fc = f < fibres ? f : fibres - 1;
+      const double nv = sm_v[fc], r = sm_r[fc];
+      double par = 0.0;
+      hm_keep_stored(d[j]);
+      if constexpr (Q == Q2) par = nv > r ? r / nv : 1.0;
+      if constexpr (Q == Q1) {
+        // (the fixed point of fibre_map_cached_kernel, on the elements as fp32: |x| > t is |x| >= above(t))
+        bool open = nv > r && r > 0.0 && f < fibres;
+        const double floor_t = open ? (nv - r) / (double)p.len : 0.0;
+        const float guess = open ? -0.75f * (float)(nv / (double)p.len) * __logf((float)(r / nv)) : 0.0f;
+        bool first = (double)guess > floor_t;
+        par = first ? (double)guess : floor_t;
+        if (nv > r && !(r > 0.0)) par = HUGE_VAL;
+        unsigned kprev = 0xffffffffu;
+        while (__any(open)) {
+          const float ct = hm_above(par);
+          double s = 0.0;
+          unsigned c = 0;
+          hm_keep_stored(d[j]);
+#pragma unroll
+          for (int k = 0; k < KPF; ++k)
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+              const float h = fabsf((float)d[j][k].e[e]);
+              const bool in = h >= ct;
+              s += (double)(in ? h : 0.0f);
+              c += in ? 1u : 0u;
+            }
+          s = seg_sum<SEG>(s);
+          c = seg_sum_u<SEG>(c);
+          const double t = (s - r) / (double)c;
+          if (open) {
+            if (first) {
+              kprev = c > 0u ? c : 0xffffffffu;
+              par = c > 0u ? fmax(t, floor_t) : floor_t;
+            } else if (c == 0u || c == kprev) {
+              open = false;
+            } else {
+              kprev = c;
+              if (t > par) par = t;
+            }
+          }
+          first = false;
+        }
+        hm_keep_stored(d[j]);
+      }
+      const float rf = (float)r;
+      T* out = X + origin + (long long)fc * p.len;
+#pragma unroll
+      for (int k = 0; k < KPF; ++k) {
+        Pack<T, VEC> z;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+          const float x = (float)d[j][k].e[e];
+          if constexpr (Q == QINF) z.e[e] = (T)copysignf(fminf(fabsf(x), rf), x);
+          else if constexpr (Q == Q2) z.e[e] = round_to<T>((double)x * par);
+          else z.e[e] = round_to<T>(copysign(fmax(fabs((double)x) - par, 0.0), (double)x));
+        }
+        const int b = f < fibres ? hl.blank(p, k) : VEC;
+        if (b == 0) {
+          store_pack(out + hl.at(p, k), z);
+        } else if (b < VEC) {
+#pragma unroll
+          for (int e = 0; e < VEC; ++e)
+            if (e >= b) store_one_nt(out + hl.at(p, k) + e, z.e[e]);
+        }
+      }
+    }
+  }
+}
+
+template <int Q, typename T, int SEG>
+static HmKernel with_kpf(int kpf) {
+  if (kpf == 4) return held_multi_kernel<Q, T, SEG, 4>;
+  if (kpf == 8) return held_multi_kernel<Q, T, SEG, 8>;
+  if constexpr (SEG == 4) {
+    if (kpf == 2) return held_multi_kernel<Q, T, SEG, 2>;
+  } else if constexpr (sizeof(T) == 4) {
+    if (kpf == 16) return held_multi_kernel<Q, T, SEG, 16>;
+  }
+  return nullptr;
+}
+template <int Q, typename T>
+static HmKernel with_seg(int seg, int kpf) {
+  return seg == 4 ? with_kpf<Q, T, 4>(kpf) : seg == 16 ? with_kpf<Q, T, 16>(kpf) : nullptr;
+}
+template <int Q>
+static HmKernel with_storage(int storage, int seg, int kpf) {
+  switch (storage) {
+    case MLPROJ_STORE_F32: return with_seg<Q, float>(seg, kpf);
+    case MLPROJ_STORE_BF16: return with_seg<Q, bf16_t>(seg, kpf);
+    default: return with_seg<Q, f16_t>(seg, kpf);
+  }
+}
+
+HmKernel hm_kernel(int q1, int storage, int seg, int kpf) {
+  return q1 == QINF ? with_storage<QINF>(storage, seg, kpf) : q1 == Q1 ? with_storage<Q1>(storage, seg, kpf) : with_storage<Q2>(storage, seg, kpf);
+}
+HmClear hm_clear() { return hm_clear_kernel; }
+
+}  // namespace mlproj

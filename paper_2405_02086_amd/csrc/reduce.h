@@ -261,6 +261,14 @@ __device__ __forceinline__ unsigned seg_sum_u(unsigned x) {
   return x;
 }
 
+// One element into an fp64 aggregate of its fibre.
+template <int Q>
+__device__ __forceinline__ void accumulate_d(double& a, double y) {
+  if constexpr (Q == QINF) a = fmax(a, fabs(y));
+  else if constexpr (Q == Q1) a += fabs(y);
+  else a = fma(y, y, a);
+}
+
 }  // namespace mlproj
 
 #endif

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 from oracle import mlproj_oracle as orc
-from test_gpu_parity import ATOL, QNAME, RTOL, STORE_DTYPES, check_stored, eta_for, run_stored, stored_input, mp  # noqa: F401
+from test_gpu_parity import ATOL, QNAME, RTOL, STORE_DTYPES, check_multi, check_stored, eta_for, nested_norm, run_multi, run_stored, stored_input, mp  # noqa: F401
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -69,3 +69,80 @@ def test_search_over_part_of_its_register_slots(mp, q, m):
     for frac in (1e-5, 0.3):
         eta = eta_for(Y, q, frac)
         check_stored(run_stored(mp, Y, eta, q, "f32"), orc.bilevel_stored(Y, eta, q, "f32"), q, "f32")
+
+
+# Tensors of two inner levels that take the one-pass kernel: fibres of one chunk, of a ragged last chunk, of the most chunks
+# (256); one fibre per slab and the most fibres; one slab, one slab per workgroup, several, a last workgroup with fewer.
+HM_CASES = [((1, 1, 4), [1, 1]), ((3, 5, 7), [2, 1]), ((256, 3, 9), [1, 1]), ((257, 2, 8), ["inf", 1]), ((1000, 20, 77), [1, 1]),
+            ((2048, 2, 5), [1, 2]), ((200, 128, 130), [1, 1]), ((5, 2000, 30), [2, 2]), ((4, 64, 1024), [2, 1]), ((3, 33, 1001), ["inf", 2]),
+            ((600, 300, 33), [2, 1]), ((190, 60, 513), [1, "inf"]), ((40, 30, 64), [1, 1]), ((255, 256, 256), [1, 1])]
+
+
+@pytest.mark.parametrize("shape,norms", HM_CASES)
+def test_multilevel_in_one_pass(mp, shape, norms):
+    rng = np.random.default_rng(list(shape) + [4])
+    Y = rng.standard_normal(shape).astype(np.float32)
+    Y *= np.power(10.0, rng.uniform(-1.0, 0.0, shape[0])).astype(np.float32)[:, None, None]
+    nrm = nested_norm(Y, norms)
+    for frac in (0.03, 0.4, 1.5, 0.0):
+        eta = float(np.float32(frac * nrm))
+        ref = orc.multilevel(Y, norms, eta)
+        check_multi(run_multi(mp, Y, norms, eta), ref)
+        Z = torch.from_numpy(Y).cuda()
+        mp.multilevel_proj(Z, norms, eta, X=Z)
+        np.testing.assert_allclose(Z.cpu().numpy(), ref["X"], rtol=RTOL, atol=ATOL)
+
+
+@pytest.mark.parametrize("limit", [0, 1])
+@pytest.mark.parametrize("shape,norms", [((256, 3, 40), [1, 1]), ((600, 7, 33), [2, 1]), ((9, 100, 500), ["inf", 1])])
+def test_multilevel_in_one_pass_without_patience(mp, shape, norms, limit):
+    """Every workgroup computes the slab norms it does not find posted itself, as on a GPU too busy to run all of
+    them at once: the same result, in place too, and every kernel ends."""
+    rng = np.random.default_rng(list(shape) + [limit])
+    Y = rng.standard_normal(shape).astype(np.float32)
+    eta = float(np.float32(0.2 * nested_norm(Y, norms)))
+    ref = orc.multilevel(Y, norms, eta)
+    before = mp.set_search_spin_limit(limit)
+    try:
+        check_multi(run_multi(mp, Y, norms, eta), ref)
+        Z = torch.from_numpy(Y).cuda()
+        mp.multilevel_proj(Z, norms, eta, X=Z)
+        np.testing.assert_allclose(Z.cpu().numpy(), ref["X"], rtol=RTOL, atol=ATOL)
+    finally:
+        mp.set_search_spin_limit(before)
+
+
+@pytest.mark.parametrize("storage", ["bf16", "f16"])
+@pytest.mark.parametrize("shape,norms", [((100, 16, 65), [1, 1]), ((30, 40, 128), [2, 2]), ((300, 5, 520), ["inf", 1]), ((64, 64, 64), [1, 1])])
+def test_multilevel_in_one_pass_on_16_bit_storage(mp, storage, shape, norms):
+    dt = getattr(torch, STORE_DTYPES[storage])
+    Y = orc.round_to_storage(np.random.default_rng(list(shape)).standard_normal(shape).astype(np.float32), storage)
+    eta = float(np.float32(0.3 * nested_norm(Y, norms)))
+    Yd = torch.from_numpy(Y).cuda().to(dt)
+    X = mp.multilevel_proj_stored(Yd, norms, eta)
+    x = orc.multilevel_stored(Y, norms, eta, storage)["X32"].astype(np.float64)
+    tol = RTOL * np.abs(x) + ATOL
+    got = X.float().cpu().numpy()
+    assert np.all(got >= orc.round_to_storage((x - tol).astype(np.float32), storage))
+    assert np.all(got <= orc.round_to_storage((x + tol).astype(np.float32), storage))
+    assert torch.equal(mp.multilevel_proj_stored(Yd, norms, eta, X=Yd), X)
+
+
+def test_multilevel_in_one_pass_in_a_graph(mp):
+    """Replays of a captured call, eager calls on other contents between them."""
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    Y = torch.randn((200, 40, 60), generator=gen, device="cuda")
+    X, E = torch.empty_like(Y), torch.empty_like(Y)
+    ws = mp.Workspace(mp.multilevel_workspace_bytes(tuple(Y.shape)))
+    eta = 0.2 * float(Y.abs().sum())
+    mp.multilevel_proj(Y, [1, 1], eta, X=X, workspace=ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        mp.multilevel_proj(Y, [1, 1], eta, X=X, workspace=ws)
+    for _ in range(3):
+        Y.copy_(torch.randn(Y.shape, generator=gen, device="cuda"))
+        mp.multilevel_proj(Y, [1, 1], eta, X=E)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(X, E)
