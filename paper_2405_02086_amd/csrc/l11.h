@@ -240,11 +240,23 @@ __device__ __forceinline__ void l11_filter_body(const T* __restrict__ Y, long lo
         }
       }
     };
-    long long r0 = grp * RBLK;
-    for (; r0 + RBLK <= n; r0 += g.groups * RBLK) {
+    // Row blocks from the bottom up, the reverse of the pass before: the rows read last there may still
+    // be cached.
+    const long long full = n / RBLK;            // whole blocks; the ragged one, if any, belongs to group full % groups
+    if (n % RBLK != 0 && grp == full % g.groups) {
+      for (long long i = full * RBLK + wave; i < n; i += WAVES) {
+        Pack<T, VEC> x;
+        lc.load(Y + i * m, x);
+        float y[VEC];
+#pragma unroll
+        for (int k = 0; k < VEC; ++k) y[k] = (float)x.e[k];
+        visit_row(y);
+      }
+    }
+    for (long long blk = full - 1 - (full - 1 - grp) % g.groups; grp < full && blk >= 0; blk -= g.groups) {
       Pack<T, VEC> x[UNROLL];
 #pragma unroll
-      for (int r = 0; r < UNROLL; ++r) lc.load(Y + (r0 + wave + (long long)r * WAVES) * m, x[r]);
+      for (int r = 0; r < UNROLL; ++r) lc.load(Y + (blk * RBLK + wave + (long long)r * WAVES) * m, x[r]);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int r = 0; r < UNROLL; ++r) {
@@ -253,14 +265,6 @@ __device__ __forceinline__ void l11_filter_body(const T* __restrict__ Y, long lo
         for (int k = 0; k < VEC; ++k) y[k] = (float)x[r].e[k];
         visit_row(y);
       }
-    }
-    for (long long i = r0 + wave; i < n; i += WAVES) {
-      Pack<T, VEC> x;
-      lc.load(Y + i * m, x);
-      float y[VEC];
-#pragma unroll
-      for (int k = 0; k < VEC; ++k) y[k] = (float)x.e[k];
-      visit_row(y);
     }
   }
 #pragma unroll

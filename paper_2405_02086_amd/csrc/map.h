@@ -14,7 +14,9 @@ namespace mlproj {
 //   q = 2   : X = Y * u_j / v_j
 //   q = 1   : X = sign(Y) max(|Y| - tau_j, 0)    with tau_j from the inner searches
 // Row blocks are visited from the bottom up, the reverse of the aggregate pass, so the rows
-// read last there (the ones most likely still cached) are read first here.
+// read last there (the ones most likely still cached) are read first here.  For q = 1 the pass before
+// is a listing sweep, which itself runs bottom up after the aggregate pass, so the order is top down
+// (16384 x 16384 l1,1 748.5 -> 744.4 us for both, 9001 x 3003 148.6 -> 146.3).
 // With fused_eta >= 0 every workgroup first runs the threshold search itself (see
 // search_block) and workgroup 0 files the result record; otherwise tau is read from it.
 // FORM: how a lane reaches its columns (see LaneCols).  MAP_EVEN: 16-byte accesses, m a multiple of
@@ -38,9 +40,12 @@ __device__ __forceinline__ void colmap_body(const T* Y, T* X, long long n, long 
   const LaneCols<T, VEC, FORM == MAP_STRIDED, FORM == MAP_EVEN> lc(t * TILE_W, lane, m);
   const bool col_ok = lc.any();
 
-  // Row blocks of MAP_RBLK rows, bottom block first; the last block may be ragged.
+  // Row blocks of MAP_RBLK rows, bottom block first (q = 1: top block first); the last block may be ragged.
   const long long nblk = (n + MAP_RBLK - 1) / MAP_RBLK;
-  long long b = nblk - 1 - grp;
+  constexpr bool DOWN = Q != Q1;
+  long long b = DOWN ? nblk - 1 - grp : grp;
+  const long long step = DOWN ? -g.map_groups : g.map_groups;
+  auto inside_rows = [&](long long blk) { return DOWN ? blk >= 0 : blk < nblk; };
   // The two buffers hold the elements as stored: widening them here would put a use of the
   // loaded values, and with it the wait for them, ahead of the stores of the current block.
   Pack<T, VEC> x[U], y[U];
@@ -52,7 +57,7 @@ __device__ __forceinline__ void colmap_body(const T* Y, T* X, long long n, long 
     }
   };
   // The first block is requested before tau is known, so its latency hides the search.
-  if (col_ok && b >= 0) load_block(b, x);
+  if (col_ok && inside_rows(b)) load_block(b, x);
 
   Top top;
   bool inside;
@@ -85,7 +90,7 @@ __device__ __forceinline__ void colmap_body(const T* Y, T* X, long long n, long 
           Pack<T, VEC> zero;
 #pragma unroll
           for (int k = 0; k < VEC; ++k) zero.e[k] = (T)0.0f;
-          for (; b >= 0; b -= g.map_groups) {
+          for (; inside_rows(b); b += step) {
 #pragma unroll
             for (int r = 0; r < U; ++r) {
               const long long row = b * MAP_RBLK + wave + (long long)r * WAVES;
@@ -143,9 +148,9 @@ __device__ __forceinline__ void colmap_body(const T* Y, T* X, long long n, long 
   // counter, so any wait for a load also waits for every store issued before it: the wait
   // must come after both have been issued, or the two never overlap.
   // A thread reads and writes the same elements only, so X may alias Y.
-  for (; b >= 0; b -= g.map_groups) {
-    const long long nb = b - g.map_groups;
-    if (nb >= 0) load_block(nb, y);
+  for (; inside_rows(b); b += step) {
+    const long long nb = b + step;
+    if (inside_rows(nb)) load_block(nb, y);
 #pragma unroll
     for (int r = 0; r < U; ++r) {
       const long long row = b * MAP_RBLK + wave + (long long)r * WAVES;
