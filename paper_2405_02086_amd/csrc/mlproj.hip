@@ -1078,7 +1078,7 @@ using namespace mlproj;
 
 extern "C" {
 
-int mlproj_version(void) { return 386; }
+int mlproj_version(void) { return 387; }
 
 const char* mlproj_status_string(int status) {
   switch (status) {
