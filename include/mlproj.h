@@ -162,7 +162,7 @@ int mlproj_stripe_of_workgroup(long long workgroup, long long stripes);
  * (the default, 256 polls of 1-2 us each, plus the one-workgroup search), never a stall.
  * 0 makes the several-workgroup search give up at once (which is how the tests exercise the
  * kernel behind it).  The same number, capped at 64, is the patience of the one-pass tri-level
- * kernel (see trilevel_proj_l1infinf): with 0 its workgroups never wait for one another.
+ * and multi-level kernels (see trilevel_proj_l1infinf): with 0 its workgroups never wait for one another.
  * Returns the previous value, or MLPROJ_ERR_BAD_DIMENSION for a value outside 0..4194304.    */
 int mlproj_set_search_spin_limit(int polls);
 
@@ -370,7 +370,11 @@ int trilevel_proj_stored(int storage, const void* Y /* device, d0*d1*d2 elements
  * tensor with its axes reversed: ndim = 3 with two MLPROJ_NORM_INF is the tri-level
  * l1,inf,inf, three MLPROJ_NORM_L1 levels give the l1,1,1 of Sec. 6.1, ndim = 2 is the bi-level
  * projection of the transposed matrix.  dims and norms are host arrays; v_out / u_out have
- * dims[0] entries.  The workspace comes from mlproj_multilevel_workspace_bytes.            */
+ * dims[0] entries.  The workspace comes from mlproj_multilevel_workspace_bytes.
+ * Two inner levels (neighbouring MLPROJ_NORM_INF levels count as one) on a tensor of at most 2048
+ * groups whose groups fit a workgroup's registers are projected in one pass over memory, with the
+ * exchange between workgroups described at trilevel_proj_l1infinf: slower on a GPU that other
+ * streams keep full, never stalled, and the result is the same.                            */
 int mlproj_multilevel_workspace_bytes(int ndim, const long long* dims /* host */,
                                       size_t* bytes_out /* host */);
 int multilevel_proj(const float* Y /* device */, float* X /* device, same size */, int ndim,

@@ -33,6 +33,7 @@ constexpr int HM_MAX_FIBRES = 2048;      // per workgroup (LDS: norms and radii,
 constexpr int HM_MAX_SLABS = 2048;       // of the tensor (LDS: 16 KiB)
 constexpr int HM_MAX_WGS = 256;
 constexpr unsigned long long HM_ABSENT = ~0ull;
+
 struct HmPlan {
   int d0, d1, len;       // slabs, fibres per slab, elements per fibre
   int spw, nwg;          // slabs per workgroup, workgroups
@@ -65,8 +66,9 @@ static inline bool hm_plan(long long d0, long long d1, long long len, int elem_b
   const long long nwg = cdiv(d0, spw);
   // l1 fibres: the searches cost a workgroup the more the fuller its registers are, and the chain
   // spreads them over the whole chip: one pass only for lightly filled workgroups (64 x 200 x 64
-  // l1,2: 15 against 18 us) or nearly a full grid (180 x 128 x 512: 33 against 43, 256^3 l1,1,1: 43.7 against 46.2; but
-  // 30 x 128 x 512 29 against 19, 150 x 60 x 1000 34 against 32, 64 x 400 x 64 24 against 21).
+  // l1,2: 15 against 18 us) or nearly a full grid (180 x 128 x 512: 33 against 43, 256^3 l1,1,1: 43.5
+  // against 46.1; but 30 x 128 x 512 29 against 19, 150 x 60 x 1000 34 against 32, 64 x 400 x 64 24
+  // against 21).
   const long long rounds = cdiv(spw * d1, nseg);
   if (q1 == Q1 && rounds * kpf > 8 && nwg < 176) return false;
   p->d0 = (int)d0; p->d1 = (int)d1; p->len = (int)len;

@@ -17,12 +17,14 @@
 // costs an L2 write-back, so cross-workgroup results travel across kernel boundaries only
 // (the one exception, the search over more than 32768 groups, exchanges a few words per round
 // through device-scope atomics alone).  The tri-level form uses the same chain with groups that are
-// contiguous slabs; the generic multi-level form works on contiguous fibres, level by level;
+// contiguous slabs; the generic multi-level form works on contiguous fibres, level by level (or, with
+// two inner levels on a tensor the registers hold, in one pass);
 // a batch of matrices shares the three launches of the chain; a matrix of at most 128 KiB takes
 // one kernel in which every workgroup holds all of Y (tiny.h).
 //
-// This file is the one translation unit: the kernels live in the headers it includes (one per
-// pass), the host code below checks arguments, plans the launch geometry and enqueues.
+// The kernels live in the headers this file includes (one per pass) and, those of the one-pass
+// multi-level projection, in heldmulti.hip, a translation unit of its own; the host code below checks
+// arguments, plans the launch geometry and enqueues.
 #include <atomic>
 #include <mutex>
 #include <tuple>

@@ -167,9 +167,9 @@ __device__ __forceinline__ SearchOut search_block(const VT* __restrict__ v, long
 }
 
 // The same search for at most 64 * CACHE groups by ONE wavefront, for itself: no barrier and no LDS fold
-// in a round (0.15 us against 0.5 for search_block in a workgroup of 512 threads).  Every wavefront that
-// runs it on the same v gets the same bits (they may differ from search_block's in the last bit of a
-// sum: another order).
+// in a round, two barriers and a fold over eight wavefronts less than search_block takes in a workgroup of
+// 512 threads (see tiny.h for what that measured).  Every wavefront that runs it on the same v gets the
+// same bits (they may differ from search_block's in the last bit of a sum: another order).
 template <int CACHE, typename VT>
 __device__ __forceinline__ SearchOut search_wave(const VT* v, int ngroups, double eta, int outer) {
   const int lane = threadIdx.x & (WAVE - 1);
