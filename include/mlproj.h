@@ -372,7 +372,8 @@ int trilevel_proj_stored(int storage, const void* Y /* device, d0*d1*d2 elements
  * projection of the transposed matrix.  dims and norms are host arrays; v_out / u_out have
  * dims[0] entries.  The workspace comes from mlproj_multilevel_workspace_bytes.
  * Two inner levels (neighbouring MLPROJ_NORM_INF levels count as one) on a tensor of at most 2048
- * groups whose groups fit a workgroup's registers are projected in one pass over memory, with the
+ * groups whose groups fit a workgroup's registers are projected in one pass over memory where that is
+ * the faster form (see mlproj_multilevel_one_pass), with the
  * exchange between workgroups described at trilevel_proj_l1infinf: slower on a GPU that other
  * streams keep full, never stalled, and the result is the same.                            */
 int mlproj_multilevel_workspace_bytes(int ndim, const long long* dims /* host */,
@@ -400,6 +401,14 @@ int multilevel_proj_stored(int storage, int outer_norm, const void* Y /* device 
                            void* workspace /* device */, size_t workspace_bytes,
                            float* v_out /* device, dims[0]; may be NULL */,
                            float* u_out /* device, dims[0]; may be NULL */, void* stream);
+
+/* mlproj_multilevel_one_pass -- whether a multilevel_proj call on a d0 x d1 x d2 tensor stored as
+ * `storage`, with `fibre_norm` (a mlproj_norm) along its last axis, takes the one-pass kernel on a GPU
+ * with `compute_units` compute units (1) or the chain of kernels, level by level (0); an error status
+ * for arguments out of range.  The rule depends on nothing else (a weighted call always takes the
+ * chain).  Host only, touches no GPU: here so that the rule can be checked without one.      */
+int mlproj_multilevel_one_pass(int storage, int fibre_norm, long long d0, long long d1, long long d2,
+                               int compute_units);
 
 #ifdef __cplusplus
 }

@@ -51,6 +51,50 @@ static inline void hm_layout(long long nvec, int* seg, int* kpf) {
   *kpf = per_lane <= 2 ? 2 : per_lane <= 4 ? 4 : per_lane <= 8 ? 8 : 16;
 }
 
+// Whether one pass over memory beats the chain.  It has the traffic on its side (8 bytes per fp32 element
+// against 12) and two launches against four, and three things against it: only its own workgroups work (the
+// chain spreads a few large slabs over the whole chip), every chunk slot costs its arithmetic whether it holds
+// elements or not, and a segment's streamed stores leave partly written 64-byte sectors where a fibre is no
+// whole number of them.  The lines below were drawn on 4900 tensors of random sizes, radii and distributions on an
+// MI355X (256 CUs): a class of tensors takes the one pass where its median is ahead of the chain's and its worst
+// close to it.  What they send here takes 0.84 of the chain's time (geometric mean; 1.8 % of it is behind
+// by more than 2 %), what they keep away would have taken 1.10.  Chain / one pass, us, some of either kind:
+//   taken    256^3 l1,2,2 39.1 / 30.3, l1,1,1 46.2 / 43.7; 6 x 71 x 64 l1,1,inf 15.8 / 12.7; 1000 x 128 x 81
+//            l1,1,2 138 / 59; 256 x 64 x 1024 l1,2,2 42.8 / 37.3 (spilled registers and all, see below)
+//   refused  1 x 64 x 1000 l1,2,2 10.6 / 18.9 (one workgroup); 64 x 64 x 1000 l1,2,2 15.9 / 20.9; 1000 x 128 x 72
+//            l1,inf,2 32.0 / 37.1 (sectors, idle slots); 2000 x 256 x 15 l1,1,1 50.7 / 57.2; 4 x 512 x 8 bf16 l1,1,1 17.7 / 26.5
+// q1: norm of the fibres; fibres, rounds: of a workgroup; cus: compute units.
+static inline bool hm_pays(int q1, int elem_bytes, long long len, long long nvec, int seg, int kpf, long long fibres,
+                           long long rounds, long long nwg, int cus) {
+  const bool f32 = elem_bytes == 4, l1 = q1 == Q1;
+  const bool few = nwg * 4 < cus, half = nwg * 2 >= cus, most = nwg * 16 >= (long long)cus * 11;   // of the chip at work
+  const long long slots = rounds * kpf;                       // chunk slots per thread that are worked through
+  const bool ragged = len % (16 / elem_bytes) != 0;           // (the chain goes element by element there)
+  const bool sectors = len * elem_bytes % 64 == 0;
+  const bool filled = nvec * 2 > seg * kpf;                   // a fibre uses more than half of its segment's slots
+  const double used = (double)(fibres * nvec) / (double)(rounds * (HM_WG / seg) * seg * kpf);
+  if (kpf == (f32 ? 16 : 8)) {
+    // the most chunks per lane: fp32 spills 29 to 36 registers here, 16-bit has one round only
+    if (l1 && ragged) return most && used >= 0.25;
+    if (f32) return most && slots == HELD_SLOTS && (l1 ? len % 8 == 0 : nvec == seg * kpf && sectors && used > 0.6);
+    if (ragged) return most && seg == 16 && used >= 0.25;
+    return sectors && !few && used >= (l1 ? 0.75 : 0.4);
+  }
+  if (!l1) {
+    if (!f32) return slots <= 4 || !ragged || (kpf == 4 && !few) || (most && !filled);
+    if (slots <= 8) return !(ragged && slots == 8 && kpf == 4 && seg == 4);
+    if (few || (slots > 16 && seg == 16 && !half)) return false;
+    return seg == 16 || kpf == 2 || sectors || (kpf == 4 && len % 8 == 0);
+  }
+  if (kpf == 2 && rounds > 1 && !filled) return most && (f32 ? !ragged && slots <= 8 : ragged && len > 16);
+  if (!f32) return slots <= 4 ? !(ragged && kpf == 4) || !few : most && (ragged || kpf == 4);
+  if (slots <= 4) return true;
+  if (slots <= 8) return kpf == 2 ? most : !few;
+  if (!most) return false;
+  if (kpf == 2) return ragged || nvec >= 7;
+  return seg == 16 || kpf == 8 || sectors || (ragged && (slots <= 12 || len <= 48));
+}
+
 static inline bool hm_plan(long long d0, long long d1, long long len, int elem_bytes, int cus, int q1, HmPlan* p) {
   const int vec = 16 / elem_bytes;
   if (len < vec || d0 > HM_MAX_SLABS || d1 > HM_MAX_FIBRES) return false;
@@ -64,13 +108,8 @@ static inline bool hm_plan(long long d0, long long d1, long long len, int elem_b
   const long long nseg = HM_WG / seg;
   if (spw * d1 > nseg * (hm_slots(elem_bytes) / kpf)) return false;
   const long long nwg = cdiv(d0, spw);
-  // l1 fibres: the searches cost a workgroup the more the fuller its registers are, and the chain
-  // spreads them over the whole chip: one pass only for lightly filled workgroups (64 x 200 x 64
-  // l1,2: 15 against 18 us) or nearly a full grid (180 x 128 x 512: 33 against 43, 256^3 l1,1,1: 43.5
-  // against 46.1; but 30 x 128 x 512 29 against 19, 150 x 60 x 1000 34 against 32, 64 x 400 x 64 24
-  // against 21).
   const long long rounds = cdiv(spw * d1, nseg);
-  if (q1 == Q1 && rounds * kpf > 8 && nwg < 176) return false;
+  if (!hm_pays(q1, elem_bytes, len, nvec, seg, kpf, spw * d1, rounds, nwg, cus)) return false;
   p->d0 = (int)d0; p->d1 = (int)d1; p->len = (int)len;
   p->spw = (int)spw; p->nwg = (int)nwg;
   p->nvec = (int)nvec; p->dup = (int)(nvec * vec - len);
@@ -85,6 +124,15 @@ typedef void (*HmKernel)(const void* Y, void* X, HmPlan p, int q2, double eta, i
 typedef void (*HmClear)(unsigned long long* posts, int n);
 HmKernel hm_kernel(int q1, int storage, int seg, int kpf);
 HmClear hm_clear();
+
+// The kernel and plan of a tensor that takes the one pass (q1: norm of its fibres), null for one that does not.
+static_assert((int)MLPROJ_NORM_INF == QINF && (int)MLPROJ_NORM_L1 == Q1 && (int)MLPROJ_NORM_L2 == Q2, "norms and kernel variants share their numbers");
+static inline HmKernel hm_route(int storage, int q1, long long d0, long long d1, long long len, int cus, HmPlan* p) {
+  if (!hm_plan(d0, d1, len, storage == MLPROJ_STORE_F32 ? 4 : 2, cus, q1, p)) return nullptr;
+  int seg, kpf;
+  hm_layout(p->nvec, &seg, &kpf);
+  return hm_kernel(q1, storage, seg, kpf);
+}
 
 }  // namespace mlproj
 

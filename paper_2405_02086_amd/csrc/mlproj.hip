@@ -969,21 +969,17 @@ static int run_multilevel(int outer, const T* Y, T* X, int ndim, const long long
 
   if (ndim == 3 && !weights) {
     // Two inner levels on a tensor that the register files hold, whole slabs per workgroup: one pass
-    // over memory (heldmulti.h) instead of two aggregates and two maps.  Chain / one pass, us: 256^3
-    // l1,2,2 39.1 / 30.3, l1,1,1 46.2 / 43.7; 250 x 1000 x 32 l1,1,1 42.6 / 38.1; 1000 x 20 x 77 l1,1,1
-    // 34.1 / 17.7; 64^3 l1,1,1 18.4 / 12.4; 8 x 128 x 512 l1,2,2 18.3 / 15.5.
+    // over memory (heldmulti.h) instead of two aggregates and two maps, where that is the faster (hm_pays).
     HmPlan hp;
-    int seg = 0, kpf = 0;
-    if (hm_plan(dims[0], dims[1], dims[2], (int)sizeof(T), compute_units(), norms_use[0], &hp)) {
-      hm_layout(hp.nvec, &seg, &kpf);
-      const int storage = std::is_same<T, float>::value ? MLPROJ_STORE_F32 : std::is_same<T, bf16_t>::value ? MLPROJ_STORE_BF16 : MLPROJ_STORE_F16;
+    const int storage = std::is_same<T, float>::value ? MLPROJ_STORE_F32 : std::is_same<T, bf16_t>::value ? MLPROJ_STORE_BF16 : MLPROJ_STORE_F16;
+    if (const HmKernel kernel = hm_route(storage, norms_use[0], dims[0], dims[1], dims[2], compute_units(), &hp)) {
       unsigned long long* posts = reinterpret_cast<unsigned long long*>(V[1]);   // (nothing else uses the level arrays)
       const unsigned limit = g_spin_limit.load(std::memory_order_relaxed);
       const unsigned patience = limit < HELD_PATIENCE ? limit : HELD_PATIENCE;
       mark(stream);
       launch(hm_clear(), dim3((unsigned)cdiv(dims[0], WG)), dim3(WG), stream, posts, hp.d0);
       mark(stream);
-      launch(hm_kernel(norms_use[0], storage, seg, kpf), dim3((unsigned)hp.nwg), dim3(HM_WG), stream, Y, X, hp, norms_use[1],
+      launch(kernel, dim3((unsigned)hp.nwg), dim3(HM_WG), stream, Y, X, hp, norms_use[1],
              (double)eta, outer, ws, posts, v_out, u_out, patience);
       mark(stream);
       return launch_status();
@@ -1080,7 +1076,7 @@ using namespace mlproj;
 
 extern "C" {
 
-int mlproj_version(void) { return 387; }
+int mlproj_version(void) { return 388; }
 
 const char* mlproj_status_string(int status) {
   switch (status) {
@@ -1096,6 +1092,15 @@ const char* mlproj_status_string(int status) {
     case MLPROJ_ERR_NO_ALLOC_LIMIT: return "input needs more scratch memory than the built-in buffer of the no-allocation entry point holds";
     default: return "unknown status";
   }
+}
+
+int mlproj_multilevel_one_pass(int storage, int fibre_norm, long long d0, long long d1, long long d2, int compute_units) {
+  if (storage < MLPROJ_STORE_F32 || storage > MLPROJ_STORE_F16 || fibre_norm < MLPROJ_NORM_INF || fibre_norm > MLPROJ_NORM_L2) return MLPROJ_ERR_BAD_VARIANT;
+  const int st = check_dims(d0, d1, d2);
+  if (st != MLPROJ_OK) return st;
+  if (compute_units <= 0) return MLPROJ_ERR_BAD_DIMENSION;
+  HmPlan hp;
+  return hm_route(storage, fibre_norm, d0, d1, d2, compute_units, &hp) ? 1 : 0;
 }
 
 int mlproj_trace_begin(void** events, int capacity) {

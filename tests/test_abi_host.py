@@ -367,3 +367,30 @@ def test_bench_refuses_more_than_one_gpu():
     proc = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert proc.returncode != 0
     assert "one GPU" in (proc.stdout + proc.stderr)
+
+
+# Two inner levels on a tensor the registers hold: one pass where it was measured ahead of the chain of kernels, the chain where
+# it was measured ahead of the one pass (256 compute units; storage, norm of the fibres, tensor).
+ONE_PASS = [(0, 1, (256, 256, 256)), (0, 2, (256, 256, 256)), (0, 1, (64, 64, 64)), (0, 1, (6, 71, 64)), (0, 1, (1000, 128, 81)), (0, 1, (1000, 20, 77)),
+            (0, 1, (250, 1000, 32)), (0, 2, (256, 64, 1024)), (0, 0, (974, 100, 64)), (1, 1, (100, 4, 408)), (1, 2, (220, 128, 256)), (2, 1, (250, 100, 169))]
+CHAIN = [(0, 2, (1, 64, 1000)), (0, 2, (1, 2048, 32)), (0, 0, (64, 64, 1000)), (0, 2, (1000, 16, 1000)), (0, 0, (1000, 128, 72)), (0, 1, (2000, 256, 15)),
+         (0, 2, (256, 313, 39)), (0, 1, (8, 128, 512)), (0, 1, (30, 128, 512)), (1, 1, (4, 512, 8)), (1, 1, (64, 512, 64)), (1, 0, (2000, 5, 255)),
+         (0, 1, (2049, 2, 64)), (0, 1, (256, 3, 3)), (0, 1, (256, 2, 1025)), (0, 1, (256, 257, 256))]
+
+
+@pytest.mark.parametrize("expected,storage,norm,shape", [(1, *c) for c in ONE_PASS] + [(0, *c) for c in CHAIN])
+def test_multilevel_route_is_the_faster_one(lib, expected, storage, norm, shape):
+    assert lib.mlproj_multilevel_one_pass(storage, norm, *shape, 256) == expected
+
+
+def test_multilevel_route_counts_the_compute_units_it_has(lib):
+    """A nearly full grid is a share of the device's compute units: 32 slabs fill a partition of 32."""
+    assert lib.mlproj_multilevel_one_pass(0, 1, 32, 256, 256, 256) == 0
+    assert lib.mlproj_multilevel_one_pass(0, 1, 32, 256, 256, 32) == 1
+    assert lib.mlproj_multilevel_one_pass(0, 1, 21, 256, 256, 32) == 0
+
+
+def test_multilevel_route_argument_checks(lib):
+    f = lib.mlproj_multilevel_one_pass
+    assert f(3, 1, 4, 4, 4, 256) == -6 and f(0, 3, 4, 4, 4, 256) == -6
+    assert f(0, 1, 0, 4, 4, 256) == -2 and f(0, 1, 4, 4, 4, 0) == -2 and f(0, 1, 1 << 30, 1 << 30, 1, 256) == -3

@@ -71,15 +71,25 @@ def test_search_over_part_of_its_register_slots(mp, q, m):
         check_stored(run_stored(mp, Y, eta, q, "f32"), orc.bilevel_stored(Y, eta, q, "f32"), q, "f32")
 
 
+def one_pass(mp, storage, shape, norms):
+    """Whether a call on this GPU takes the one-pass kernel (the rule the library's dispatch asks)."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    return mp.lib().mlproj_multilevel_one_pass({"f32": 0, "bf16": 1, "f16": 2}[storage], {"inf": 0, 1: 1, 2: 2}[norms[0]], *shape, cus) == 1
+
+
 # Tensors of two inner levels that take the one-pass kernel: fibres of one chunk, of a ragged last chunk, of the most chunks
-# (256); one fibre per slab and the most fibres; one slab, one slab per workgroup, several, a last workgroup with fewer.
+# (256); one fibre per slab and the most fibres; one slab, one slab per workgroup, several, a last workgroup with fewer; every
+# layout of the kernel.
 HM_CASES = [((1, 1, 4), [1, 1]), ((3, 5, 7), [2, 1]), ((256, 3, 9), [1, 1]), ((257, 2, 8), ["inf", 1]), ((1000, 20, 77), [1, 1]),
-            ((2048, 2, 5), [1, 2]), ((200, 128, 130), [1, 1]), ((5, 2000, 30), [2, 2]), ((4, 64, 1024), [2, 1]), ((3, 33, 1001), ["inf", 2]),
-            ((600, 300, 33), [2, 1]), ((190, 60, 513), [1, "inf"]), ((40, 30, 64), [1, 1]), ((255, 256, 256), [1, 1])]
+            ((2048, 2, 5), [1, 2]), ((200, 128, 130), [1, 1]), ((190, 60, 513), [1, "inf"]), ((40, 30, 64), [1, 1]), ((255, 256, 256), [1, 1]),
+            ((255, 2048, 4), ["inf", 1]), ((128, 512, 30), [2, 2]), ((200, 128, 257), ["inf", 2]), ((200, 64, 1023), [1, 2]), ((256, 64, 1024), [2, 1])]
+# ... and tensors that would fit it but where the chain is the faster.
+HM_REFUSED = [((5, 2000, 30), [2, 2]), ((4, 64, 1024), [2, 1]), ((3, 33, 1001), ["inf", 2]), ((600, 300, 33), [2, 1]), ((9, 100, 500), ["inf", 1])]
 
 
-@pytest.mark.parametrize("shape,norms", HM_CASES)
-def test_multilevel_in_one_pass(mp, shape, norms):
+@pytest.mark.parametrize("taken,shape,norms", [(True, *c) for c in HM_CASES] + [(False, *c) for c in HM_REFUSED])
+def test_multilevel_in_one_pass(mp, taken, shape, norms):
+    assert one_pass(mp, "f32", shape, norms) == taken
     rng = np.random.default_rng(list(shape) + [4])
     Y = rng.standard_normal(shape).astype(np.float32)
     Y *= np.power(10.0, rng.uniform(-1.0, 0.0, shape[0])).astype(np.float32)[:, None, None]
@@ -94,10 +104,11 @@ def test_multilevel_in_one_pass(mp, shape, norms):
 
 
 @pytest.mark.parametrize("limit", [0, 1])
-@pytest.mark.parametrize("shape,norms", [((256, 3, 40), [1, 1]), ((600, 7, 33), [2, 1]), ((9, 100, 500), ["inf", 1])])
+@pytest.mark.parametrize("shape,norms", [((256, 3, 40), [1, 1]), ((600, 7, 33), [2, 1]), ((130, 40, 500), ["inf", 1])])
 def test_multilevel_in_one_pass_without_patience(mp, shape, norms, limit):
     """Every workgroup computes the slab norms it does not find posted itself, as on a GPU too busy to run all of
     them at once: the same result, in place too, and every kernel ends."""
+    assert one_pass(mp, "f32", shape, norms)
     rng = np.random.default_rng(list(shape) + [limit])
     Y = rng.standard_normal(shape).astype(np.float32)
     eta = float(np.float32(0.2 * nested_norm(Y, norms)))
@@ -113,8 +124,10 @@ def test_multilevel_in_one_pass_without_patience(mp, shape, norms, limit):
 
 
 @pytest.mark.parametrize("storage", ["bf16", "f16"])
-@pytest.mark.parametrize("shape,norms", [((100, 16, 65), [1, 1]), ((30, 40, 128), [2, 2]), ((300, 5, 520), ["inf", 1]), ((64, 64, 64), [1, 1])])
-def test_multilevel_in_one_pass_on_16_bit_storage(mp, storage, shape, norms):
+@pytest.mark.parametrize("taken,shape,norms", [(True, (100, 16, 65), [1, 1]), (True, (30, 40, 128), [2, 2]), (False, (300, 5, 520), ["inf", 1]), (True, (64, 64, 64), [1, 1]),
+                                               (True, (256, 70, 256), [2, 1]), (True, (200, 30, 1001), ["inf", 1]), (True, (200, 100, 255), [1, 1]), (True, (200, 500, 30), [2, 2])])
+def test_multilevel_in_one_pass_on_16_bit_storage(mp, storage, taken, shape, norms):
+    assert one_pass(mp, storage, shape, norms) == taken
     dt = getattr(torch, STORE_DTYPES[storage])
     Y = orc.round_to_storage(np.random.default_rng(list(shape)).standard_normal(shape).astype(np.float32), storage)
     eta = float(np.float32(0.3 * nested_norm(Y, norms)))
@@ -130,6 +143,7 @@ def test_multilevel_in_one_pass_on_16_bit_storage(mp, storage, shape, norms):
 
 def test_multilevel_in_one_pass_in_a_graph(mp):
     """Replays of a captured call, eager calls on other contents between them."""
+    assert one_pass(mp, "f32", (200, 40, 60), [1, 1])
     gen = torch.Generator(device="cuda").manual_seed(3)
     Y = torch.randn((200, 40, 60), generator=gen, device="cuda")
     X, E = torch.empty_like(Y), torch.empty_like(Y)
