@@ -20,8 +20,12 @@ namespace mlproj {
 // them.  Measured, chain / one pass: see run_multilevel.
 //
 // Meeting.  As in held.h, with one 64-bit word per slab: its norm, an absent one all ones (a NaN no
-// norm has).  A workgroup that has polled `patience` times computes the missing slabs' norms itself,
-// in the owner's order (so with the owner's bits), and posts them if they are still absent.  Every
+// norm has).  A workgroup that has polled `patience` times computes missing slabs' norms itself,
+// in the owner's order (so with the owner's bits), and posts those still absent.  The workgroups that run
+// divide the missing shares among themselves.  (Every one of them going through all of them, 256 KiB of reading
+// each, made 256^3 l1,1,1 on four streams take 327 to 347 us per projection where the streams ran at once;
+// divided, 41 to 90.  The chain takes 33 to 37 there, but 48 against 46 alone.  l1,2,2: 311 to 325 / 28 to 60, chain 31
+// to 34.  Beside a stream of matrix products as well: 372 to 602 / 344 to 351, chain 304.)  Every
 // wait is bounded and everything waited for can be produced alone; in place is as safe as there, for
 // the same reasons.
 constexpr int HM_WG = HELD_WG;

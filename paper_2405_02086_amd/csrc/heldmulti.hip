@@ -158,8 +158,10 @@ __global__ __launch_bounds__(HM_WG) void held_multi_kernel(const void* Yv, void*
   __shared__ double sm_r[HM_MAX_FIBRES];   // ... their radii (a helper's scratch before that)
   __shared__ double sm_w[HM_MAX_SLABS];    // slab norms, of the whole tensor
   __shared__ PairScratch<HM_WAVES> bs;
-  __shared__ unsigned char sm_missing[HM_MAX_WGS];
+  __shared__ unsigned char sm_missing[HM_MAX_WGS], sm_list[HM_MAX_WGS];
+  static_assert(HM_MAX_WGS <= 256, "a workgroup's number fits a byte");
   __shared__ unsigned sm_any;
+  __shared__ int sm_left, sm_start;
   const int tid = threadIdx.x;
   const int wave = tid / WAVE, lane = tid & (WAVE - 1);
   const int seg = tid / SEG;
@@ -235,9 +237,31 @@ __global__ __launch_bounds__(HM_WG) void held_multi_kernel(const void* Yv, void*
     __syncthreads();
     complete = sm_any == 0u;
     if (!complete) {
-      for (int i = 1; i <= p.nwg; ++i) {
-        const int g = (wg + i) % p.nwg;
-        if (!sm_missing[g]) continue;   // (uniform: an LDS flag)
+      // The shares still missing, listed.  Those that run (the others, as far as anyone can see) divide them: a
+      // workgroup starts with its own section of the list, goes on around it, and looks at a share's words
+      // once more before it computes it.
+      if (wave == 0) {
+        int n = 0, below = 0;   // missing so far; ... with a number below this workgroup's
+        for (int g0 = 0; g0 < p.nwg; g0 += WAVE) {
+          const bool miss = g0 + lane < p.nwg && sm_missing[g0 + lane] != 0;
+          const unsigned long long all = __ballot(miss);
+          if (miss) sm_list[n + __popcll(all & ((1ull << lane) - 1ull))] = (unsigned char)(g0 + lane);
+          if (g0 <= wg && wg < g0 + WAVE) below = n + __popcll(all & ((1ull << (wg - g0)) - 1ull));
+          n += __popcll(all);
+        }
+        if (lane == 0) {
+          sm_left = n;
+          sm_start = p.nwg > n ? (wg - below) * n / (p.nwg - n) : wg;
+        }
+      }
+      __syncthreads();
+      const int missing = sm_left, start = sm_start;
+      for (int i = 0; i < missing; ++i) {
+        const int g = sm_list[(start + i) % missing];   // (uniform)
+        bool absent = false;
+        for (int s = g * p.spw + tid; s < p.d0 && s < (g + 1) * p.spw; s += HM_WG)
+          absent = absent || __hip_atomic_load(posts + s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == HM_ABSENT;
+        if (!__syncthreads_or(absent ? 1 : 0)) continue;
         // the share of workgroup g, its fibres and slabs normed in its own order
         const int g_slab0 = g * p.spw;
         const int g_slabs = p.d0 - g_slab0 < p.spw ? p.d0 - g_slab0 : p.spw;

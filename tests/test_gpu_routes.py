@@ -123,6 +123,31 @@ def test_multilevel_in_one_pass_without_patience(mp, shape, norms, limit):
         mp.set_search_spin_limit(before)
 
 
+@pytest.mark.parametrize("inplace", [False, True])
+def test_multilevel_in_one_pass_on_several_streams(mp, inplace):
+    """Four streams at once, each with a tensor whose workgroups would fill the chip alone: workgroups of one call wait for
+    some that cannot start, and divide their shares among them.  The bits of a call that has the GPU to itself."""
+    shape, norms = (256, 128, 512), [1, 1]
+    assert one_pass(mp, "f32", shape, norms)
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    Ys = [torch.randn(shape, generator=gen, device="cuda") for _ in range(4)]
+    etas = [0.2 * float(Y.abs().sum()) for Y in Ys]
+    alone = [mp.multilevel_proj(Y, norms, eta) for Y, eta in zip(Ys, etas)]
+    Xs = [Y.clone() if inplace else torch.empty_like(Y) for Y in Ys]
+    spaces = [mp.Workspace(mp.multilevel_workspace_bytes(shape)) for _ in Ys]
+    streams = [torch.cuda.Stream() for _ in Ys]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for Y, X, eta, ws, stream in zip(Ys, Xs, etas, spaces, streams):
+            if inplace:
+                with torch.cuda.stream(stream):
+                    X.copy_(Y)
+            mp.multilevel_proj(X if inplace else Y, norms, eta, X=X, workspace=ws, stream=stream)
+    torch.cuda.synchronize()
+    for X, A in zip(Xs, alone):
+        assert torch.equal(X, A)
+
+
 @pytest.mark.parametrize("storage", ["bf16", "f16"])
 @pytest.mark.parametrize("taken,shape,norms", [(True, (100, 16, 65), [1, 1]), (True, (30, 40, 128), [2, 2]), (False, (300, 5, 520), ["inf", 1]), (True, (64, 64, 64), [1, 1]),
                                                (True, (256, 70, 256), [2, 1]), (True, (200, 30, 1001), ["inf", 1]), (True, (200, 100, 255), [1, 1]), (True, (200, 500, 30), [2, 2])])
