@@ -122,10 +122,10 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
   const long long own0 = bid * COLS;                 // first column the workgroup owns
   const long long s0 = EVEN || own0 + COLS <= m ? own0 : (m < COLS ? 0 : m - COLS);   // first column of the stripe
   const long long want = s0 + (long long)cw * VEC;
-  const long long col0c = want + VEC <= m ? want : m - VEC;   // the lane's columns: col0c .. col0c + VEC - 1
+  const long long col0c = (EVEN ? want < m : want + VEC <= m) ? want : m - VEC;   // the lane's columns: col0c .. col0c + VEC - 1
   const int lc = EVEN ? cw * VEC : (int)(col0c - s0);         // ... and their place in the stripe
   const long long mine0 = want > own0 ? want : own0;
-  const int skip = mine0 - col0c < VEC ? (int)(mine0 - col0c) : VEC;   // leading columns somebody else owns
+  const int skip = EVEN ? (want < m ? 0 : VEC) : mine0 - col0c < VEC ? (int)(mine0 - col0c) : VEC;   // leading columns somebody else owns
   // Byte offsets of the thread's elements from the start of the matrix, in 32 bits (the host
   // sends at most lh_max_elems<T>() elements here): one address register per access instead of two.
   const unsigned off0 = (unsigned)(((long long)rl * m + col0c) * (long long)sizeof(T));
@@ -201,7 +201,7 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
 
   // The owner of column c of the stripe: thread c.
   const long long j = s0 + tid;
-  const bool owner = tid < COLS && j >= own0 && j < m;
+  const bool owner = tid < COLS && (EVEN || j >= own0) && j < m;
   const long long jj = owner ? j : 0;
   double vj = 0.0;
 

@@ -672,6 +672,7 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
       it.count = 0;
       unsigned a = 0, r = 0, h = 0;
       int values = 0;
+      bool even = true;
       for (; k < count && it.count < BATCH_MAX; ++k) {
         if (!held_batchable(k)) continue;
         const mlproj_problem& p = pr[k];
@@ -685,6 +686,7 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
         red.first[it.count] = r; r += (unsigned)cdiv(p.m, SWG / reduce_parts(g.groups, fold_threads(g.groups)));
         hel.first[it.count] = h; h += (unsigned)cdiv(p.m, LH_COLS);
         if (held_values(k) > values) values = held_values(k);
+        even = even && lh_even_rows(p.X, p.m, (int)sizeof(T));
         ++it.count;
       }
       if (it.count == 0) break;
@@ -695,11 +697,17 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
       launch((reduce_batch_kernel<Q, T>), dim3(r), dim3(SWG), stream, it, red);
       mark(stream);
       // (a problem's threads hold the rows they would hold in its single call, whatever the
-      // largest problem of the launch needs: slots past its last row stay empty)
-      if (values == 32) launch((l11_held_batch_kernel<T, 32>), dim3(h), dim3(LH_WG), stream, it, hel, outer);
-      else if (values == 64 && (long long)h > compute_units()) launch((l11_held_batch_kernel<T, 64, true>), dim3(h), dim3(LH_WG), stream, it, hel, outer);
-      else if (values == 64) launch((l11_held_batch_kernel<T, 64>), dim3(h), dim3(LH_WG), stream, it, hel, outer);
-      else launch((l11_held_batch_kernel<T, 128>), dim3(h), dim3(LH_WG), stream, it, hel, outer);
+      // largest problem of the launch needs: slots past its last row stay empty; the ragged build
+      // takes even rows too)
+      auto held = [&](auto even) {
+        constexpr bool EVEN = decltype(even)::value;
+        if (values == 32) launch((l11_held_batch_kernel<T, 32, EVEN>), dim3(h), dim3(LH_WG), stream, it, hel, outer);
+        else if (values == 64 && (long long)h > compute_units()) launch((l11_held_batch_kernel<T, 64, EVEN, true>), dim3(h), dim3(LH_WG), stream, it, hel, outer);
+        else if (values == 64) launch((l11_held_batch_kernel<T, 64, EVEN>), dim3(h), dim3(LH_WG), stream, it, hel, outer);
+        else launch((l11_held_batch_kernel<T, 128, EVEN>), dim3(h), dim3(LH_WG), stream, it, hel, outer);
+      };
+      if (even) held(std::true_type());
+      else held(std::false_type());
       mark(stream);
     }
   }

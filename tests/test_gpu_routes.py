@@ -31,7 +31,7 @@ def test_batch_map_grid_is_planned_for_the_launch(mp, q, shapes):
 RAGGED = [("f32", (5, 5)), ("f32", (7, 4)), ("f32", (100, 77)), ("f32", (300, 257)), ("f32", (129, 259)), ("f32", (1025, 511)),
           ("f32", (4096, 9)), ("f32", (2049, 31)), ("f32", (1, 70001)), ("f32", (40, 5003)), ("f32", (4097, 15)),
           ("f32", (8192, 7)), ("f32", (6000, 1001)), ("f32", (9000, 301)), ("f32", (33, 17)),
-          ("bf16", (9, 9)), ("bf16", (200, 65)), ("bf16", (700, 513)), ("bf16", (2047, 135)), ("bf16", (65, 4103)),
+          ("f32", (1100, 4101)), ("bf16", (1100, 4101)), ("bf16", (9, 9)), ("bf16", (200, 65)), ("bf16", (700, 513)), ("bf16", (2047, 135)), ("bf16", (65, 4103)),
           ("f16", (40, 1031)), ("f16", (5000, 71)), ("f16", (300, 15))]
 
 
@@ -57,6 +57,25 @@ def test_batch_of_ragged_rows_gives_the_bits_of_the_single_calls(mp, q, storage)
     etas = [eta_for(Y.float().cpu().numpy(), q, 0.2) for Y in Yd]
     for Y, eta, X in zip(Yd, etas, mp.bilevel_proj_batch(Yd, etas, q)):
         assert torch.equal(mp.bilevel_proj_stored(Y, eta, q), X)
+
+
+# Batches by the values per thread of their tallest matrix (32, 64, 128) and, at 64, by whether there are more stripes than
+# compute units; rows on whole 64-byte sectors, ragged ones, and both in one batch.
+L11_BATCHES = [[(1024, 64), (512, 128)], [(1000, 77), (500, 333)], [(2048, 256), (1500, 64)], [(2000, 333), (1500, 70)],
+               [(2048, 1024)] * 5, [(2000, 1003)] * 5, [(2048, 1024)] * 3 + [(2000, 1003)] * 3, [(1024, 64), (1000, 77), (2048, 64), (3000, 333)]]
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+@pytest.mark.parametrize("shapes", L11_BATCHES)
+def test_l11_batches_give_the_bits_of_the_single_calls(mp, shapes, storage):
+    dev = torch.device("cuda:0")
+    Yh = [stored_input(sh, storage, i) for i, sh in enumerate(shapes)]
+    Yd = [torch.from_numpy(Y).to(dev).to(getattr(torch, STORE_DTYPES[storage])) for Y in Yh]
+    etas = [eta_for(Y, 1, 0.2) for Y in Yh]
+    Xs = mp.bilevel_proj_batch(Yd, etas, 1)
+    for Y, eta, X in zip(Yd, etas, Xs):
+        assert torch.equal(mp.bilevel_proj_stored(Y, eta, 1), X)
+    check_stored(run_stored(mp, Yh[-1], etas[-1], 1, storage), orc.bilevel_stored(Yh[-1], etas[-1], 1, storage), 1, storage)
 
 
 @pytest.mark.parametrize("q", ["inf", 2])
