@@ -225,7 +225,9 @@ __global__ __launch_bounds__(FIN_WG) void l11_finish_batch_kernel(BatchItems it,
 // problem of the launch.  (Both bodies in one kernel: the two-per-CU builds spill 42 to 48 registers
 // instead of 19 to 29, every build holds the LDS twice; 8 x (2048 x 2048) fp32 136 against 132 us.  A launch each
 // for the even and the ragged problems of a mixed batch: 300x257 + 3 x (64x64) + 1000x512 40 against 25 us.)
-template <typename T, int NV, bool EVEN, bool PACKED = false>
+// SC and COLS as in l11_held_body: the values of v per thread of the search (0: the record is read, see
+// search_batch_kernel), and the columns of a stripe.
+template <typename T, int NV, int SC, bool EVEN, bool PACKED = false, int COLS = LH_COLS>
 __global__ __launch_bounds__(LH_WG, lh_min_waves(NV, PACKED)) void l11_held_batch_kernel(BatchItems it, BatchGrid gr,
                                                                                         int outer) {
   constexpr int WIDE = 16 / (int)sizeof(T);
@@ -235,8 +237,20 @@ __global__ __launch_bounds__(LH_WG, lh_min_waves(NV, PACKED)) void l11_held_batc
   const Geometry g = plan_columns(b.n, b.m, WIDE, Q1);
   const Ws ws = bind(b.ws, layout_for(g, b.m, Q1));
   const long long stripes = (long long)(gr.first[p + 1] - gr.first[p]);
-  l11_held_body<T, NV, LH_SEARCH_CACHE, LH_COLS, EVEN>(static_cast<const T*>(b.Y), static_cast<T*>(b.X), b.n, b.m, ws, b.u_out,
-                                                      b.mask_out, b.eta, outer, stripe_of_workgroup(bid, stripes));
+  l11_held_body<T, NV, SC, COLS, EVEN>(static_cast<const T*>(b.Y), static_cast<T*>(b.X), b.n, b.m, ws, b.u_out,
+                                       b.mask_out, SC > 0 ? b.eta : -1.0, outer, stripe_of_workgroup(bid, stripes));
+}
+
+// The outer searches of l1,1 problems of 4097 to 16384 columns, one workgroup each: the search of a
+// single call (search_kernel, same bits).
+template <typename T>
+__global__ __launch_bounds__(WG) void search_batch_kernel(BatchItems it, int outer) {
+  __shared__ PairScratch<WG / WAVE> s;
+  const BatchItem& b = it.item[blockIdx.x];
+  const Geometry g = plan_columns(b.n, b.m, 16 / (int)sizeof(T), Q1);
+  const Ws ws = bind(b.ws, layout_for(g, b.m, Q1));
+  const SearchOut o = search_block<WG, SEARCH_CACHE_BIG>(ws.v, b.m, b.eta, MODE_PROJECT, outer, s);
+  if (threadIdx.x == 0) write_result(ws, o, nullptr);
 }
 
 }  // namespace mlproj

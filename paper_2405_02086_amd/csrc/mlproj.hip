@@ -622,8 +622,7 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
   };
   // l1,1 problems that a single call sends through the columns-in-registers kernel (see
   // run_bilevel) take the same kernel here, so that a batch gives the bits of its single calls:
-  // the values per thread such a problem needs, 0 for the others.  Those of them with more than
-  // 4096 columns need a search kernel of their own ahead and are enqueued one by one.
+  // the values per thread such a problem needs (negative: on the narrow stripes), 0 for the others.
   auto held_values = [&](int i) {
     if constexpr (Q != Q1) return 0;
     const mlproj_problem& p = pr[i];
@@ -631,10 +630,14 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
         g_l11_sweeps.load(std::memory_order_relaxed) != 0)
       return 0;
     const int wide_stripes = lh_values_for<T>(p.n);
-    if (wide_stripes == 0 && sizeof(T) == 4 && l11_narrow_stripes_fit(p.n, p.m)) return -1;   // the narrow stripes: single calls only
+    if (wide_stripes == 0 && sizeof(T) == 4 && l11_narrow_stripes_fit(p.n, p.m)) return -128;
     return wide_stripes;
   };
-  auto held_batchable = [&](int i) { return held_values(i) > 0 && pr[i].m <= (long long)LH_WG * LH_SEARCH_CACHE; };
+  auto held_seeded = [&](const auto& p) { return p.m <= (long long)LH_WG * LH_SEARCH_CACHE; };
+  auto held_batchable = [&](int i) {
+    const int values = held_values(i);
+    return values > 0 ? pr[i].m <= FUSED_SEARCH_MAX_BIG : values < 0 && held_seeded(pr[i]);
+  };
   auto batchable = [&](int i) { return pr[i].m <= FUSED_SEARCH_MAX_BIG && !tinyable(i) && held_values(i) == 0; };
   if constexpr (tiny_built<Q, T>()) {
     int k = 0;
@@ -668,11 +671,10 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
     int k = 0;
     while (k < count) {
       BatchItems it;
-      BatchGrid agg, red, hel;
+      BatchGrid agg, red;
+      int values[BATCH_MAX];
       it.count = 0;
-      unsigned a = 0, r = 0, h = 0;
-      int values = 0;
-      bool even = true;
+      unsigned a = 0, r = 0;
       for (; k < count && it.count < BATCH_MAX; ++k) {
         if (!held_batchable(k)) continue;
         const mlproj_problem& p = pr[k];
@@ -684,30 +686,61 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
         const Geometry g = plan_columns(p.n, p.m, WIDE, Q);
         agg.first[it.count] = a; a += (unsigned)(g.tiles * g.groups);
         red.first[it.count] = r; r += (unsigned)cdiv(p.m, SWG / reduce_parts(g.groups, fold_threads(g.groups)));
-        hel.first[it.count] = h; h += (unsigned)cdiv(p.m, LH_COLS);
-        if (held_values(k) > values) values = held_values(k);
-        even = even && lh_even_rows(p.X, p.m, (int)sizeof(T));
+        values[it.count] = held_values(k);
         ++it.count;
       }
       if (it.count == 0) break;
-      agg.first[it.count] = a; red.first[it.count] = r; hel.first[it.count] = h;
+      agg.first[it.count] = a; red.first[it.count] = r;
       mark(stream);
       launch((colagg_batch_kernel<Q, T>), dim3(a), dim3(WG), stream, it, agg);
       mark(stream);
       launch((reduce_batch_kernel<Q, T>), dim3(r), dim3(SWG), stream, it, red);
       mark(stream);
-      // (a problem's threads hold the rows they would hold in its single call, whatever the
-      // largest problem of the launch needs: slots past its last row stay empty; the ragged build
-      // takes even rows too)
-      auto held = [&](auto even) {
-        constexpr bool EVEN = decltype(even)::value;
-        if (values == 32) launch((l11_held_batch_kernel<T, 32, EVEN>), dim3(h), dim3(LH_WG), stream, it, hel, outer);
-        else if (values == 64 && (long long)h > compute_units()) launch((l11_held_batch_kernel<T, 64, EVEN, true>), dim3(h), dim3(LH_WG), stream, it, hel, outer);
-        else if (values == 64) launch((l11_held_batch_kernel<T, 64, EVEN>), dim3(h), dim3(LH_WG), stream, it, hel, outer);
-        else launch((l11_held_batch_kernel<T, 128, EVEN>), dim3(h), dim3(LH_WG), stream, it, hel, outer);
+      // Then the problems of each form of the held kernel in a launch of their own: the search inside,
+      // the search ahead (more than 4096 columns), the narrow stripes (fp32).
+      auto part = [&](bool narrow, bool seeded, auto go) {
+        BatchItems some;
+        BatchGrid grid;
+        unsigned h = 0;
+        int most = 0;
+        bool even = true;
+        some.count = 0;
+        for (int q = 0; q < it.count; ++q) {
+          const BatchItem& b = it.item[q];
+          if ((values[q] < 0) != narrow || held_seeded(b) != seeded) continue;
+          grid.first[some.count] = h; h += (unsigned)cdiv(b.m, narrow ? LH_COLS_NARROW : LH_COLS);
+          if (std::abs(values[q]) > most) most = std::abs(values[q]);
+          even = even && lh_even_rows(b.X, b.m, (int)sizeof(T));
+          some.item[some.count++] = b;
+        }
+        if (some.count == 0) return;
+        grid.first[some.count] = h;
+        if (!seeded) launch((search_batch_kernel<T>), dim3((unsigned)some.count), dim3(WG), stream, some, outer);
+        // (a problem's threads hold the rows they would hold in its single call, whatever the
+        // largest problem of the launch needs: slots past its last row stay empty; the ragged build
+        // takes even rows too)
+        auto enqueue = [&](auto kernel) { launch(kernel, dim3(h), dim3(LH_WG), stream, some, grid, outer); };
+        if (even) go(std::true_type(), most, h, enqueue);
+        else go(std::false_type(), most, h, enqueue);
       };
-      if (even) held(std::true_type());
-      else held(std::false_type());
+      part(false, true, [&](auto e, int most, unsigned h, auto enqueue) {
+        constexpr bool EVEN = decltype(e)::value;
+        constexpr int SC = LH_SEARCH_CACHE;
+        if (most == 32) enqueue(l11_held_batch_kernel<T, 32, SC, EVEN>);
+        else if (most == 64 && (long long)h > compute_units()) enqueue(l11_held_batch_kernel<T, 64, SC, EVEN, true>);
+        else if (most == 64) enqueue(l11_held_batch_kernel<T, 64, SC, EVEN>);
+        else enqueue(l11_held_batch_kernel<T, 128, SC, EVEN>);
+      });
+      part(false, false, [&](auto e, int most, unsigned, auto enqueue) {
+        constexpr bool EVEN = decltype(e)::value;
+        if (most == 32) enqueue(l11_held_batch_kernel<T, 32, 0, EVEN>);
+        else if (most == 64) enqueue(l11_held_batch_kernel<T, 64, 0, EVEN, true>);   // (more than 256 stripes)
+        else enqueue(l11_held_batch_kernel<T, 128, 0, EVEN>);
+      });
+      if constexpr (sizeof(T) == 4)
+        part(true, true, [&](auto e, int, unsigned, auto enqueue) {
+          enqueue(l11_held_batch_kernel<T, 128, LH_SEARCH_CACHE, decltype(e)::value, false, LH_COLS_NARROW>);
+        });
       mark(stream);
     }
   }

@@ -62,7 +62,10 @@ def test_batch_of_ragged_rows_gives_the_bits_of_the_single_calls(mp, q, storage)
 # Batches by the values per thread of their tallest matrix (32, 64, 128) and, at 64, by whether there are more stripes than
 # compute units; rows on whole 64-byte sectors, ragged ones, and both in one batch.
 L11_BATCHES = [[(1024, 64), (512, 128)], [(1000, 77), (500, 333)], [(2048, 256), (1500, 64)], [(2000, 333), (1500, 70)],
-               [(2048, 1024)] * 5, [(2000, 1003)] * 5, [(2048, 1024)] * 3 + [(2000, 1003)] * 3, [(1024, 64), (1000, 77), (2048, 64), (3000, 333)]]
+               [(2048, 1024)] * 5, [(2000, 1003)] * 5, [(2048, 1024)] * 3 + [(2000, 1003)] * 3, [(1024, 64), (1000, 77), (2048, 64), (3000, 333)],
+               # ... of 4097 to 16384 columns (the search ahead), of 4097 to 8192 rows (fp32: narrow stripes), and of every kind
+               [(200, 5001), (100, 4100), (33, 16384)], [(256, 5120)] * 2, [(1500, 4101), (2048, 4112)], [(2100, 4101)], [(5000, 101), (8192, 33), (4097, 15)],
+               [(6000, 48), (4097, 16)], [(5000, 101), (200, 5001), (1000, 77), (64, 64), (3, 3), (9000, 40), (40, 20000)]]
 
 
 @pytest.mark.parametrize("storage", ["f32", "bf16"])
@@ -76,6 +79,27 @@ def test_l11_batches_give_the_bits_of_the_single_calls(mp, shapes, storage):
     for Y, eta, X in zip(Yd, etas, Xs):
         assert torch.equal(mp.bilevel_proj_stored(Y, eta, 1), X)
     check_stored(run_stored(mp, Yh[-1], etas[-1], 1, storage), orc.bilevel_stored(Yh[-1], etas[-1], 1, storage), 1, storage)
+    for p in (2, "inf"):
+        for Y, eta, X in zip(Yd, etas, mp.bilevel_proj_batch(Yd, etas, 1, p=p)):
+            assert torch.equal(mp.bilevel_proj_stored(Y, eta, 1, p=p), X)
+    Zs = [Y.clone() for Y in Yd]
+    masks = [torch.empty(Y.shape[1], dtype=torch.uint8, device=dev) for Y in Yd]
+    mp.bilevel_proj_batch(Zs, etas, 1, Xs=Zs, mask_outs=masks)
+    for Z, X, mask in zip(Zs, Xs, masks):
+        assert torch.equal(Z, X) and torch.equal(mask.bool() | (X != 0).any(0), mask.bool())
+
+
+@pytest.mark.parametrize("shape", [(200, 5001), (256, 5120), (5000, 101), (6000, 48), (1000, 77), (2048, 64), (9000, 40)])
+def test_l11_batches_share_their_launches(mp, shape):
+    """Six matrices take the launches of two, whatever form of the l1,1 kernels they go to (16 x (5000 x 101): 84 us, 650 one
+    after another)."""
+    def intervals(count):
+        Yd = [torch.randn(shape, device="cuda") for _ in range(count)]
+        with mp.KernelTrace(256) as trace:
+            mp.bilevel_proj_batch(Yd, [1.0] * count, 1)
+        torch.cuda.synchronize()
+        return len(trace.durations_ms())
+    assert intervals(6) == intervals(2)
 
 
 @pytest.mark.parametrize("q", ["inf", 2])
