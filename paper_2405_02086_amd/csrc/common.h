@@ -25,6 +25,7 @@ constexpr int MAX_INNER_SWEEPS = 16;     // l1,1: most lock-step passes over Y a
 constexpr double L11_WINDOW = 1.0 / 16;  // l1,1: relative width of the window that samples the density
 constexpr int FILTER_LDS_SLOTS = 8192;   // l1,1: entries a workgroup can stage for its tile (32 KiB of LDS)
 constexpr int FILTER_MAX_LIST = 256;     // l1,1: entries kept per column
+constexpr long long L11_GRID_ELEMS = 32LL << 20;   // l1,1, fp32: elements from which on the sweeps start from a grid of thresholds
 constexpr unsigned NO_COUNT = 0xffffffffu;
 constexpr int QINF = MLPROJ_L1INF, Q1 = MLPROJ_L11, Q2 = MLPROJ_L12;
 constexpr int MODE_PROJECT = 0, MODE_NORM = 1;

@@ -63,6 +63,27 @@ __host__ __device__ static inline bool lh_even_rows(const void* X, long long m, 
   return (reinterpret_cast<uintptr_t>(X) | (unsigned long long)(m * elem_bytes)) % 64 == 0;
 }
 
+// Whether a matrix that the registers hold is left to the sweeps: fp32 rows of no whole 64-byte sectors, one workgroup
+// per CU, and the 32M elements from which on the sweeps start from the grid (held / sweeps, us: 4096 x 8193
+// 169 / 159, 2100 x 27963 331 / 259, 4096 x 16004 299 / 253; but 2048 x 24577, two workgroups per CU, 207 / 226,
+// 4096 x 6145 131 / 180, and with X over Y, whose lines the stripes' stores then find cached, 4001 x 15001 and
+// a copy of Y 312 / 336).
+template <typename T>
+static inline bool lh_left_to_grid(long long n, long long m, bool apart) {
+  return sizeof(T) == 4 && apart && lh_values_for<T>(n) == 128 && m * (long long)sizeof(T) % 64 != 0 && n * m >= L11_GRID_ELEMS;
+}
+
+// The values per thread a whole l1,1 call on an n x m matrix takes this kernel with, 0 for a matrix that goes through the
+// sweeps (apart: X lies apart from Y).  (Against the sweeps: ahead up to 64M elements, 57 against 97 us at 4096 x 4096, 108 against 146
+// at 4096 x 8192, 219 against 227 at 4096 x 16384, and far ahead where most columns are dropped, whose
+// stripes are not even read; behind at 128M.  Rows that are not 16-byte aligned: 38 against 65 us at 2001 x
+// 3003, 21 against 27 at 1001 x 333.)
+template <typename T>
+static inline int lh_values(long long n, long long m, bool apart) {
+  if (m < 16 / (int)sizeof(T) || n * m > lh_max_elems<T>() || lh_left_to_grid<T>(n, m, apart)) return 0;
+  return lh_values_for<T>(n);
+}
+
 struct LhLds {
   double s[LH_FOLD_ROWS][LH_COLS];
   unsigned k[LH_FOLD_ROWS][LH_COLS];

@@ -302,12 +302,12 @@ static int run_bilevel(const T* Y, T* X, long long n, long long m, float eta,
   const bool fuse = mode == MODE_PROJECT && stages == STAGE_ALL && Q != Q1 && m <= FUSED_SEARCH_MAX_BIG && !weights;
   const bool fuse_big = fuse && m > FUSED_SEARCH_MAX;
   const double fused_eta = fuse ? (double)eta : -1.0;
+  const bool apart = X && (X + n * m <= Y || Y + n * m <= X);
 
   if constexpr (tiny_built<Q, T>()) {
     // a matrix of at most 128 KiB: one kernel does it all (up to 16 workgroups when X lies apart
     // from Y, a single one when they overlap)
     TinyPlan tp;
-    const bool apart = X && (X + n * m <= Y || Y + n * m <= X);
     if (mode == MODE_PROJECT && stages == STAGE_ALL && !weights && tiny_plan(n, m, WIDE, &tp)) {
       mark(stream);
       launch((tiny_kernel<Q, T, WIDE>), dim3(apart ? (unsigned)tp.slots : 1u), dim3(TINY_WG), stream, Y, X, n, m,
@@ -322,17 +322,12 @@ static int run_bilevel(const T* Y, T* X, long long n, long long m, float eta,
   int held_values = 0;
   int held_cols = LH_COLS;
   if constexpr (Q == Q1) {
-    // (measured: ahead of the lock-step sweeps up to 64M elements, 57 against 97 us at 4096 x 4096,
-    // 108 against 146 at 4096 x 8192, 219 against 227 at 4096 x 16384, and far ahead where most
-    // columns are dropped, whose stripes are not even read; behind at 128M.  Rows that are not
-    // 16-byte aligned: 38 against 65 us at 2001 x 3003, 21 against 27 at 1001 x 333.  A forced sweep
-    // count, the test hook, keeps the sweeps.)
-    if (mode == MODE_PROJECT && stages == STAGE_ALL && m >= WIDE &&
-        n * m <= lh_max_elems<T>() && g_l11_sweeps.load(std::memory_order_relaxed) == 0)
-      held_values = lh_values_for<T>(n);
+    // (where that is ahead of the lock-step sweeps: see lh_values.  A forced sweep count, the test hook, keeps the sweeps.)
+    if (mode == MODE_PROJECT && stages == STAGE_ALL && g_l11_sweeps.load(std::memory_order_relaxed) == 0)
+      held_values = lh_values<T>(n, m, apart);
     // (fp32 up to 8192 rows: stripes of 8 columns)
     if constexpr (sizeof(T) == 4) {
-      if (held_values == 0 && mode == MODE_PROJECT && stages == STAGE_ALL && m >= WIDE && n * m <= lh_max_elems<T>() &&
+      if (lh_values_for<T>(n) == 0 && mode == MODE_PROJECT && stages == STAGE_ALL && m >= WIDE && n * m <= lh_max_elems<T>() &&
           g_l11_sweeps.load(std::memory_order_relaxed) == 0 && l11_narrow_stripes_fit(n, m)) {
         held_values = 128;
         held_cols = LH_COLS_NARROW;
@@ -349,7 +344,7 @@ static int run_bilevel(const T* Y, T* X, long long n, long long m, float eta,
     // (worth it from 128 MiB on, where the probing pass costs more than the scale kernel, the grid
     // arithmetic and the longer seeding; not on 16-bit storage, where the aggregate pass has twice
     // the elements per byte and the grid arithmetic would double its time)
-    grid = mode == MODE_PROJECT && sweeps >= 1 && n * m >= (32LL << 20) && held_values == 0;
+    grid = mode == MODE_PROJECT && sweeps >= 1 && n * m >= L11_GRID_ELEMS && held_values == 0;
   }
   if (stages & STAGE_AGGREGATE) {
     mark(stream);
@@ -626,19 +621,19 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
   auto held_values = [&](int i) {
     if constexpr (Q != Q1) return 0;
     const mlproj_problem& p = pr[i];
-    if (p.m < WIDE || p.n * p.m > lh_max_elems<T>() ||
-        g_l11_sweeps.load(std::memory_order_relaxed) != 0)
-      return 0;
-    const int wide_stripes = lh_values_for<T>(p.n);
-    if (wide_stripes == 0 && sizeof(T) == 4 && l11_narrow_stripes_fit(p.n, p.m)) return -128;
-    return wide_stripes;
+    if (g_l11_sweeps.load(std::memory_order_relaxed) != 0) return 0;
+    if (sizeof(T) == 4 && lh_values_for<T>(p.n) == 0 && p.m >= WIDE && p.n * p.m <= lh_max_elems<T>() && l11_narrow_stripes_fit(p.n, p.m)) return -128;
+    return lh_values<T>(p.n, p.m, apart(i));
   };
   auto held_seeded = [&](const auto& p) { return p.m <= (long long)LH_WG * LH_SEARCH_CACHE; };
   auto held_batchable = [&](int i) {
     const int values = held_values(i);
     return values > 0 ? pr[i].m <= FUSED_SEARCH_MAX_BIG : values < 0 && held_seeded(pr[i]);
   };
-  auto batchable = [&](int i) { return pr[i].m <= FUSED_SEARCH_MAX_BIG && !tinyable(i) && held_values(i) == 0; };
+  // (matrices whose single call starts from the grid go one by one: the batch sweeps probe instead)
+  auto batchable = [&](int i) {
+    return pr[i].m <= FUSED_SEARCH_MAX_BIG && !tinyable(i) && held_values(i) == 0 && !(Q == Q1 && lh_left_to_grid<T>(pr[i].n, pr[i].m, apart(i)));
+  };
   if constexpr (tiny_built<Q, T>()) {
     int k = 0;
     while (k < count) {

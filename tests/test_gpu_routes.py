@@ -89,6 +89,29 @@ def test_l11_batches_give_the_bits_of_the_single_calls(mp, shapes, storage):
         assert torch.equal(Z, X) and torch.equal(mask.bool() | (X != 0).any(0), mask.bool())
 
 
+# Where a matrix that the registers hold is left to the sweeps: ragged rows, one workgroup per CU, X apart from Y, 32M elements.
+@pytest.mark.parametrize("held,shape,inplace", [(False, (4096, 8193), False), (False, (2049, 16380), False), (True, (4096, 8192), False), (True, (2048, 16385), False),
+                                                (True, (4095, 8193), False), (True, (4096, 8193), True)])
+def test_l11_leaves_large_ragged_matrices_to_the_grid(mp, held, shape, inplace):
+    """(Held, no lock-step sweep runs: the result record shows it.)  Both forms give the same projection."""
+    Y = torch.randn(shape, generator=torch.Generator(device="cuda").manual_seed(5), device="cuda")
+    eta = 0.1 * mp.norm_l1q(Y, "l11")
+    X = Y.clone()
+    ws = mp.Workspace.for_call("l11", *shape)
+    mp.bilevel_proj_l11(X if inplace else Y, eta, X=X, workspace=ws)
+    assert (ws.result()["inner_sweeps"] == 0) == held
+    before = mp.set_l11_sweeps(4)
+    try:
+        Z = mp.bilevel_proj_l11(Y, eta)
+    finally:
+        mp.set_l11_sweeps(before)
+    torch.testing.assert_close(X, Z, rtol=RTOL, atol=ATOL)
+    assert abs(float(X.abs().sum(dtype=torch.float64)) - eta) <= 1e-5 * eta
+    Xb = mp.bilevel_proj_batch([Y[:, :64].contiguous(), Y], [1.0, eta], 1)[1]
+    if not inplace:
+        assert torch.equal(Xb, X)
+
+
 @pytest.mark.parametrize("shape", [(200, 5001), (256, 5120), (5000, 101), (6000, 48), (1000, 77), (2048, 64), (9000, 40)])
 def test_l11_batches_share_their_launches(mp, shape):
     """Six matrices take the launches of two, whatever form of the l1,1 kernels they go to (16 x (5000 x 101): 84 us, 650 one
