@@ -117,9 +117,10 @@ __global__ __launch_bounds__(WG) void colmap_batch_kernel(BatchItems it, BatchGr
   const T* Y = static_cast<const T*>(b.Y);
   T* X = static_cast<T*>(b.X);
   const double eta = Q == Q1 ? -1.0 : b.eta;   // l1,1: tau comes from the record, not from a search here
-  if (b.wide && b.m % WIDE == 0)
+  const int form = map_form(b.wide != 0, b.m, WIDE);
+  if (form == MAP_EVEN)
     colmap_body<Q, T, WIDE, MAP_EVEN, SC>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid);
-  else if (b.wide)
+  else if (form == MAP_RAGGED)
     colmap_body<Q, T, WIDE, MAP_RAGGED, SC>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid);
   else
     colmap_body<Q, T, WIDE, MAP_STRIDED, SC>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid);

@@ -24,6 +24,20 @@ namespace mlproj {
 // for the ragged lane at every store costs 1 % where there is none: 35.6 against 35.9 us at 4096 x 4096.)
 // `bid` is the workgroup's number within its own problem (blockIdx.x for a single matrix).
 constexpr int MAP_EVEN = 0, MAP_RAGGED = 1, MAP_STRIDED = 2;
+
+// The form of a matrix whose aggregate pass is `wide` (see wide_rows).  Ragged rows are not worth 16-byte stores where
+// a large part of the workgroups have next to nothing to store: two column tiles of which the second is an eighth full
+// or less, or one tile of 16-bit elements up to three eighths full (map pass, one element / 16 bytes, us: 30000 x 257
+// fp32 20.8 / 24.3, x 285 21.1 / 25.2, x 297 21.2 / 21.0; 40000 x 575 bf16 36.0 / 46.8, x 590 35.6 / 32.1, x 127 17.3 /
+// 20.8, x 180 18.0 / 19.1, x 201 19.3 / 19.1; three tiles: 30000 x 513 fp32 27.9 / 26.8).
+__host__ __device__ static inline int map_form(bool wide, long long m, int vec) {
+  if (!wide) return MAP_STRIDED;
+  if (m % vec == 0) return MAP_EVEN;
+  const long long tile = (long long)WAVE * vec;
+  if (m < tile ? m * 8 <= tile * 3 : m < 2 * tile && (m - tile) * 8 <= tile) return MAP_STRIDED;
+  return MAP_RAGGED;
+}
+
 template <int Q, typename T, int VEC, int FORM, int SC>
 __device__ __forceinline__ void colmap_body(const T* Y, T* X, long long n, long long m,
                                             const Geometry& g, const Ws& ws,

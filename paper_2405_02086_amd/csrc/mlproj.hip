@@ -69,9 +69,9 @@ static int pick_vec(const void* Y, long long row_len, int elem_bytes = 4) {
 }
 
 // Whether the column kernels read a row in 16-byte pieces (the wide form of LaneCols) or element by
-// element.  The wide form takes any address; on rows of a fraction of a tile, most of whose lanes
-// are idle, the ragged lane's extra stores outweigh the wider loads unless the elements are 16-bit
-// (70000 rows, l1,inf, element by element / wide, us: fp32 33 columns 25.6 / 28.7, 130 31.9 / 33.1,
+// element; the map pass asks map_form as well.  The wide form takes any address; on rows of a fraction of a tile, most
+// of whose lanes are idle, the ragged lane's extra stores outweigh the wider loads unless the elements are
+// 16-bit (70000 rows, l1,inf, element by element / wide, us: fp32 33 columns 25.6 / 28.7, 130 31.9 / 33.1,
 // 200 34.7 / 34.8; bf16 33 columns 34.2 / 51.1, 201 41.0 / 35.4, 403 46.0 / 41.1; and 5001 x 8195
 // bf16 61 / 54).  16-byte aligned rows were always wide.
 static bool wide_rows(const void* Y, long long m, int elem_bytes) {
@@ -490,14 +490,14 @@ static int run_bilevel(const T* Y, T* X, long long n, long long m, float eta,
   }
   if (stages & STAGE_APPLY) {
     mark(stream);
-    const bool even = wide && m % WIDE == 0;
-    if (fuse_big && even)   // (more than 4096 columns: wide whatever the alignment)
+    const int form = map_form(wide, m, WIDE);
+    if (fuse_big && form == MAP_EVEN)   // (more than 4096 columns: wide whatever the alignment)
       launch((colmap_kernel<Q, T, WIDE, MAP_EVEN, SEARCH_CACHE_BIG>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
     else if (fuse_big)
       launch((colmap_kernel<Q, T, WIDE, MAP_RAGGED, SEARCH_CACHE_BIG>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
-    else if (even)
+    else if (form == MAP_EVEN)
       launch((colmap_kernel<Q, T, WIDE, MAP_EVEN>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
-    else if (wide)
+    else if (form == MAP_RAGGED)
       launch((colmap_kernel<Q, T, WIDE, MAP_RAGGED>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
     else
       launch((colmap_kernel<Q, T, WIDE, MAP_STRIDED>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
