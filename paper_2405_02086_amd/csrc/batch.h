@@ -46,24 +46,34 @@ struct BatchGrid {
 // Row groups of the map pass per column tile, for every problem of a launch.  Every map workgroup
 // runs the whole threshold search of its problem, so their number is planned for the launch, not
 // problem by problem: one by one, sixteen matrices of 1024 x 1024 made 4096 workgroups with a
-// search and one block of 16 rows each.  All problems get the same number of row blocks per
-// workgroup, the smallest that keeps the launch within 512 workgroups (256 for a single matrix, as
-// in a single call; twice the column tiles where those are more, so that a tall matrix beside wide
-// ones is still shared).  Measured, us per batch before / with 256 / 512 / 1024 workgroups:
-// 16 x (1024 x 1024) 50.5 / 41.1 / 41.4 / 40.5; 6 x (4096 x 4096) 206 / 222 / 202 / 205;
-// 300x5000 + 4000x64 + 77x900 + 2000x2000 47.3 / 28.5 / 28.4 / 34.7.
+// search and one block of 16 rows each.  Where the grids of the single calls come to at most 512 workgroups together they
+// are kept.  Otherwise all problems get the same number of row blocks per
+// workgroup, the smallest that keeps the launch within 512 workgroups (1024 where no matrix has more than 256 columns,
+// whose search is one value per thread; twice the column tiles where those are more, so that a tall matrix beside wide
+// ones is still shared).  Measured, us per batch with the single calls' grids / 256 / 512 / 1024 workgroups:
+// 16 x (1024 x 1024) 55.3 / 46.3 / 45.2 / 44.4; 6 x (4096 x 4096) 209 / 224 / 201 / 205; 8 x (10000 x 256) 50.8 / 52.5 /
+// 52.0 / 51.1; 300x5000 + 4000x64 + 77x900 + 2000x2000 36.8 / 26.3 / 25.5 / 27.8; 16384x4096 + 1024x1024 (512 in all) 126 /
+// 143 / 135 / 136.
 // (A row's result does not depend on the workgroup that maps it: the bits stay those of the
 // single calls.)
 struct BatchMapPlan {
   int groups[BATCH_MAX];
 };
-static inline void plan_batch_map(int count, const long long* tiles, const long long* rows, BatchMapPlan* plan) {
-  long long all_tiles = 0, most = 1;   // most: row blocks of the tallest matrix
+// tiles, rows, columns, own: of every problem; own: row groups of its single call.
+static inline void plan_batch_map(int count, const long long* tiles, const long long* rows, const long long* columns,
+                                  const long long* own, BatchMapPlan* plan) {
+  long long all_tiles = 0, all_own = 0, most = 1, widest = 0;   // most: row blocks of the tallest matrix
   for (int i = 0; i < count; ++i) {
     all_tiles += tiles[i];
+    all_own += tiles[i] * own[i];
     if (cdiv(rows[i], MAP_RBLK) > most) most = cdiv(rows[i], MAP_RBLK);
+    if (columns[i] > widest) widest = columns[i];
   }
-  long long target = count == 1 ? TARGET_WGS_MAP : BATCH_MAP_WGS;
+  if (all_own <= BATCH_MAP_WGS) {
+    for (int i = 0; i < count; ++i) plan->groups[i] = (int)own[i];
+    return;
+  }
+  long long target = widest <= WG ? 2 * BATCH_MAP_WGS : BATCH_MAP_WGS;
   if (target < 2 * all_tiles) target = 2 * all_tiles;
   long long lo = 1, hi = most;         // (the number of workgroups falls as blocks per workgroup rise; `most` always fits)
   while (lo < hi) {

@@ -747,7 +747,7 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
     it.count = 0;
     bool big = false;
     unsigned a = 0, r = 0, mp = 0, in = 0, up = 0;
-    long long tiles[BATCH_MAX], rows[BATCH_MAX];
+    long long tiles[BATCH_MAX], rows[BATCH_MAX], columns[BATCH_MAX], own[BATCH_MAX];
     int max_sweeps = 0;
     for (; i < count && it.count < BATCH_MAX; ++i) {
       if (!batchable(i)) continue;
@@ -763,6 +763,8 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
       red.first[it.count] = r; r += (unsigned)cdiv(p.m, SWG / reduce_parts(g.groups, fold_threads(g.groups)));
       tiles[it.count] = g.tiles;
       rows[it.count] = p.n;
+      columns[it.count] = p.m;
+      own[it.count] = g.map_groups;
       ini.first[it.count] = in; in += (unsigned)cdiv(p.m, WG);
       upd.first[it.count] = up; up += (unsigned)cdiv(p.m, UPD_COLS);
       plan_l11(p.n, p.m, (int)sizeof(T), &plan.sweeps[it.count], &plan.handoff[it.count]);
@@ -772,7 +774,7 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
     }
     if (it.count == 0) break;
     BatchMapPlan mplan;
-    plan_batch_map(it.count, tiles, rows, &mplan);
+    plan_batch_map(it.count, tiles, rows, columns, own, &mplan);
     for (int k = 0; k < it.count; ++k) { map.first[k] = mp; mp += (unsigned)(tiles[k] * mplan.groups[k]); }
     agg.first[it.count] = a; red.first[it.count] = r; map.first[it.count] = mp;
     ini.first[it.count] = in; upd.first[it.count] = up;

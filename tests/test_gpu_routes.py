@@ -11,10 +11,11 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("q", ["inf", 2])
-@pytest.mark.parametrize("shapes", [[(1024, 1024)] * 16, [(20000, 64)] + [(100, 16384)] * 12, [(4099, 4097)], [(17, 300), (16, 5000)]])
+@pytest.mark.parametrize("shapes", [[(1024, 1024)] * 16, [(20000, 64)] + [(100, 16384)] * 12, [(4099, 4097)], [(17, 300), (16, 5000)], [(2000, 4096), (256, 256)], [(10000, 256)] * 8])
 def test_batch_map_grid_is_planned_for_the_launch(mp, q, shapes):
     """Batches whose map workgroups take several row blocks each, a tall matrix beside wide ones (more column tiles
-    than workgroups planned for), one matrix alone, and ragged last blocks: the bits of the single calls."""
+    than workgroups planned for), one matrix alone, ragged last blocks, the grids of the single calls kept, and narrow matrices:
+    the bits of the single calls."""
     dev = torch.device("cuda:0")
     gen = torch.Generator(device="cuda").manual_seed(len(shapes))
     Yd = [torch.randn(sh, generator=gen, device=dev) for sh in shapes]
