@@ -48,6 +48,9 @@ struct TinyPlan {
 // Whether an n x m matrix with `vec` elements per 16-byte chunk fits, and how.
 __host__ __device__ static inline bool tiny_plan(long long n, long long m, int vec, TinyPlan* p) {
   if (m < vec || m > FUSED_SEARCH_MAX) return false;
+  // (long ragged rows of 16-bit elements: the lanes' unaligned LDS accesses cost more than the second launch of the
+  // chain, 8 x 4001 bf16 12.0 against 10.7 us; 16 x 2001 11.3 against 11.1, and 25 against 28 where the caller waits)
+  if (vec == 8 && m % vec != 0 && m > 2048) return false;
   const long long cpr = cdiv(m, vec);
   if (cpr > TINY_WG) return false;
   int cw = 1;
@@ -69,7 +72,7 @@ __device__ __forceinline__ void tiny_body(const T* Y, T* X, long long n,
                                           unsigned char* __restrict__ mask_out, long long bid,
                                           bool whole) {
   using Acc = typename AccOf<Q>::type;
-  __shared__ Acc sm_part[TINY_WG * VEC];   // [row lane][column]
+  __shared__ alignas(16) Acc sm_part[TINY_WG * VEC];   // [row lane][column]
   __shared__ PairScratch<TINY_WAVES> bs;
   // v (zero beyond column m) takes the place of row lane 0 of the partials, in their type (fp32
   // maxima are exact, sums stay fp64): column c of that row is read by the one thread that then
@@ -116,10 +119,17 @@ __device__ __forceinline__ void tiny_body(const T* Y, T* X, long long n,
   const bool lanes_meet = cw < WAVE;
   const int rows = lanes_meet ? TINY_WAVES : rl;
   const int my_row = lanes_meet ? (int)threadIdx.x / WAVE : tr;
+  // (a whole chunk in one or two wide LDS accesses, here and below: element by element, eight lanes meet on every
+  // bank; 8 x 4096 bf16 10.8 against 10.4 us)
   if (!lanes_meet || (int)(threadIdx.x & (WAVE - 1)) < cw) {
+    if (shadow == 0) {
 #pragma unroll
-    for (int e = 0; e < VEC; ++e)
-      if (e >= shadow) sm_part[my_row * width + at + e] = acc[e];
+      for (int e = 0; e < VEC; ++e) sm_part[my_row * width + tc * VEC + e] = acc[e];
+    } else {
+#pragma unroll
+      for (int e = 0; e < VEC; ++e)
+        if (e >= shadow) sm_part[my_row * width + at + e] = acc[e];
+    }
   }
   __syncthreads();
   for (int c = threadIdx.x; c < width; c += TINY_WG) {
@@ -148,9 +158,17 @@ __device__ __forceinline__ void tiny_body(const T* Y, T* X, long long n,
   }
   float uf[VEC];
   double par[VEC];   // q = 2: scale u_j / v_j
+  Acc mine[VEC];
+  if (shadow == 0) {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) mine[e] = sm_v[tc * VEC + e];
+  } else {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) mine[e] = sm_v[at + e];
+  }
 #pragma unroll
   for (int e = 0; e < VEC; ++e) {
-    const double vj = (double)sm_v[at + e];
+    const double vj = (double)mine[e];
     const double uj = radius(vj, top);
     uf[e] = (float)uj;
     par[e] = (Q == Q2 && vj > 0.0) ? uj / vj : 0.0;

@@ -33,7 +33,7 @@ def test_batch_map_grid_is_planned_for_the_launch(mp, q, shapes):
 RAGGED = [("f32", (5, 5)), ("f32", (7, 4)), ("f32", (100, 77)), ("f32", (300, 257)), ("f32", (129, 259)), ("f32", (1025, 511)),
           ("f32", (4096, 9)), ("f32", (2049, 31)), ("f32", (1, 70001)), ("f32", (40, 5003)), ("f32", (4097, 15)),
           ("f32", (8192, 7)), ("f32", (6000, 1001)), ("f32", (9000, 301)), ("f32", (33, 17)),
-          ("f32", (700, 288)), ("f32", (700, 287)), ("f32", (700, 289)), ("bf16", (1100, 191)), ("bf16", (1100, 193)), ("bf16", (700, 575)), ("f16", (700, 577)), ("f32", (1100, 4101)), ("bf16", (1100, 4101)), ("bf16", (9, 9)), ("bf16", (200, 65)), ("bf16", (700, 513)), ("bf16", (2047, 135)), ("bf16", (65, 4103)),
+          ("f32", (700, 288)), ("f32", (700, 287)), ("f32", (700, 289)), ("bf16", (8, 4001)), ("bf16", (16, 2049)), ("f16", (16, 2047)), ("bf16", (1100, 191)), ("bf16", (1100, 193)), ("bf16", (700, 575)), ("f16", (700, 577)), ("f32", (1100, 4101)), ("bf16", (1100, 4101)), ("bf16", (9, 9)), ("bf16", (200, 65)), ("bf16", (700, 513)), ("bf16", (2047, 135)), ("bf16", (65, 4103)),
           ("f16", (40, 1031)), ("f16", (5000, 71)), ("f16", (300, 15))]
 
 
