@@ -45,6 +45,19 @@ def run_gpu(mp, Y, eta, q, workspace=None, inplace=False):
     return {"X": X.cpu().numpy(), "v": v.cpu().numpy(), "u": u.cpu().numpy(), "res": ws.result()}
 
 
+def split_call(mp, Y, eta, q):
+    """bilevel_radii and bilevel_apply: the kernels of the general chain, whatever form a whole call would take."""
+    Yd = torch.from_numpy(Y).to("cuda:0")
+    m = Y.shape[1]
+    ws = mp.Workspace.for_call(QNAME[q], *Y.shape, device=Yd.device)
+    v, u = (torch.full((m,), -1.0, dtype=torch.float32, device=Yd.device) for _ in range(2))
+    X = torch.empty_like(Yd)
+    mp.bilevel_radii(QNAME[q], Yd, eta, ws, v_out=v)
+    mp.bilevel_apply(QNAME[q], Yd, X, ws, u_out=u)
+    torch.cuda.synchronize()
+    return {"X": X.cpu().numpy(), "v": v.cpu().numpy(), "u": u.cpu().numpy(), "res": ws.result()}
+
+
 def eta_for(Y, q, frac):
     """The radius both sides receive: a fraction of the oracle's fp64 norm, rounded to fp32."""
     return float(np.float32(frac * orc.norm_l1q(Y, q)))
@@ -440,8 +453,9 @@ def test_trilevel_more_than_2_to_the_31_elements(mp, beyond_int32):
 
 # ------------------------------------------------------------------ API corners
 @pytest.mark.parametrize("q", ["inf", 1, 2])
-def test_unaligned_pointers_take_the_narrow_paths(mp, q):
-    """Y or X starting 4 bytes into an allocation cannot use 16-byte accesses."""
+def test_unaligned_pointers(mp, q):
+    """Y or X starting 4 bytes into an allocation, on the kernels that read and write 16 bytes at any address; nothing
+    outside X is written."""
     rng = np.random.default_rng(21)
     dev = torch.device("cuda:0")
     n, m = 130, 264
@@ -1198,7 +1212,7 @@ def test_l11_grid_start_on_hard_distributions(mp, family, shape):
     thresholds anchored at the mean magnitude of its first 128 rows, and the inner searches start
     from that instead of a probing pass.  Whatever the grid says (heavy tails, ties, a head that
     is a thousand times the rest or all zero), every threshold is still closed exactly.  The
-    second shape has rows that are not 16-byte aligned (the element-wise access form)."""
+    second shape has rows that are not 16-byte aligned."""
     rng = np.random.default_rng([len(family), shape[1], 80])
     n, m = shape
     if family == "gaussian":
@@ -1278,8 +1292,8 @@ def test_batch_l11_problems_keep_their_own_sweep_plans(mp, l11_sweeps):
 @pytest.mark.parametrize("storage", ["f32", "bf16"])
 def test_batch_l11_columns_in_registers(mp, storage):
     """Problems a single call keeps in registers take the same kernel inside a batch (32, 64 and
-    128 values per thread in one launch), next to one with too many columns for the batch form
-    and one with unaligned rows; the bits of the single calls either way."""
+    128 values per thread in one launch), next to one whose search runs ahead and one with
+    unaligned rows; the bits of the single calls either way."""
     dev = torch.device("cuda:0")
     dt = getattr(torch, STORE_DTYPES[storage])
     shapes = [(256, 128), (1024, 1024), (2048, 64), (4096, 32), (700, 2000), (37, 48), (3000, 400), (100, 4096),
@@ -1436,8 +1450,9 @@ def test_l11_finishing_pass_closes_what_the_sweeps_leave(mp, l11_sweeps, family,
 @pytest.mark.parametrize("family", ["gaussian", "cauchy", "lognormal3", "sparse", "clusters", "constant",
                                     "integers", "geometric", "uniform"])
 def test_l11_default_plan_on_short_matrices(mp, family, n):
-    """Up to 1024 rows the default plan has no lock-step sweep at all (the finishing pass holds
-    the columns in registers and starts from the seeding guess); just above, two and three."""
+    """Whole calls of at most 4096 rows hold the columns in registers: no lock-step sweep.  Split calls take the
+    sweeps' kernels, up to 4M elements without a sweep: up to 1024 rows the finishing kernel that seeds itself and runs
+    the outer search, the seeding and finishing kernels above."""
     rng = np.random.default_rng([len(family), 79, n])
     m = 150
     Y = (rng.standard_normal((n, m)) if family == "gaussian" else _hard_family(family, rng, n, m)).astype(np.float32)
@@ -1445,7 +1460,12 @@ def test_l11_default_plan_on_short_matrices(mp, family, n):
         eta = eta_for(Y, 1, frac)
         got = run_gpu(mp, Y, eta, 1)
         check_against_oracle(got, orc.bilevel(Y, eta, 1), 1)
-        assert got["res"]["inner_sweeps"] <= (0 if n <= 1024 else 2 if n <= 2048 else 3)
+        assert got["res"]["inner_sweeps"] == 0
+        ref = orc.bilevel(Y, eta, 1)
+        got = split_call(mp, Y, eta, 1)
+        check_against_oracle(got, ref, 1)
+        assert got["res"]["inner_sweeps"] == 0
+        assert got["res"]["inner_finished"] == (0 if got["res"]["inside_ball"] else got["res"]["n_active"])
 
 
 @pytest.mark.parametrize("name", ["binary", "outlier", "pow2", "two_levels", "two_rows", "denormal", "huge", "ramp",
@@ -1495,7 +1515,7 @@ def test_l11_root_exactly_on_repeated_entries(mp):
 
 
 # ------------------------------------------------------------------ l1,1 with the columns in registers
-# Up to 4096 rows and 64M elements, with 16-byte aligned rows, one kernel holds 16 whole columns per
+# Up to 4096 rows and 64M elements one kernel holds 16 whole columns per
 # workgroup, runs the inner searches there and maps from the same registers.  The result record
 # shows it: no lock-step sweep, every kept column closed by the column-wise pass.
 # (rows: 1..4096 around the 1024 / 2048 register-count steps; columns: ragged stripes, more than
@@ -1734,12 +1754,28 @@ TINY_SHAPES = {"f32": [(256, 128), (16, 2048), (1, 2048), (8, 2048), (64, 512), 
                "f16": [(128, 512), (100, 24)]}
 
 
+def chain_result(mp, Y, eta, q, storage):
+    """X of the general chain of kernels: a split call (fp32), or a weighted one with all weights 1 (16-bit storage: the
+    search of a weighted ball is a kernel of its own).  Neither ever takes the one-kernel form, as the trace shows."""
+    with mp.KernelTrace(24) as tr:
+        if storage == "f32":
+            X = split_call(mp, Y, eta, q)["X"]
+        else:
+            Yd = torch.from_numpy(Y).to("cuda:0").to(getattr(torch, STORE_DTYPES[storage]))
+            X = mp.bilevel_proj_weighted(Yd, eta, q, torch.ones(Y.shape[1], device="cuda:0")).float().cpu().numpy()
+    tr.close()
+    assert tr.count > 3, "an aggregate, a search and a map at least"
+    return X
+
+
 @pytest.mark.parametrize("q", ["inf", 2, 1])   # (q = 1 has no one-kernel form: the general path)
 @pytest.mark.parametrize("storage,shape", [(st, sh) for st, shapes in TINY_SHAPES.items() for sh in shapes])
 def test_tiny_matrices_one_kernel_path(mp, storage, shape, q):
     """A matrix small enough for the single-kernel path: the oracle's result, one kernel in the
-    trace, for q = inf the bits of the three-kernel chain (which a call on misaligned rows still
-    takes), and the same bits again when projected in place (one workgroup does the whole matrix)."""
+    trace, what the chain of kernels gives (its sums run in another order: tau to a few units of fp64, so a radius
+    to one unit of fp32 and X to one unit of its storage type, with an absolute part where v_j - tau cancels), and the
+    same bits again on rows that are not 16-byte aligned and when projected in place (one workgroup does the whole
+    matrix)."""
     dev = torch.device("cuda:0")
     dt = getattr(torch, STORE_DTYPES[storage])
     Y = stored_input(shape, storage, 71)
@@ -1749,11 +1785,10 @@ def test_tiny_matrices_one_kernel_path(mp, storage, shape, q):
         eta = float(np.float32(frac * norm_p))
         got = run_stored(mp, Y, eta, q, storage, p=p)
         check_stored(got, orc.bilevel_stored(Y, eta, q, storage, p=p), q, storage)
-        chain = run_stored(mp, Y, eta, q, storage, p=p, offset=1)["X"]          # rows not 16-byte aligned: the chain
-        if q == "inf":
-            assert np.array_equal(chain, got["X"])
-        else:
-            np.testing.assert_allclose(chain, got["X"], rtol=2e-2 if storage != "f32" else RTOL, atol=ATOL)
+        assert np.array_equal(run_stored(mp, Y, eta, q, storage, p=p, offset=1)["X"], got["X"])
+        if p == 1:
+            np.testing.assert_allclose(chain_result(mp, Y, eta, q, storage), got["X"], rtol={"f32": 2.0 ** -22, "bf16": 2.0 ** -7, "f16": 2.0 ** -10}[storage],
+                                       atol=2.0 ** -24 if storage == "f16" else 1e-12 * np.abs(Y).max() if q != 1 else ATOL)
         inplace = torch.from_numpy(Y).to(dev).to(dt)
         mp.bilevel_proj_stored(inplace, eta, q, p=p, X=inplace)
         assert np.array_equal(inplace.float().cpu().numpy(), got["X"]), "in place differs from out of place"

@@ -4,7 +4,8 @@ import numpy as np
 import pytest
 
 from oracle import mlproj_oracle as orc
-from test_gpu_parity import ATOL, QNAME, RTOL, STORE_DTYPES, check_multi, check_stored, eta_for, nested_norm, run_multi, run_stored, stored_input, mp  # noqa: F401
+from test_gpu_parity import (ATOL, QNAME, RTOL, STORE_DTYPES, check_against_oracle, check_multi, check_stored, eta_for, nested_norm,  # noqa: F401
+                             run_gpu, run_multi, run_stored, stored_input, mp)
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -89,6 +90,19 @@ def test_l11_batches_give_the_bits_of_the_single_calls(mp, shapes, storage):
     mp.bilevel_proj_batch(Zs, etas, 1, Xs=Zs, mask_outs=masks)
     for Z, X, mask in zip(Zs, Xs, masks):
         assert torch.equal(Z, X) and torch.equal(mask.bool() | (X != 0).any(0), mask.bool())
+
+
+@pytest.mark.parametrize("family", ["gaussian", "cauchy", "misleading_head"])
+def test_l11_grid_start_on_short_ragged_rows(mp, family):
+    """The aggregate pass with the grid of thresholds, one element per access: rows shorter than a tile, 32M elements."""
+    rng = np.random.default_rng([len(family), 81])
+    Y = (rng.standard_cauchy if family == "cauchy" else rng.standard_normal)((262147, 129)).astype(np.float32)
+    if family == "misleading_head":
+        Y[:128] *= 1000.0
+    eta = eta_for(Y, 1, 0.1)
+    got = run_gpu(mp, Y, eta, 1)
+    check_against_oracle(got, orc.bilevel(Y, eta, 1), 1)
+    assert got["res"]["inner_sweeps"] >= 1
 
 
 # Where a matrix that the registers hold is left to the sweeps: ragged rows, one workgroup per CU, X apart from Y, 32M elements.
