@@ -135,7 +135,8 @@ int mlproj_trace_end(void);
  * rows, or up to 4096 rows when the matrix has at most 4M elements; else 3 at 4096, 6 at 16384,
  * 12 beyond 131072): the finishing pass costs more per column the taller the matrix.  With the
  * default, a matrix of at most 4096 rows and 64M elements (32M in 16-bit storage) whose rows are
- * at least 16 bytes long is not swept at all: one kernel keeps 16 whole columns per workgroup in
+ * at least 16 bytes long is not swept at all (fp32 of more than 2048 rows and at least 32M elements: only if
+ * rows are a multiple of 64 bytes, or X overlaps Y): one kernel keeps 16 whole columns per workgroup in
  * registers (a stripe whose columns are all dropped is zeroed with most of it unread), finds their
  * thresholds there and maps from the same registers (fp32: also up to 8192 rows, 8 columns per
  * workgroup, while there are no more such stripes than compute units); any forced value keeps

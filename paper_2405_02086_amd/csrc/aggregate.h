@@ -44,8 +44,9 @@ __device__ __forceinline__ void colagg_body(const T* __restrict__ Y, long long n
   using Acc = typename AccOf<Q>::type;
   constexpr int TILE_W = WAVE * VEC;
   // Rows in flight per wavefront.  A direct pass over a wide matrix has more workgroups per CU than the
-  // two the plan of the others aims at, and is faster with fewer rows each: 256 x 262144 152.9 us per projection
-  // with 8 (or 16), 150.8 with 4.
+  // two the plan of the others aims at, and is mostly faster with fewer rows each (us per projection with 8 / 4:
+  // 500 x 70000 99.3 / 92.4, 2000 x 66000 353 / 336, 8 x 10000 13.9 / 12.8, 256 x 262144 154.8 / 152.2, but
+  // 64 x 500000 85.9 / 87.1).
   constexpr int ROWS = DIRECT ? UNROLL / 2 : UNROLL;
   constexpr int BLOCK = WAVES * ROWS;
   __shared__ Acc sm[WAVES][TILE_W];

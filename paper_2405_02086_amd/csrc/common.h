@@ -276,9 +276,6 @@ __device__ __forceinline__ void store_one_nt(T* p, T x) {
   }
 }
 
-// X is written once and never read again by this call: a non-temporal store keeps it from
-// displacing Y in the caches between the two passes over Y.  (NT = false: an ordinary store, for runs
-// that leave cache lines partly written which a neighbour is about to complete.)
 // A product of fp64, rounded to fp32 and then to the storage type.  The fp32 value is made opaque: the
 // compiler is free to round fp64 straight to 16 bits instead and does so depending on the code around
 // it, so that two kernels would differ in the last bit (and that conversion takes a dozen
@@ -290,6 +287,9 @@ __device__ __forceinline__ T round_to(double x) {
   return (T)f;
 }
 
+// X is written once and never read again by this call: a non-temporal store keeps it from
+// displacing Y in the caches between the two passes over Y.  (NT = false: an ordinary store, for runs
+// that leave cache lines partly written which a neighbour is about to complete.)
 template <bool NT = true, typename T, int VEC>
 __device__ __forceinline__ void store_pack(T* p, const Pack<T, VEC>& t) {
   if constexpr (VEC > 1) {
@@ -315,7 +315,8 @@ __device__ __forceinline__ void store_row_nt(T* p, const float (&x)[VEC]) { stor
 //   wide    : VEC consecutive columns, one 16-byte access per row, wherever the row starts.  The
 //             lane whose columns would run past the end of the row (m not a multiple of VEC) reads
 //             the row's last 16 bytes instead: its first slots then shadow columns of its
-//             neighbour, and are neither kept nor stored.  Needs m >= VEC.
+//             neighbour, which in place may be storing them meanwhile: what comes of a shadow slot reaches no
+//             owned column, no LDS cell and no store.  Needs m >= VEC.
 //   strided : columns lane, lane + 64, lane + 128, ... of the tile, one element per access, for
 //             rows shorter than one 16-byte access.  A slot whose column does not exist reads the
 //             lane's first column instead, so that no load is conditional (a conditional load

@@ -138,7 +138,8 @@ __device__ __forceinline__ void hm_keep_stored(Pack<T, VEC> (&x)[KPF]) {
   }
 }
 
-// above() of l11.h for t >= 0 (an infinite t gives a NaN: nothing is above it).
+// above() of l11.h, without its test for an infinite t in the serial part of every step: that t gives a NaN here, and
+// nothing is above it either way (there an infinite bound has to compare as a number).
 __device__ __forceinline__ float hm_above(double t) {
   const float f = (float)t;
   return (double)f <= t ? __uint_as_float(__float_as_uint(f) + 1u) : f;

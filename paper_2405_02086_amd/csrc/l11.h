@@ -39,7 +39,7 @@ namespace mlproj {
 
 // The smallest float strictly above t >= 0 (inf for inf): a float a satisfies a > t exactly when
 // a >= above(t).  (By the bit pattern: nextafterf stood in the serial part of every fixed-point step.  l1,1 at
-// 256 x 128 19.6 -> 18.95 us, 1000 x 10000 39.6 -> 39.1, 16384 x 16384 743.5 -> 740.3.)
+// 256 x 128 19.6 -> 18.95 us, 1000 x 10000 39.6 -> 39.1.)
 __device__ __forceinline__ float above(double t) {
   const float f = fabsf((float)t);   // (-0 as +0)
   return (double)f <= t && f < INFINITY ? __uint_as_float(__float_as_uint(f) + 1u) : f;

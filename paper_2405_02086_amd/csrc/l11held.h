@@ -121,8 +121,8 @@ __device__ __forceinline__ float lh_row_max(float x) {
 
 // NV: values per thread (rows per thread x VEC).  SC > 0: every workgroup runs the outer search
 // itself (SC values of v per thread), workgroup 0 files the result record; SC = 0: a search
-// kernel ran before and the record is read.  X may alias Y (a thread reads and writes the same
-// elements only).
+// kernel ran before and the record is read.  X may alias Y: a thread writes only elements it has read, and
+// what it reads beside them (see below) goes nowhere.
 // EVEN: every stripe's runs lie on whole 64-byte sectors of X (lh_even_rows); otherwise rows may start
 // anywhere.  (Two builds: with the ragged form's tests and stores beside it the even one lost 1 to 2 %.)
 template <typename T, int NV, int SC, int COLS, bool EVEN>
@@ -141,9 +141,10 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
   const int rl = tid / CW;            // row lane
   // The stripe is COLS whole columns.  Ragged rows: the last stripe ends with the row and overlaps the
   // stripe before it (in a row shorter than a stripe the last lanes overlap their neighbours instead;
-  // m >= VEC).  What a column gives does not depend on who computes it, so the overlap is loaded and
-  // summed like the rest, by both with the same values, and only its owner stores it and publishes
-  // its threshold.  Even rows: a lane past the end shadows the last columns and stores nothing.
+  // m >= VEC).  The overlap is loaded and summed like the rest.  Lanes of one workgroup that overlap (m < COLS) hold
+  // the same values and file the same sums; columns of the stripe before belong to another workgroup, which in place may be
+  // storing them meanwhile: what comes of them reaches no threshold (their owner thread here is none, so it neither
+  // opens nor steps them), no loop exit and no store.  Even rows: a lane past the end shadows the last columns and stores nothing.
   const long long own0 = bid * COLS;                 // first column the workgroup owns
   const long long s0 = EVEN || own0 + COLS <= m ? own0 : (m < COLS ? 0 : m - COLS);   // first column of the stripe
   const long long want = s0 + (long long)cw * VEC;

@@ -16,7 +16,7 @@ namespace mlproj {
 // Row blocks are visited from the bottom up, the reverse of the aggregate pass, so the rows
 // read last there (the ones most likely still cached) are read first here.  For q = 1 the pass before
 // is a listing sweep, which itself runs bottom up after the aggregate pass, so the order is top down
-// (16384 x 16384 l1,1 748.5 -> 744.4 us for both, 9001 x 3003 148.6 -> 146.3).
+// (both together: 9001 x 3003 l1,1 148.6 -> 146.3 us; 16384 x 16384 746 -> 742, hardly more than two runs differ).
 // With fused_eta >= 0 every workgroup first runs the threshold search itself (see
 // search_block) and workgroup 0 files the result record; otherwise tau is read from it.
 // FORM: how a lane reaches its columns (see LaneCols).  MAP_EVEN: 16-byte accesses, m a multiple of
@@ -161,7 +161,8 @@ __device__ __forceinline__ void colmap_body(const T* Y, T* X, long long n, long 
   // and stored, and only then does the wavefront wait.  On gfx9 loads and stores share one
   // counter, so any wait for a load also waits for every store issued before it: the wait
   // must come after both have been issued, or the two never overlap.
-  // A thread reads and writes the same elements only, so X may alias Y.
+  // X may alias Y: a thread writes only elements that it has read, and what it reads beside them (a ragged lane the
+  // columns of its neighbour, perhaps of another workgroup, stored by now or not) goes nowhere.
   for (; inside_rows(b); b += step) {
     const long long nb = b + step;
     if (inside_rows(nb)) load_block(nb, y);

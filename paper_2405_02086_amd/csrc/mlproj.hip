@@ -392,7 +392,8 @@ static int run_bilevel(const T* Y, T* X, long long n, long long m, float eta,
         mark(stream);   // (the same number of intervals as the longer chain: the sweeps' is empty)
         mark(stream);
         const double seed_eta = seeded ? (double)eta : -1.0;
-        // (64 values per thread: two workgroups per CU when there are more stripes than CUs)
+        // (64 values per thread: two workgroups per CU when there are more stripes than CUs; with the search inside, at
+        // most 256 stripes, only on a device or partition of fewer than 256 CUs)
         const bool packed = held_values == 64 && cdiv(m, LH_COLS) > compute_units();
         const bool even = lh_even_rows(X, m, (int)sizeof(T));
         auto go = [&](auto values, auto sc, auto packed_build, auto cols) {

@@ -63,7 +63,9 @@ __device__ __forceinline__ SearchOut search_block(const VT* __restrict__ v, long
   // The slots are worked through in chunks that end with v: a workgroup that holds room for 16384
   // values spends on 4097 of them what those take (the same test in every thread; the slots beyond
   // would add zeros).  Per projection, with all slots in every round / with
-  // those in use: 1000 x 10000 l1,2 (10 rounds) 35.4 / 32.5 us, 4097 x 4097 l1,inf (2 rounds) 45.0 / 43.5.
+  // those in use: 1000 x 10000 l1,2 (10 rounds) 35.4 / 32.5 us, 4097 x 4097 l1,inf (2 rounds) 45.0 / 43.5.  Where all are
+  // in use the tests cost 0.1 to 0.4 us (100 x 16384 l1,inf 17.9 / 18.2, 1000 x 16384 40.5 / 40.7); a second copy of every loop
+  // without them gives that back and costs 0.3 to 0.9 us below 14337 groups.
   constexpr int CHUNK = CACHE > 16 ? 8 : CACHE;
   static_assert(CACHE % CHUNK == 0, "whole chunks");
   double vr[CACHE];
