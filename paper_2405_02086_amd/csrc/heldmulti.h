@@ -91,9 +91,9 @@ static inline bool hm_pays(int q1, int elem_bytes, long long len, long long nvec
     return seg == 16 || kpf == 2 || sectors || (kpf == 4 && len % 8 == 0);
   }
   if (kpf == 2 && rounds > 1 && !filled) return most && (f32 ? !ragged && slots <= 8 : ragged && len > 16);
-  if (!f32) return slots <= 4 ? !(ragged && kpf == 4) || !few : most && (ragged || kpf == 4);
+  if (!f32) return slots <= 4 ? !(ragged && (rounds > 1 || (kpf == 4 && seg == 4))) || !few : most && (ragged || kpf == 4);
   if (slots <= 4) return true;
-  if (slots <= 8) return kpf == 2 ? most : !few;
+  if (slots <= 8) return kpf == 2 ? most : !few || !ragged || (seg == 16 && kpf == 8);
   if (!most) return false;
   if (kpf == 2) return ragged || nvec >= 7;
   return seg == 16 || kpf == 8 || sectors || (ragged && (slots <= 12 || len <= 48));

@@ -92,6 +92,7 @@ __device__ __forceinline__ void tiny_body(const T* Y, T* X, long long n,
   const long long at = ((long long)tc + 1) * VEC <= m ? (long long)tc * VEC : m - VEC;
   const int shadow = col_ok ? (int)(tc * VEC - at) : VEC;
   const int width = cw * VEC;
+  const bool whole_chunks = VEC == 8 && m % VEC == 0;   // (the same for the whole workgroup; see below)
 
   Pack<T, VEC> raw[TINY_SLOTS];
 #pragma unroll
@@ -119,10 +120,11 @@ __device__ __forceinline__ void tiny_body(const T* Y, T* X, long long n,
   const bool lanes_meet = cw < WAVE;
   const int rows = lanes_meet ? TINY_WAVES : rl;
   const int my_row = lanes_meet ? (int)threadIdx.x / WAVE : tr;
-  // (a whole chunk in one or two wide LDS accesses, here and below: element by element, eight lanes meet on every
-  // bank; 8 x 4096 bf16 10.8 against 10.4 us)
+  // (Whole chunks of 16-bit elements in wide LDS accesses, here and below: element by element, eight lanes meet on
+  // every bank; 8 x 4096 bf16 10.8 against 10.4 us.  fp32 gains nothing, and a batch of 15 fp32 l1,2 matrices took 25.4
+  // instead of 24.6.)
   if (!lanes_meet || (int)(threadIdx.x & (WAVE - 1)) < cw) {
-    if (shadow == 0) {
+    if (whole_chunks) {   // (columns past the end included: nobody reads what is made of them)
 #pragma unroll
       for (int e = 0; e < VEC; ++e) sm_part[my_row * width + tc * VEC + e] = acc[e];
     } else {
@@ -159,7 +161,7 @@ __device__ __forceinline__ void tiny_body(const T* Y, T* X, long long n,
   float uf[VEC];
   double par[VEC];   // q = 2: scale u_j / v_j
   Acc mine[VEC];
-  if (shadow == 0) {
+  if (whole_chunks) {
 #pragma unroll
     for (int e = 0; e < VEC; ++e) mine[e] = sm_v[tc * VEC + e];
   } else {
