@@ -30,9 +30,9 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0
 # HBM-side bytes per launch of the map kernel from the rocprofv3 --pmc runs summarised in
 # profiles/ (FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, in KiB), valid for these library versions only.
-TRAFFIC_VERSIONS = (382, 383, 384, 385, 386, 387)   # the library versions the counters in profiles/ hold for (383, 385 and 386 changed l1,1 kernels only, 384 no kernel; 387 the map kernel and the one-pass tri-level kernel for other inputs than these only)
-TRAFFIC_KIB = {"square_4096": 32979.1 * 1.999 + 65557.7, "square_16384": 524922.6 * 1.999 + 1048622.9,
-               "tensor_256x256x256": 32906.8 * 1.999 + 65625.0}
+TRAFFIC_VERSIONS = (388,)   # the library versions the counters in profiles/ hold for
+TRAFFIC_KIB = {"square_4096": 32972.1 * 1.999 + 65622.5, "square_16384": 524931.1 * 1.999 + 1048631.2,
+               "tensor_256x256x256": 32903.1 * 1.999 + 65626.1}
 INFINITY_CACHE_BYTES = 256 * 1024 * 1024
 
 

@@ -61,8 +61,8 @@ static inline void hm_layout(long long nvec, int* seg, int* kpf) {
 // elements or not, and a segment's streamed stores leave partly written 64-byte sectors where a fibre is no
 // whole number of them.  The lines below were drawn on 4900 tensors of random sizes, radii and distributions on an
 // MI355X (256 CUs): a class of tensors takes the one pass where its median is ahead of the chain's and its worst
-// close to it.  What they send here takes 0.84 of the chain's time (geometric mean; 1.8 % of it is behind
-// by more than 2 %), what they keep away would have taken 1.10.  Chain / one pass, us, some of either kind:
+// close to it.  What they send here takes 0.84 of the chain's time (geometric mean; 2.3 % of it is behind
+// by more than 2 %), what they keep away would have taken 1.11.  Chain / one pass, us, some of either kind:
 //   taken    256^3 l1,2,2 39.1 / 30.3, l1,1,1 46.2 / 43.7; 6 x 71 x 64 l1,1,inf 15.8 / 12.7; 1000 x 128 x 81
 //            l1,1,2 138 / 59; 256 x 64 x 1024 l1,2,2 42.8 / 37.3 (spilled registers and all, see below)
 //   refused  1 x 64 x 1000 l1,2,2 10.6 / 18.9 (one workgroup); 64 x 64 x 1000 l1,2,2 15.9 / 20.9; 1000 x 128 x 72
