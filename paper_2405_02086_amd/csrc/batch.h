@@ -31,7 +31,7 @@ struct BatchItem {
   long long n, m;
   double eta;
   int wide;   // the wide form of LaneCols (see wide_rows)
-  int whole;  // one-kernel form: X overlaps Y, one workgroup does the whole matrix
+  int whole;  // one-kernel form: X overlaps Y, one workgroup does the whole matrix; chain: the map pass takes that form's search
 };
 
 struct BatchItems {
@@ -128,12 +128,13 @@ __global__ __launch_bounds__(WG) void colmap_batch_kernel(BatchItems it, BatchGr
   T* X = static_cast<T*>(b.X);
   const double eta = Q == Q1 ? -1.0 : b.eta;   // l1,1: tau comes from the record, not from a search here
   const int form = map_form(b.wide != 0, b.m, WIDE);
+  const bool wave = Q == QINF && b.whole != 0;
   if (form == MAP_EVEN)
-    colmap_body<Q, T, WIDE, MAP_EVEN, SC>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid);
+    colmap_body<Q, T, WIDE, MAP_EVEN, SC>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid, wave);
   else if (form == MAP_RAGGED)
-    colmap_body<Q, T, WIDE, MAP_RAGGED, SC>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid);
+    colmap_body<Q, T, WIDE, MAP_RAGGED, SC>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid, wave);
   else
-    colmap_body<Q, T, WIDE, MAP_STRIDED, SC>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid);
+    colmap_body<Q, T, WIDE, MAP_STRIDED, SC>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid, wave);
 }
 
 // Matrices of at most 128 KiB each: the one-kernel form of tiny.h for all of them in one launch

@@ -23,6 +23,7 @@ namespace mlproj {
 // VEC; MAP_RAGGED: 16-byte accesses, any m >= VEC; MAP_STRIDED: one element per access.  (The test
 // for the ragged lane at every store costs 1 % where there is none: 35.6 against 35.9 us at 4096 x 4096.)
 // `bid` is the workgroup's number within its own problem (blockIdx.x for a single matrix).
+// wave_search: the search of the one-kernel form, for a matrix whose single call takes that (at most WAVE_SEARCH_MAX columns).
 constexpr int MAP_EVEN = 0, MAP_RAGGED = 1, MAP_STRIDED = 2;
 
 // The form of a matrix whose aggregate pass is `wide` (see wide_rows).  Ragged rows are not worth 16-byte stores where
@@ -43,7 +44,8 @@ __device__ __forceinline__ void colmap_body(const T* Y, T* X, long long n, long 
                                             const Geometry& g, const Ws& ws,
                                             float* __restrict__ u_out,
                                             unsigned char* __restrict__ mask_out,
-                                            double fused_eta, int outer, long long bid) {
+                                            double fused_eta, int outer, long long bid,
+                                            bool wave_search = false) {
   constexpr int TILE_W = WAVE * VEC;
   constexpr int U = MAP_UNROLL;
   __shared__ PairScratch<WAVES> bs;
@@ -76,7 +78,8 @@ __device__ __forceinline__ void colmap_body(const T* Y, T* X, long long n, long 
   Top top;
   bool inside;
   if (fused_eta >= 0.0) {
-    const SearchOut o = search_block<WG, SC>(ws.v, m, fused_eta, MODE_PROJECT, outer, bs);
+    const SearchOut o = wave_search ? search_wave<WAVE_SEARCH_CACHE, double>(ws.v, (int)m, fused_eta, outer)
+                                    : search_block<WG, SC>(ws.v, m, fused_eta, MODE_PROJECT, outer, bs);
     top = top_of(o);
     inside = o.inside != 0u;
     if (bid == 0 && threadIdx.x == 0) write_result(ws, o, nullptr);

@@ -610,12 +610,23 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
     const T* Xp = static_cast<const T*>(p.X);
     return Xp + p.n * p.m <= Yp || Yp + p.n * p.m <= Xp;
   };
-  auto tinyable = [&](int i) {
+  auto fits_tiny = [&](int i) {
     if (!tiny_built<Q, T>()) return false;
     const mlproj_problem& p = pr[i];
     TinyPlan tp;
     return tiny_plan(p.n, p.m, WIDE, &tp);
   };
+  // Beside larger matrices a launch of their own costs the batch more than the chain's launches, which are there anyway
+  // (681x60 + 272x144 + 47x291 18.6 against 13.3 us).  Where only ragged rows would need it they ride with the chain, for
+  // q = inf, which gives them the bits of their single calls: the maxima are exact, and the map pass takes the search of
+  // the one-kernel form.
+  int larger = 0, whole_rows = 0;
+  for (int i = 0; i < count; ++i) {
+    larger += pr[i].m <= FUSED_SEARCH_MAX_BIG && !fits_tiny(i) ? 1 : 0;
+    whole_rows += fits_tiny(i) && pr[i].m % WIDE == 0 ? 1 : 0;
+  }
+  const bool ride = Q == QINF && larger > 0 && whole_rows == 0 && count <= BATCH_MAX;
+  auto tinyable = [&](int i) { return !ride && fits_tiny(i); };
   // l1,1 problems that a single call sends through the columns-in-registers kernel (see
   // run_bilevel) take the same kernel here, so that a batch gives the bits of its single calls:
   // the values per thread such a problem needs (negative: on the narrow stripes), 0 for the others.
@@ -758,7 +769,7 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
       b.v_out = p.v_out; b.u_out = p.u_out; b.mask_out = p.mask_out;
       b.n = p.n; b.m = p.m; b.eta = (double)p.eta;
       b.wide = wide_rows(p.Y, p.m, (int)sizeof(T)) ? 1 : 0;
-      b.whole = 0;
+      b.whole = ride && fits_tiny(i) && p.m <= WAVE_SEARCH_MAX ? 1 : 0;
       const Geometry g = plan_columns(p.n, p.m, WIDE, Q);
       agg.first[it.count] = a; a += (unsigned)(g.tiles * g.groups);
       red.first[it.count] = r; r += (unsigned)cdiv(p.m, SWG / reduce_parts(g.groups, fold_threads(g.groups)));

@@ -172,6 +172,8 @@ __device__ __forceinline__ SearchOut search_block(const VT* __restrict__ v, long
 // in a round, two barriers and a fold over eight wavefronts less than search_block takes in a workgroup of
 // 512 threads (see tiny.h for what that measured).  Every wavefront that runs it on the same v gets the
 // same bits (they may differ from search_block's in the last bit of a sum: another order).
+constexpr int WAVE_SEARCH_CACHE = 8;
+constexpr int WAVE_SEARCH_MAX = WAVE * WAVE_SEARCH_CACHE;   // groups up to which the one-kernel form searches this way
 template <int CACHE, typename VT>
 __device__ __forceinline__ SearchOut search_wave(const VT* v, int ngroups, double eta, int outer) {
   const int lane = threadIdx.x & (WAVE - 1);

@@ -144,9 +144,8 @@ __device__ __forceinline__ void tiny_body(const T* Y, T* X, long long n,
 
   // Few groups: every wavefront searches for itself (16 x (256 x 128) in a batch: 11.0 -> 9.2 us
   // with the fold above).
-  constexpr int WAVE_CACHE = 8;
-  const SearchOut o = m <= WAVE * WAVE_CACHE
-      ? search_wave<WAVE_CACHE, Acc>(sm_v, (int)m, eta, outer)
+  const SearchOut o = m <= WAVE_SEARCH_MAX
+      ? search_wave<WAVE_SEARCH_CACHE, Acc>(sm_v, (int)m, eta, outer)
       : search_block<WG, SEARCH_CACHE, TINY_WG, Acc>(sm_v, m, eta, MODE_PROJECT, outer, bs);
   const Top top = top_of(o);
   if (bid == 0) {

@@ -62,6 +62,32 @@ def test_batch_of_ragged_rows_gives_the_bits_of_the_single_calls(mp, q, storage)
         assert torch.equal(mp.bilevel_proj_stored(Y, eta, q), X)
 
 
+@pytest.mark.parametrize("inplace", [False, True])
+@pytest.mark.parametrize("p", [1, 2, "inf"])
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+@pytest.mark.parametrize("more", [[], [(16, 2048), (64, 512)]])
+def test_small_matrices_beside_larger_ones(mp, more, storage, p, inplace):
+    """q = inf: ragged matrices of the one-kernel form in a batch with larger ones go through the launches of those, with the
+    bits of their single calls in every output: up to 512 columns (a wavefront's search there), more, and rows shorter than a
+    16-byte access; beside matrices of whole chunks they share the launch of those."""
+    dev = torch.device("cuda:0")
+    shapes = [(1200, 60), (272, 544), (47, 291), (16, 2047), (5, 5), (60, 517), (33, 17), (100, 3), (64, 511)] + more
+    Yd = [torch.from_numpy(stored_input(sh, storage, i)).to(dev).to(getattr(torch, STORE_DTYPES[storage])) for i, sh in enumerate(shapes)]
+    for frac in (0.05, 0.7, 1.5, 0.0):
+        etas = [frac * float(Y.float().abs().amax(0).sum() if p == 1 else Y.float().abs().amax(0).norm() if p == 2 else Y.float().abs().max()) for Y in Yd]
+        def outputs():
+            return [torch.full((Y.shape[1],), -1.0, device=dev) for Y in Yd], [torch.full((Y.shape[1],), -1.0, device=dev) for Y in Yd], \
+                   [torch.full((Y.shape[1],), 7, dtype=torch.uint8, device=dev) for Y in Yd], [mp.Workspace.for_call("l1inf", *Y.shape, device=dev) for Y in Yd]
+        v, u, mask, ws = outputs()
+        Xs = [Y.clone() if inplace else torch.empty_like(Y) for Y in Yd]
+        mp.bilevel_proj_batch(Xs if inplace else Yd, etas, "inf", p=p, Xs=Xs, v_outs=v, u_outs=u, mask_outs=mask, workspaces=ws)
+        v1, u1, mask1, ws1 = outputs()
+        for i, (Y, X) in enumerate(zip(Yd, Xs)):
+            assert torch.equal(mp.bilevel_proj_stored(Y, etas[i], "inf", p=p, v_out=v1[i], u_out=u1[i], mask_out=mask1[i], workspace=ws1[i]), X)
+            assert torch.equal(v1[i], v[i]) and torch.equal(u1[i], u[i]) and torch.equal(mask1[i], mask[i])
+            assert ws1[i].result() == ws[i].result()
+
+
 # Batches by the values per thread of their tallest matrix (32, 64, 128) and, at 64, by whether there are more stripes than
 # compute units; rows on whole 64-byte sectors, ragged ones, and both in one batch.
 L11_BATCHES = [[(1024, 64), (512, 128)], [(1000, 77), (500, 333)], [(2048, 256), (1500, 64)], [(2000, 333), (1500, 70)],
