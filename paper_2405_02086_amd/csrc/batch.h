@@ -115,7 +115,9 @@ __global__ __launch_bounds__(SWG) void reduce_batch_kernel(BatchItems it, BatchG
   reduce_body<Q>(ws.partial, b.m, g, reduce_parts(g.groups, fold_threads(g.groups)), ws.v, b.v_out, ws.flags, bid);
 }
 
-template <int Q, typename T, int SC>
+// RIDE: some of the problems take the search of the one-kernel form (a build of its own: with both searches in every
+// batch 16 x (1024 x 1024) takes 41.25 instead of 41.1 us).
+template <int Q, typename T, int SC, bool RIDE = false>
 __global__ __launch_bounds__(WG) void colmap_batch_kernel(BatchItems it, BatchGrid gr, BatchMapPlan mp, int outer) {
   constexpr int WIDE = 16 / (int)sizeof(T);
   long long bid;
@@ -128,7 +130,7 @@ __global__ __launch_bounds__(WG) void colmap_batch_kernel(BatchItems it, BatchGr
   T* X = static_cast<T*>(b.X);
   const double eta = Q == Q1 ? -1.0 : b.eta;   // l1,1: tau comes from the record, not from a search here
   const int form = map_form(b.wide != 0, b.m, WIDE);
-  const bool wave = Q == QINF && b.whole != 0;
+  const bool wave = RIDE && b.whole != 0;
   if (form == MAP_EVEN)
     colmap_body<Q, T, WIDE, MAP_EVEN, SC>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid, wave);
   else if (form == MAP_RAGGED)

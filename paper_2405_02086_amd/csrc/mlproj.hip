@@ -620,12 +620,13 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
   // (681x60 + 272x144 + 47x291 18.6 against 13.3 us).  Where only ragged rows would need it they ride with the chain, for
   // q = inf, which gives them the bits of their single calls: the maxima are exact, and the map pass takes the search of
   // the one-kernel form.
-  int larger = 0, whole_rows = 0;
+  int larger = 0, small = 0, whole_rows = 0;
   for (int i = 0; i < count; ++i) {
     larger += pr[i].m <= FUSED_SEARCH_MAX_BIG && !fits_tiny(i) ? 1 : 0;
+    small += fits_tiny(i) ? 1 : 0;
     whole_rows += fits_tiny(i) && pr[i].m % WIDE == 0 ? 1 : 0;
   }
-  const bool ride = Q == QINF && larger > 0 && whole_rows == 0 && count <= BATCH_MAX;
+  const bool ride = Q == QINF && larger > 0 && small > 0 && whole_rows == 0 && count <= BATCH_MAX;
   auto tinyable = [&](int i) { return !ride && fits_tiny(i); };
   // l1,1 problems that a single call sends through the columns-in-registers kernel (see
   // run_bilevel) take the same kernel here, so that a batch gives the bits of its single calls:
@@ -808,8 +809,16 @@ static int run_batch(int outer, int count, const mlproj_problem* pr, void* strea
       launch((l11_finish_batch_kernel<T>), dim3(up), dim3(FIN_WG), stream, it, upd, plan);
     }
     mark(stream);
-    if (big) launch((colmap_batch_kernel<Q, T, SEARCH_CACHE_BIG>), dim3(mp), dim3(WG), stream, it, map, mplan, outer);
-    else launch((colmap_batch_kernel<Q, T, SEARCH_CACHE>), dim3(mp), dim3(WG), stream, it, map, mplan, outer);
+    if (ride) {
+      if constexpr (Q == QINF) {
+        if (big) launch((colmap_batch_kernel<Q, T, SEARCH_CACHE_BIG, true>), dim3(mp), dim3(WG), stream, it, map, mplan, outer);
+        else launch((colmap_batch_kernel<Q, T, SEARCH_CACHE, true>), dim3(mp), dim3(WG), stream, it, map, mplan, outer);
+      }
+    } else if (big) {
+      launch((colmap_batch_kernel<Q, T, SEARCH_CACHE_BIG>), dim3(mp), dim3(WG), stream, it, map, mplan, outer);
+    } else {
+      launch((colmap_batch_kernel<Q, T, SEARCH_CACHE>), dim3(mp), dim3(WG), stream, it, map, mplan, outer);
+    }
     mark(stream);
   }
   int st = launch_status();
