@@ -308,23 +308,15 @@ __global__ __launch_bounds__(WG) void l11_filter_kernel(const T* __restrict__ Y,
 // Starting points of the inner searches.  Dropped columns get +inf (every entry maps to 0).
 // For a kept column the guess assumes its entries are Gaussian with the scale its l1 norm
 // implies: E|y| = sigma*sqrt(2/pi) = v_j/n and E max(|y| - t, 0) = sigma*h(t/sigma) with
-// h(z) = 2*phi(z) - z*erfc(z/sqrt 2), so z solves h(z) = (u_j/v_j)*sqrt(2/pi) (a few Newton
-// steps on the convex h) and the guess is sigma*z.  Only the speed depends on the guess.
+// h(z) = 2*phi(z) - z*erfc(z/sqrt 2), so z solves h(z) = (u_j/v_j)*sqrt(2/pi) (gauss_z) and the
+// guess is sigma*z.  Only the speed depends on the guess.
 // The first certified bounds: every entry active gives the lower bound (v_j - u_j)/n.
 // With fused_eta >= 0 every workgroup first runs the outer threshold search itself (see
 // search_block) and workgroup 0 files the result record and clears the sweep counters, which
 // takes the one-workgroup search kernel off the critical path; otherwise the record is read.
 // The guess for a kept column (see above) and the all-active lower bound.
 __device__ __forceinline__ double l11_guess(double vj, double uj, long long n, double& floor_t) {
-  // (fp32 is plenty here: the guess is a statistical estimate, off by percents)
-  const float c = (float)(uj / vj) * 0.79788456f;  // sqrt(2/pi)
-  float z = 0.0f;
-  for (int it = 0; it < 8; ++it) {
-    const float tail = erfcf(z * 0.70710678f);                  // 2*(1 - Phi(z))
-    const float h = 0.79788456f * expf(-0.5f * z * z) - z * tail;
-    if (!(tail > 1e-30f)) break;
-    z += (h - c) / tail;
-  }
+  const float z = gauss_z((float)(uj * __builtin_amdgcn_rcp(vj)));
   const double sigma = (vj / (double)n) * 1.2533141373155001;   // sqrt(pi/2)
   floor_t = fmax((vj - uj) / (double)n, 0.0);
   return fmax(sigma * (double)z, floor_t);  // never below the all-active bound

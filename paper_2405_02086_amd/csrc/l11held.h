@@ -88,20 +88,29 @@ static inline int lh_values(long long n, long long m, bool apart) {
   return lh_values_for<T>(n);
 }
 
+constexpr int LH_LIST = 128;            // window entries kept per column
+constexpr int LH_LIST_SPAN = 48;        // ... and the most a window is laid out for
+constexpr int LH_WINDOWS = 6;           // windows a column tries before it goes on in plain steps
+constexpr int LH_HALF = 32;             // lanes that step one column
+
 struct LhLds {
-  double s[LH_FOLD_ROWS][LH_COLS];
-  unsigned k[LH_FOLD_ROWS][LH_COLS];
-  float ct[LH_COLS];      // the columns' current thresholds as published by their owners: the smallest float above each
-  float th[LH_COLS];      // ... and the final ones as fp32 pairs (see colmap_body)
+  double s[LH_COLS][LH_FOLD_ROWS + 1];
+  unsigned k[LH_COLS][LH_FOLD_ROWS + 1];
+  float list[LH_COLS][LH_LIST];   // the entries of the columns' windows, in any order
+  unsigned listed[LH_COLS];
+  float hi[LH_COLS];      // the columns' windows as published: the smallest float above the upper end
+  float lo[LH_COLS];      // ... and above the lower
+  unsigned open[LH_COLS];
+  float th[LH_COLS];      // the thresholds as fp32 pairs (see colmap_body)
   float tl[LH_COLS];
 };
 
 // Sum over the lanes of a 16-lane row that own the same columns (the same lane % CW).
 template <int CW>
 __device__ __forceinline__ double lh_row_sum(double x) {
-  if constexpr (CW <= 2) x += dpp_f64<DPP_ROR2>(x);
-  x += dpp_f64<DPP_ROR4>(x);
-  x += dpp_f64<DPP_ROR8>(x);
+  if constexpr (CW <= 2) x += dpp_all_f64<DPP_ROR2>(x);
+  x += dpp_all_f64<DPP_ROR4>(x);
+  x += dpp_all_f64<DPP_ROR8>(x);
   return x;
 }
 template <int CW>
@@ -111,12 +120,55 @@ __device__ __forceinline__ unsigned lh_row_sum_u(unsigned x) {
   x += dpp_u32<DPP_ROR8>(x);
   return x;
 }
+// max(a, |x|) for a >= 0 (fmaxf spends two more instructions on what it makes of signalling NaNs).
+__device__ __forceinline__ float max_abs(float a, float x) {
+  asm("v_max_f32 %0, %0, |%1|" : "+v"(a) : "v"(x));
+  return a;
+}
+template <int CTRL>
+__device__ __forceinline__ float max_with_dpp(float x) {
+  return max_abs(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xf, 0xf, true)));
+}
 template <int CW>
 __device__ __forceinline__ float lh_row_max(float x) {
-  if constexpr (CW <= 2) x = fmaxf(x, __uint_as_float(dpp_u32<DPP_ROR2>(__float_as_uint(x))));
-  x = fmaxf(x, __uint_as_float(dpp_u32<DPP_ROR4>(__float_as_uint(x))));
-  x = fmaxf(x, __uint_as_float(dpp_u32<DPP_ROR8>(__float_as_uint(x))));
-  return x;
+  if constexpr (CW <= 2) x = max_with_dpp<DPP_ROR2>(x);
+  x = max_with_dpp<DPP_ROR4>(x);
+  return max_with_dpp<DPP_ROR8>(x);
+}
+
+// Sums and maxima over 32 lanes, the same bits in every one of them: in each step two lanes, or two groups of
+// lanes that agree, exchange what they hold.
+constexpr int DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140;
+struct Halves { unsigned even, odd; };   // what the even and the odd one of two neighbouring 16-lane rows hold
+__device__ __forceinline__ Halves rows_of(unsigned x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  return Halves{r[0], r[1]};
+}
+__device__ __forceinline__ double half_sum(double x) {
+  x += dpp_all_f64<DPP_SWAP1>(x);
+  x += dpp_all_f64<DPP_SWAP2>(x);
+  x += dpp_all_f64<DPP_HALF_MIRROR>(x);
+  x += dpp_all_f64<DPP_MIRROR>(x);
+  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+  const Halves lo = rows_of((unsigned)b), hi = rows_of((unsigned)(b >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)hi.even << 32) | lo.even)) +
+         __longlong_as_double((long long)(((unsigned long long)hi.odd << 32) | lo.odd));
+}
+__device__ __forceinline__ unsigned half_sum_u(unsigned x) {
+  x += dpp_u32<DPP_SWAP1>(x);
+  x += dpp_u32<DPP_SWAP2>(x);
+  x += dpp_u32<DPP_HALF_MIRROR>(x);
+  x += dpp_u32<DPP_MIRROR>(x);
+  const Halves r = rows_of(x);
+  return r.even + r.odd;
+}
+__device__ __forceinline__ float half_max(float x) {
+  x = max_with_dpp<DPP_SWAP1>(x);
+  x = max_with_dpp<DPP_SWAP2>(x);
+  x = max_with_dpp<DPP_HALF_MIRROR>(x);
+  x = max_with_dpp<DPP_MIRROR>(x);
+  const Halves r = rows_of(__float_as_uint(x));
+  return max_abs(__uint_as_float(r.even), __uint_as_float(r.odd));
 }
 
 // NV: values per thread (rows per thread x VEC).  SC > 0: every workgroup runs the outer search
@@ -169,31 +221,36 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
     }
     __builtin_amdgcn_sched_barrier(0);
   };
-  // (with the search ahead: the first quarter of the rows is requested at once, the rest when
-  // the stripe is known to be needed)
-  constexpr int EARLY = ROWS >= 4 ? ROWS / 4 : 1;
+  // The rows are asked for in parts (64 KiB of them per workgroup and part): a wavefront stops at a load that the memory pipeline
+  // has no room for, and with it everything its workgroup has to do meanwhile.  With the search ahead: the first quarter at once, the
+  // rest when the stripe is known to be needed.
+  constexpr int EARLY = SC > 0 ? (ROWS < 8 ? ROWS : 8) : (ROWS >= 4 ? ROWS / 4 : 1);
+  constexpr int MIDDLE = SC > 0 ? (ROWS < 16 ? ROWS : 16) : ROWS;
   using R0 = std::integral_constant<int, 0>;
   using RE = std::integral_constant<int, EARLY>;
+  using RM = std::integral_constant<int, MIDDLE>;
   using RN = std::integral_constant<int, ROWS>;
-  auto request_stripe = [&]() { request_rows(R0(), RN()); };
 
   // Stores the lane's own columns of its rows: value(u, k) for row u, column k.  Even rows are streamed
   // past the caches.  Ragged runs end in two partly written sectors each, which the neighbouring
   // stripes (on the same XCD, see stripe_of_workgroup) complete: ordinary stores, so that the L2 can
-  // merge them (2001 x 3003: 38 against 48 us).  (There the offset and the row are made opaque in
+  // merge them (2001 x 3003: 38 against 48 us).  (The offset and the row are made opaque in
   // each branch: formed ahead of both, the addresses and row tests of all rows would sit in registers
   // beside the held data, which then spill.)
   auto store_rows = [&](auto value) {
     const int rows = (int)n;
     if constexpr (EVEN) {
       if (skip != 0) return;
+      unsigned at = off0;
+      int row = rl;
+      asm volatile("" : "+v"(at), "+v"(row));
 #pragma unroll
       for (int u = 0; u < ROWS; ++u) {
-        if (rl + u * RL < rows) {
+        if (row + u * RL < rows) {
           float f[VEC];
 #pragma unroll
           for (int k = 0; k < VEC; ++k) f[k] = value(u, k);
-          store_row<VEC, true>(reinterpret_cast<T*>(reinterpret_cast<char*>(X) + (off0 + (unsigned)u * step)), f);
+          store_row<VEC, true>(reinterpret_cast<T*>(reinterpret_cast<char*>(X) + (at + (unsigned)u * step)), f);
         }
       }
     } else {
@@ -225,17 +282,22 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
     }
   };
 
-  // The owner of column c of the stripe: thread c.
-  const long long j = s0 + tid;
-  const bool owner = tid < COLS && (EVEN || j >= own0) && j < m;
+  // The 32 lanes that step column c of the stripe: half wavefront c of the workgroup.
+  const int hc = tid / LH_HALF, hl = tid % LH_HALF;
+  const long long j = s0 + hc;
+  const bool owner = hc < COLS && (EVEN || j >= own0) && j < m;
   const long long jj = owner ? j : 0;
   double vj = 0.0;
 
   Top top;
   bool inside, nothing;
   if constexpr (SC > 0) {
-    // (the stripe is requested right behind the search's own loads: the search runs under it)
-    const SearchOut o = search_block<LH_WG, SC, LH_WG, double>(ws.v, m, seed_eta, MODE_PROJECT, outer, bs, request_stripe);
+    // (the search runs under the first half of the stripe: a quarter is requested right behind the search's own
+    // loads, a quarter ahead of its rounds; the column sum ahead of all, since loads return in order)
+    if (owner) vj = ws.v[jj];
+    __builtin_amdgcn_sched_barrier(0);
+    const SearchOut o = search_block<LH_WG, SC, LH_WG, double>(ws.v, m, seed_eta, MODE_PROJECT, outer, bs,
+                                                                      [&]() { request_rows(R0(), RE()); }, [&]() { request_rows(RE(), RM()); });
     top = top_of(o);
     inside = o.inside != 0u;
     nothing = inside || o.active == 0u;
@@ -256,156 +318,257 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
     if (bid == 0 && tid == 0) res->inner_finished = nothing ? 0u : n_active;
   }
 
-  // The owner's column: its radius, bounds and state.
+  // The column's radius, bounds and state (the same in its 32 lanes).
   double uj = 0.0, lb = 0.0, t = 0.0;
-  bool mine = false, open = false, first = true;
-  unsigned kprev = NO_COUNT;
+  bool mine = false, open = false;
   if (owner) {
-    if constexpr (SC > 0) vj = ws.v[jj];
     uj = radius_of(ws, jj, vj, top);
     mine = !inside && uj > 0.0;
     open = mine;
-    if (u_out) u_out[j] = (float)uj;
-    if (mask_out) mask_out[j] = uj > 0.0 ? 1 : 0;
+    if (hl == 0) {
+      if (u_out) u_out[j] = (float)uj;
+      if (mask_out) mask_out[j] = uj > 0.0 ? 1 : 0;
+    }
   }
   if constexpr (SC == 0) {
     // The search ran ahead, so the radii are known early: a stripe whose columns are all dropped
     // (the sparse results the projection is used for) is zeroed, and three quarters of it are
     // never read (the first quarter was requested with the radii, so that a stripe that is
     // needed does not wait twice).
-    const bool need = inside || __syncthreads_or((owner && uj > 0.0) ? 1 : 0) != 0;
+    const bool need = inside || __syncthreads_or(uj > 0.0 ? 1 : 0) != 0;
     if (!need) {
       store_rows([](int, int) { return 0.0f; });
       return;
     }
-    request_rows(RE(), RN());
+    request_rows(RE(), RM());
   }
   // (the starting guess only now: with the search ahead, the rest of the stripe is on its way)
   // a dropped column maps to zero: threshold +inf; inside the ball nothing moves: threshold 0
   t = mine ? l11_guess(vj, uj, n, lb) : (inside ? 0.0 : HUGE_VAL);   // (the same for a column somebody else owns)
 
   float held[ROWS][VEC];
-#pragma unroll
-  for (int u = 0; u < ROWS; ++u) {
+  auto widen_row = [&](int u) {
     const bool row_ok = rl + u * RL < (int)n;
 #pragma unroll
     for (int k = 0; k < VEC; ++k) held[u][k] = row_ok ? (float)raw[u].e[k] : 0.0f;   // |0| is never above a threshold
+  };
+  // What a lane found over its rows goes to LDS: first over the lanes of a 16-lane row.
+  auto file_sums = [&](double (&s)[VEC], unsigned (&cnt)[VEC]) {
+#pragma unroll
+    for (int k = 0; k < VEC; ++k) {
+      s[k] = lh_row_sum<CW>(s[k]);
+      cnt[k] = lh_row_sum_u<CW>(cnt[k]);
+    }
+    if ((lane & 15) < CW) {
+#pragma unroll
+      for (int k = 0; k < VEC; ++k) {
+        lds.s[lc + k][wave * 4 + lane / 16] = s[k];
+        lds.k[lc + k][wave * 4 + lane / 16] = cnt[k];
+      }
+    }
+  };
+
+  // First evaluation, at the guess, while the rows are still arriving: sum and count of the entries above it and the
+  // columns' largest entries.  (Also where nothing is searched: a branch around it would have the rows in two places.)
+  auto publish_threshold = [&]() {
+    const float th = (float)t;
+    lds.th[hc] = th;
+    lds.tl[hc] = t < HUGE_VAL ? (float)(t - (double)th) : 0.0f;
+  };
+  if (hl == 0 && hc < COLS) {
+    lds.hi[hc] = above(t);
+    publish_threshold();   // (final where nothing is searched)
+  }
+  request_rows(RM(), RN());
+  __syncthreads();
+  float hm[VEC];
+  double s[VEC];
+  unsigned cnt[VEC];
+  {
+    float ct[VEC];
+#pragma unroll
+    for (int k = 0; k < VEC; ++k) { ct[k] = lds.hi[lc + k]; hm[k] = 0.0f; s[k] = 0.0; cnt[k] = 0u; }
+#pragma unroll
+    for (int u = 0; u < ROWS; ++u) {
+      widen_row(u);
+#pragma unroll
+      for (int k = 0; k < VEC; ++k) {
+        const float h = fabsf(held[u][k]);
+        const bool in = h >= ct[k];
+        s[k] += (double)(in ? h : 0.0f);
+        cnt[k] += in ? 1u : 0u;
+        hm[k] = max_abs(hm[k], held[u][k]);
+      }
+#pragma unroll
+      for (int k = 0; k < VEC; ++k) asm volatile("" : "+v"(s[k]), "+v"(cnt[k]), "+v"(hm[k]));   // (row by row: nothing is put off)
+    }
   }
 
   if (!nothing) {
-    // The columns' largest entries: a_max - u_j is a second certified lower bound (the largest
-    // entry alone sums to a_max - t), next to the root where the radius is small.
-    {
-      float hm[VEC];
+    file_sums(s, cnt);
 #pragma unroll
-      for (int k = 0; k < VEC; ++k) hm[k] = 0.0f;
+    for (int k = 0; k < VEC; ++k) hm[k] = lh_row_max<CW>(hm[k]);
+    if ((lane & 15) < CW) {
 #pragma unroll
-      for (int u = 0; u < ROWS; ++u)
-#pragma unroll
-        for (int k = 0; k < VEC; ++k) hm[k] = fmaxf(hm[k], fabsf(held[u][k]));
-#pragma unroll
-      for (int k = 0; k < VEC; ++k) hm[k] = lh_row_max<CW>(hm[k]);
-      if ((lane & 15) < CW) {
-#pragma unroll
-        for (int k = 0; k < VEC; ++k) lds.s[wave * 4 + lane / 16][lc + k] = (double)hm[k];
-      }
-      __syncthreads();
-      // (the fold over the partial rows: the 64 lanes of the first wavefront take a quarter of the
-      // rows of one column each, lane = column + 16 * quarter, and meet on the crossbar)
-      double amax = 0.0;
-      if (wave == 0) {
-#pragma unroll
-        for (int w = 0; w < LH_FOLD_ROWS / 4; ++w) amax = fmax(amax, lds.s[(lane >> 4) * (LH_FOLD_ROWS / 4) + w][lane & 15]);
-        amax = fmax(amax, __shfl_xor(amax, 16));
-        amax = fmax(amax, __shfl_xor(amax, 32));
-      }
-      if (tid < COLS) {
-        if (mine) {
-          if (amax - uj > lb) lb = amax - uj;
-          if (t <= lb || t >= amax) {   // the guess is no better than the bound, or beyond every entry
-            t = lb;
-            first = false;
-          }
-        }
-        lds.ct[tid] = above(t);
-      }
-      __syncthreads();
+      for (int k = 0; k < VEC; ++k) lds.list[lc + k][wave * 4 + lane / 16] = hm[k];   // (no list yet)
     }
+    __syncthreads();
+    // The window of the next evaluation: (t, hi], or hi = t for a plain step.  With the sum and the count above a
+    // point p, and e = S / K - p the mean excess there, entries lie about e / K apart and a Newton step of length d
+    // from p ends about d^2 / (2 e) short of the root.  The window holds twice that and two entries, but no more
+    // than LH_LIST_SPAN entries.
+    double hi = HUGE_VAL;
+    unsigned kprev = NO_COUNT;
+    int windows = 0;
+    auto lay_window = [&](double S, unsigned K, double p) {
+      const float rk = __builtin_amdgcn_rcpf((float)K), d = (float)(t - p), e = (float)fma(-(double)K, p, S) * rk, gap = e * rk;
+      hi = t;
+      if (K > 0u && e > 0.0f && windows < LH_WINDOWS) {
+        const double end = t + (double)fminf(d * d * __builtin_amdgcn_rcpf(e) + 2.0f * gap, (float)LH_LIST_SPAN * gap);
+        hi = fmin(end, t + t);   // (within a factor 2 the sums of listed entries are exact, in any order)
+        if (hi > t) ++windows;
+        else hi = t;
+      }
+    };
+    auto publish = [&]() {
+      if (hl == 0 && hc < COLS) {
+        lds.hi[hc] = open ? above(hi) : INFINITY;
+        lds.lo[hc] = open ? above(t) : INFINITY;
+        lds.listed[hc] = 0u;
+        lds.open[hc] = open ? 1u : 0u;
+        publish_threshold();
+      }
+    };
+    if (hc < COLS) {   // (the same for a whole wavefront)
+      const double S = half_sum(lds.s[hc][hl]);
+      const unsigned K = half_sum_u(lds.k[hc][hl]);
+      const float amax = half_max(lds.list[hc][hl]);
+      if (mine) {
+        // (a_max - u_j is a second certified lower bound: the largest entry alone sums to a_max - t; it lies next to the root
+        // where the radius is small)
+        const double g = t;
+        lb = fmax(lb, (double)amax - uj);
+        t = K > 0u ? fmax((S - uj) / (double)K, lb) : lb;
+        lay_window(S, K, g);
+      }
+    }
+    publish();
+    __syncthreads();
     for (;;) {
-      float ct[VEC];
+      // Evaluation at the upper ends; the entries of the windows are listed.
+      float ch[VEC], cl[VEC];
 #pragma unroll
-      for (int k = 0; k < VEC; ++k) ct[k] = lds.ct[lc + k];
-      double s[VEC];
-      unsigned cnt[VEC];
-#pragma unroll
-      for (int k = 0; k < VEC; ++k) { s[k] = 0.0; cnt[k] = 0u; }
+      for (int k = 0; k < VEC; ++k) {
+        ch[k] = lds.hi[lc + k];
+        cl[k] = k < skip ? INFINITY : lds.lo[lc + k];   // (a column's entries are listed by the lane that owns it)
+        s[k] = 0.0;
+        cnt[k] = 0u;
+      }
 #pragma unroll
       for (int u = 0; u < ROWS; ++u) {
+        unsigned long long listed[VEC], any = 0ull;   // lane masks
 #pragma unroll
         for (int k = 0; k < VEC; ++k) {
           asm volatile("" : "+v"(held[u][k]));   // keeps the widening to fp64 in the loop: hoisted, it doubles the registers
           const float h = fabsf(held[u][k]);
-          const bool in = h >= ct[k];
+          const bool in = h >= ch[k];
           s[k] += (double)(in ? h : 0.0f);
           cnt[k] += in ? 1u : 0u;
+          listed[k] = __ballot(h >= cl[k]) & ~__ballot(in);
+          any |= listed[k];
+        }
+#pragma unroll
+        for (int k = 0; k < VEC; ++k) asm volatile("" : "+v"(s[k]), "+v"(cnt[k]));   // (the sums are not put off beyond the branch)
+        if (any != 0ull) {   // (one entry in some hundreds)
+          unsigned found = 0u;
+#pragma unroll
+          for (int k = 0; k < VEC; ++k) found |= __builtin_amdgcn_inverse_ballot_w64(listed[k]) ? 1u << k : 0u;
+          while (found != 0u) {
+            const int k = __ffs(found) - 1;
+            float h = held[u][0];
+#pragma unroll
+            for (int e = 1; e < VEC; ++e) h = k == e ? held[u][e] : h;
+            const unsigned at = atomicAdd(&lds.listed[lc + k], 1u);
+            if (at < (unsigned)LH_LIST) lds.list[lc + k][at] = fabsf(h);
+            found &= found - 1u;
+          }
         }
       }
-#pragma unroll
-      for (int k = 0; k < VEC; ++k) {
-        s[k] = lh_row_sum<CW>(s[k]);
-        cnt[k] = lh_row_sum_u<CW>(cnt[k]);
-      }
-      if ((lane & 15) < CW) {
-#pragma unroll
-        for (int k = 0; k < VEC; ++k) {
-          lds.s[wave * 4 + lane / 16][lc + k] = s[k];
-          lds.k[wave * 4 + lane / 16][lc + k] = cnt[k];
-        }
-      }
+      file_sums(s, cnt);
       __syncthreads();
-      double S = 0.0;
-      unsigned K = 0u;
-      if (wave == 0) {   // (as for the maxima above; always in this order, so the sums repeat bit for bit)
+      if (hc < COLS) {
+        const double S = half_sum(lds.s[hc][hl]);
+        const unsigned K = half_sum_u(lds.k[hc][hl]);
+        const unsigned listed = lds.listed[hc];
+        const bool window = open && hi > t;
+        const bool solve = window && listed <= (unsigned)LH_LIST;
+        double tn = t;
+        // Inside the window: the fixed point over the listed entries and what lies above them, from the bound t.
+        float x[LH_LIST / LH_HALF];
 #pragma unroll
-        for (int w = 0; w < LH_FOLD_ROWS / 4; ++w) {
-          S += lds.s[(lane >> 4) * (LH_FOLD_ROWS / 4) + w][lane & 15];
-          K += lds.k[(lane >> 4) * (LH_FOLD_ROWS / 4) + w][lane & 15];
+        for (int q = 0; q < LH_LIST / LH_HALF; ++q) {
+          const unsigned i = (unsigned)(hl + q * LH_HALF);
+          x[q] = solve && i < listed ? lds.list[hc][i] : 0.0f;
         }
-        S += __shfl_xor(S, 16);
-        K += __shfl_xor(K, 16);
-        S += __shfl_xor(S, 32);
-        K += __shfl_xor(K, 32);
-      }
-      if (owner && open) {
-        if (first) {
-          // from the guess: step to its fixed-point image (a lower bound from any point), or
-          // back to the bound if it overshot every entry
-          kprev = K > 0u ? K : NO_COUNT;
-          t = K > 0u ? fmax((S - uj) / (double)K, lb) : lb;
-        } else if (K == 0u || K == kprev) {
-          open = false;   // t came from this very active set: it is the root
-        } else {
-          kprev = K;
-          const double tn = (S - uj) / (double)K;
-          if (tn > t) t = tn;
-          else open = false;   // no move left: t is the root, to rounding
+        bool going = solve;
+        unsigned kk = NO_COUNT;
+        while (__any(going ? 1 : 0)) {
+          const float c = above(t);
+          double ls = 0.0;
+          unsigned lk = 0u;
+#pragma unroll
+          for (int q = 0; q < LH_LIST / LH_HALF; ++q) {
+            const bool in = x[q] >= c;
+            ls += (double)(in ? x[q] : 0.0f);
+            lk += in ? 1u : 0u;
+          }
+          ls = S + half_sum(ls);
+          lk = K + half_sum_u(lk);
+          if (going) {
+            if (lk == 0u || lk == kk) {
+              going = open = false;   // t came from this very active set: it is the root
+            } else {
+              kk = lk;
+              tn = (ls - uj) / (double)lk;
+              if (tn > hi) going = false;      // the root lies beyond the window
+              else if (tn > t) t = tn;
+              else going = open = false;       // no move left: t is the root, to rounding
+            }
+          }
         }
-        first = false;
-        lds.ct[tid] = above(t);
+        if (open && window) {
+          kprev = NO_COUNT;
+          if (solve) {   // tn is a lower bound, and so is the step from the upper end
+            const double p = hi;
+            t = K > 0u ? fmax(tn, (S - uj) / (double)K) : tn;
+            lay_window(S, K, p);
+          } else {       // more entries than the list takes (ties): plain steps from here on
+            if (K > 0u) t = fmax(t, (S - uj) / (double)K);
+            windows = LH_WINDOWS;
+            hi = t;
+          }
+        } else if (open) {
+          if (K == 0u || K == kprev) {
+            open = false;   // t came from this very active set: it is the root
+          } else {
+            const double p = t;
+            kprev = K;
+            tn = (S - uj) / (double)K;
+            if (tn > t) t = tn;
+            else open = false;   // no move left: t is the root, to rounding
+            lay_window(S, K, p);
+          }
+        }
       }
-      if (!__syncthreads_or((owner && open) ? 1 : 0)) break;
+      publish();
+      __syncthreads();
+      if (!__any(lds.open[tid % COLS] != 0u)) break;
     }
   }
-  if (tid < COLS) {
-    const float th = (float)t;
-    lds.th[tid] = th;
-    lds.tl[tid] = t < HUGE_VAL ? (float)(t - (double)th) : 0.0f;
-    if (mine) {
-      ws.tauj[j] = t;
-      ws.done[j] = 1u;
-    }
+  if (hl == 0 && mine) {
+    ws.tauj[j] = t;
+    ws.done[j] = 1u;
   }
-  __syncthreads();
   float th[VEC], tl[VEC];
 #pragma unroll
   for (int k = 0; k < VEC; ++k) {

@@ -15,6 +15,14 @@ template <int CTRL>
 __device__ __forceinline__ unsigned dpp_u32(unsigned x) {
   return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, false);
 }
+// (where every lane has a source lane: no neutral element to set up)
+template <int CTRL>
+__device__ __forceinline__ double dpp_all_f64(double x) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)b, CTRL, 0xf, 0xf, true);
+  const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
 template <int CTRL>
 __device__ __forceinline__ double dpp_f64(double x) {
   const unsigned long long b = (unsigned long long)__double_as_longlong(x);
@@ -33,8 +41,8 @@ __device__ __forceinline__ double bcast63_f64(double x) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 __device__ __forceinline__ double wave_sum(double x) {
-  x += dpp_f64<DPP_SWAP1>(x);
-  x += dpp_f64<DPP_SWAP2>(x);
+  x += dpp_all_f64<DPP_SWAP1>(x);
+  x += dpp_all_f64<DPP_SWAP2>(x);
   x += dpp_f64<DPP_SHR4>(x);
   x += dpp_f64<DPP_SHR8>(x);
   x += dpp_f64<DPP_BCAST15>(x);
@@ -43,8 +51,8 @@ __device__ __forceinline__ double wave_sum(double x) {
 }
 // maximum of non-negative values
 __device__ __forceinline__ double wave_max(double x) {
-  x = fmax(x, dpp_f64<DPP_SWAP1>(x));
-  x = fmax(x, dpp_f64<DPP_SWAP2>(x));
+  x = fmax(x, dpp_all_f64<DPP_SWAP1>(x));
+  x = fmax(x, dpp_all_f64<DPP_SWAP2>(x));
   x = fmax(x, dpp_f64<DPP_SHR4>(x));
   x = fmax(x, dpp_f64<DPP_SHR8>(x));
   x = fmax(x, dpp_f64<DPP_BCAST15>(x));
@@ -106,35 +114,37 @@ __device__ __forceinline__ unsigned block_sum_u(unsigned x, BlockScratch<NW>& s)
 // Two reductions for the price of one barrier pair: (sum, max) and (sum, count).
 template <int NW>
 struct PairScratch {
-  double a[NW];
+  double a[2][NW];
   double b[NW];
-  unsigned u[NW];
+  unsigned u[2][NW];
+  double top[NW * WAVE];   // every thread's largest value (see subset_bound)
 };
 // (AT_ONCE: how many waves' pairs are fetched together; fewer where registers are short)
 template <int NW, int AT_ONCE = NW>
 __device__ __forceinline__ void block_sum_max(double& sum, double& mx, PairScratch<NW>& s) {
   sum = wave_sum(sum);
   mx = wave_max(mx);
-  if ((threadIdx.x & (WAVE - 1)) == 0) { s.a[threadIdx.x / WAVE] = sum; s.b[threadIdx.x / WAVE] = mx; }
+  if ((threadIdx.x & (WAVE - 1)) == 0) { s.a[0][threadIdx.x / WAVE] = sum; s.b[threadIdx.x / WAVE] = mx; }
   __syncthreads();
   double r = 0.0, q = 0.0;
 #pragma unroll AT_ONCE
-  for (int w = 0; w < NW; ++w) { r += s.a[w]; q = fmax(q, s.b[w]); }
+  for (int w = 0; w < NW; ++w) { r += s.a[0][w]; q = fmax(q, s.b[w]); }
   __syncthreads();
   sum = r;
   mx = q;
 }
+// `turn`: 0 and 1 in turn over the calls of a loop.  The halves of the scratch alternate, so a call needs no second barrier:
+// a wavefront writes a half again only behind the barrier of the next call, where everybody has read it.
 template <int NW>
-__device__ __forceinline__ void block_sum_count(double& sum, unsigned& cnt, PairScratch<NW>& s) {
+__device__ __forceinline__ void block_sum_count(double& sum, unsigned& cnt, PairScratch<NW>& s, int turn) {
   sum = wave_sum(sum);
   cnt = wave_sum_u(cnt);
-  if ((threadIdx.x & (WAVE - 1)) == 0) { s.a[threadIdx.x / WAVE] = sum; s.u[threadIdx.x / WAVE] = cnt; }
+  if ((threadIdx.x & (WAVE - 1)) == 0) { s.a[turn][threadIdx.x / WAVE] = sum; s.u[turn][threadIdx.x / WAVE] = cnt; }
   __syncthreads();
   double r = 0.0;
   unsigned c = 0;
 #pragma unroll
-  for (int w = 0; w < NW; ++w) { r += s.a[w]; c += s.u[w]; }
-  __syncthreads();
+  for (int w = 0; w < NW; ++w) { r += s.a[turn][w]; c += s.u[turn][w]; }
   sum = r;
   cnt = c;
 }
@@ -183,13 +193,13 @@ __device__ __forceinline__ void block_sum2_count(double& sum, double& sum2, unsi
   sum2 = wave_sum(sum2);
   cnt = wave_sum_u(cnt);
   if ((threadIdx.x & (WAVE - 1)) == 0) {
-    s.a[threadIdx.x / WAVE] = sum; s.b[threadIdx.x / WAVE] = sum2; s.u[threadIdx.x / WAVE] = cnt;
+    s.a[0][threadIdx.x / WAVE] = sum; s.b[threadIdx.x / WAVE] = sum2; s.u[0][threadIdx.x / WAVE] = cnt;
   }
   __syncthreads();
   double r = 0.0, q = 0.0;
   unsigned c = 0;
 #pragma unroll 4   // (all 16 triples at once would take 80 registers)
-  for (int w = 0; w < NW; ++w) { r += s.a[w]; q += s.b[w]; c += s.u[w]; }
+  for (int w = 0; w < NW; ++w) { r += s.a[0][w]; q += s.b[w]; c += s.u[0][w]; }
   __syncthreads();
   sum = r;
   sum2 = q;
@@ -204,11 +214,11 @@ constexpr int DPP_ROR4 = 0x124, DPP_ROR8 = 0x128;
 
 template <int SEG>
 __device__ __forceinline__ double seg_sum(double x) {
-  x += dpp_f64<DPP_SWAP1>(x);
-  x += dpp_f64<DPP_SWAP2>(x);
+  x += dpp_all_f64<DPP_SWAP1>(x);
+  x += dpp_all_f64<DPP_SWAP2>(x);
   if constexpr (SEG >= 16) {
-    x += dpp_f64<DPP_ROR4>(x);
-    x += dpp_f64<DPP_ROR8>(x);
+    x += dpp_all_f64<DPP_ROR4>(x);
+    x += dpp_all_f64<DPP_ROR8>(x);
   }
   if constexpr (SEG == 64) {
     const unsigned long long b = (unsigned long long)__double_as_longlong(x);
@@ -225,11 +235,11 @@ __device__ __forceinline__ double seg_sum(double x) {
 }
 template <int SEG>
 __device__ __forceinline__ double seg_max(double x) {  // non-negative values
-  x = fmax(x, dpp_f64<DPP_SWAP1>(x));
-  x = fmax(x, dpp_f64<DPP_SWAP2>(x));
+  x = fmax(x, dpp_all_f64<DPP_SWAP1>(x));
+  x = fmax(x, dpp_all_f64<DPP_SWAP2>(x));
   if constexpr (SEG >= 16) {
-    x = fmax(x, dpp_f64<DPP_ROR4>(x));
-    x = fmax(x, dpp_f64<DPP_ROR8>(x));
+    x = fmax(x, dpp_all_f64<DPP_ROR4>(x));
+    x = fmax(x, dpp_all_f64<DPP_ROR8>(x));
   }
   if constexpr (SEG == 64) {
     const unsigned long long b = (unsigned long long)__double_as_longlong(x);

@@ -43,6 +43,51 @@ __device__ __forceinline__ double radius_of(const Ws& ws, long long j, double v,
 __device__ __forceinline__ Top top_of(const SearchOut& o) { return Top{o.tau, o.scale, o.cap}; }
 __device__ __forceinline__ Top top_of(const mlproj_result* r) { return Top{r->tau, r->scale, r->cap}; }
 
+// The threshold, in standard deviations, above which a standard normal variable keeps the share `ratio` of its mean magnitude:
+// the root of sqrt(2/pi) exp(-z^2/2) - z erfc(z/sqrt(2)) = sqrt(2/pi) ratio, as a rational function of L = -log(ratio) fitted to
+// that root (1e-4 up to L = 18, rising on beyond).  Starting guesses only, which are off by percents anyway: eight Newton steps with
+// erfc and exp took 0.5 to 2 us of a workgroup that waits for them.
+__device__ __forceinline__ float gauss_z(float ratio) {
+  const float L = fmaxf(-__logf(ratio), 0.0f);
+  return L * (0.79788456f + L * (0.185144017f + L * 0.0055651016f)) *
+         __builtin_amdgcn_rcpf(1.0f + L * (0.413713398f + L * (0.0311353461f + L * 0.000218333676f)));
+}
+
+// A lower bound on the root from few of the values: the root over ANY subset of v lies at or left of the root
+// over v (the subset's sum above a threshold is no larger).  The subset is every thread's largest value, which
+// where few groups survive holds nearly all that do, and each wavefront works its root out for itself, NT / 64 values
+// per lane, without a barrier: a round costs a tenth of one over v.  `tau` is a lower bound already; a first
+// step that does not pass it ends the attempt (dense results: one round).  (1000 x 10000 l1,2, 12 groups
+// survive: two rounds over v instead of ten.)
+constexpr double SUBSET_SURVIVORS = 32.0;
+template <int NT>
+__device__ __forceinline__ double subset_bound(const double* top, double tau, double eta, double vmax) {
+  // (S values above tau sum to at most S (vmax - tau): not worth it unless some tens of them could hold eta)
+  if (!(SUBSET_SURVIVORS * (vmax - tau) > eta)) return tau;
+  const int lane = threadIdx.x & (WAVE - 1);
+  double w[NT / WAVE];
+#pragma unroll
+  for (int k = 0; k < NT / WAVE; ++k) w[k] = top[lane + k * WAVE];
+  double at = tau;
+  unsigned kprev = 0xffffffffu;
+  for (;;) {
+    double sum = 0.0;
+    unsigned cnt = 0;
+#pragma unroll
+    for (int k = 0; k < NT / WAVE; ++k)
+      if (w[k] > at) { sum += w[k]; ++cnt; }
+    sum = wave_sum(sum);
+    cnt = wave_sum_u(cnt);
+    if (cnt == 0u || cnt == kprev) break;
+    kprev = cnt;
+    const double t = (sum - eta) / (double)cnt;
+    if (!(t > at)) break;
+    at = t;
+  }
+  // (a little left of it: the sums are rounded, and the search proper must not start beyond its root)
+  return fmax(tau, at - 1e-12 * vmax);
+}
+
 // NTHREADS > NT: a larger workgroup runs the search of an NT-thread one; the threads beyond
 // NT hold nothing and add zeros, so the result has the bits the NT-thread workgroup gets.
 // VT: the type v is stored in where the search reads it (fp64 in the workspace; fp32 for exact
@@ -51,12 +96,17 @@ __device__ __forceinline__ Top top_of(const mlproj_result* r) { return Top{r->ta
 // caller that has loads of its own to issue (data the search does not depend on) issues them
 // there, so that the search runs while they are in flight (loads return in order: issued ahead
 // of v's, they would hold up the search's first wait).
+// after_sums: called once more when v has arrived and its total is known, ahead of the rounds: a wavefront stops at a
+// load that the memory pipeline has no room for, and its workgroup at the next barrier, so a caller with much
+// to load asks for a part of it here.
 struct NothingAfterLoads { __device__ __forceinline__ void operator()() const {} };
-template <int NT, int CACHE = SEARCH_CACHE, int NTHREADS = NT, typename VT = double, typename AfterLoads = NothingAfterLoads>
+template <int NT, int CACHE = SEARCH_CACHE, int NTHREADS = NT, typename VT = double, typename AfterLoads = NothingAfterLoads,
+          typename AfterSums = NothingAfterLoads>
 __device__ __forceinline__ SearchOut search_block(const VT* __restrict__ v, long long ngroups,
                                                   double eta, int mode, int outer,
                                                   PairScratch<NTHREADS / WAVE>& s,
-                                                  AfterLoads after_loads = AfterLoads()) {
+                                                  AfterLoads after_loads = AfterLoads(),
+                                                  AfterSums after_sums = AfterSums()) {
   static_assert(NTHREADS >= NT && NTHREADS % WAVE == 0, "whole wavefronts, at least NT threads");
   // (a thread beyond NT starts past the end of v: every bound check below leaves it idle)
   const long long tid = (NTHREADS == NT || threadIdx.x < NT) ? (long long)threadIdx.x : ngroups;
@@ -94,7 +144,9 @@ __device__ __forceinline__ SearchOut search_block(const VT* __restrict__ v, long
     mx = fmax(mx, x);
   }
   SearchOut o;
+  if (NTHREADS == NT || threadIdx.x < NT) s.top[threadIdx.x] = mx;
   block_sum_max(a, mx, s);
+  after_sums();
   o.total = a;
   o.vmax = mx;
   o.norm = a;
@@ -116,7 +168,7 @@ __device__ __forceinline__ SearchOut search_block(const VT* __restrict__ v, long
       sq = fma(x, x, sq);
       c += x > 0.0 ? 1u : 0u;
     }
-    block_sum_count(sq, c, s);
+    block_sum_count(sq, c, s, 0);
     (void)dummy;
     if (outer == MLPROJ_OUTER_L2) {
       o.norm = sqrt(sq);
@@ -137,12 +189,13 @@ __device__ __forceinline__ SearchOut search_block(const VT* __restrict__ v, long
     for (long long i = tid + (long long)CACHE * NT; i < ngroups; i += NT)
       c += (double)v[i] > 0.0 ? 1u : 0u;
     double zero = 0.0;
-    block_sum_count(zero, c, s);
+    block_sum_count(zero, c, s, 0);
     o.active = c;
   } else {
     // two lower bounds on the root: all groups active, and only the largest active
-    double tau = fmax((o.total - eta) / (double)ngroups, o.vmax - eta);
+    double tau = subset_bound<NT>(s.top, fmax((o.total - eta) / (double)ngroups, o.vmax - eta), eta, o.vmax);
     unsigned kprev = 0xffffffffu;
+    int turn = 0;
     for (;;) {
       double sum = 0.0;
       unsigned cnt = 0;
@@ -153,7 +206,8 @@ __device__ __forceinline__ SearchOut search_block(const VT* __restrict__ v, long
         const double x = (double)v[i];
         if (x > tau) { sum += x; ++cnt; }
       }
-      block_sum_count(sum, cnt, s);
+      block_sum_count(sum, cnt, s, turn);
+      turn ^= 1;
       const double S = sum;
       const unsigned K = cnt;
       o.active = K;

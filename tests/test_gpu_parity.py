@@ -118,6 +118,25 @@ def test_many_columns_use_the_grid_wide_search(mp, q, shape):
         check_against_oracle(run_gpu(mp, Y, eta, q), orc.bilevel(Y, eta, q), q)
 
 
+@pytest.mark.parametrize("m", [600, 4096, 4100, 10000, 16384])
+@pytest.mark.parametrize("stride", [1, 256, 512])
+def test_outer_search_with_few_groups_left(mp, m, stride):
+    """The outer search starts from the root over its threads' largest values: the surviving groups lie in many threads, or
+    share a few of them (stride = a workgroup's threads), close together, tied and far apart."""
+    rng = np.random.default_rng([m, stride])
+    base = rng.uniform(0.5, 1.0, m)
+    at = (7 + stride * np.arange(min(40, (m - 8) // stride))) % m
+    for lift in (1e-3, 0.5, 100.0):
+        col = base.copy()
+        col[at] = 1.0 + lift * np.linspace(0.0, 1.0, at.size) ** 2
+        col[at[: at.size // 2]] = 1.0 + lift
+        Y = np.stack([col, -0.5 * col, 0.25 * col]).astype(np.float32)
+        for q in ("inf", 1, 2):
+            for frac in (1e-4, 1e-3, 0.02):
+                eta = eta_for(Y, q, frac)
+                check_against_oracle(run_gpu(mp, Y, eta, q), orc.bilevel(Y, eta, q), q)
+
+
 @pytest.mark.parametrize("limit", [0, 64])
 def test_grid_wide_search_gives_up_and_the_kernel_behind_it_takes_over(mp, limit):
     """With a poll limit of 0 the several-workgroup search leaves at once and the one-workgroup
@@ -1563,6 +1582,31 @@ def test_l11_columns_in_registers_on_adversarial_columns(mp, name):
     Y = np.ascontiguousarray(Y[:, : Y.shape[1] // 4 * 4])
     for frac in (1e-4, 0.01, 0.3, 0.9, 0.999):
         eta = eta_for(Y, 1, frac)
+        got = run_gpu(mp, Y, eta, 1)
+        check_against_oracle(got, orc.bilevel(Y, eta, 1), 1)
+        assert_columns_in_registers(got["res"])
+
+
+@pytest.mark.parametrize("ties", [1, 2, 31, 32, 33, 127, 128, 129, 500])
+def test_l11_columns_in_registers_entries_close_to_the_threshold(mp, ties):
+    """The window the second evaluation lists (128 entries per column): as many entries as named lie next to the root of
+    every column, equal in some columns and one float apart in the others, on wide, ragged and narrow stripes."""
+    for n, m in ((1500, 48), (1499, 37), (4500, 24)):
+        rng = np.random.default_rng([n, ties])
+        Y = rng.standard_normal((n, m)).astype(np.float32)
+        eta = eta_for(Y, 1, 0.2)
+        ref = orc.bilevel(Y, eta, 1)
+        kept = np.abs(ref["X"]) > 0
+        for j in range(m):
+            rows = np.flatnonzero(kept[:, j])
+            if rows.size == 0:
+                continue
+            root = np.float32(np.abs(Y[rows[0], j].astype(np.float64)) - np.abs(ref["X"][rows[0], j]))
+            near = np.full(ties, root)
+            if j % 2:
+                near = (root.view(np.int32) + np.arange(ties) - ties // 2).astype(np.int32).view(np.float32)
+            where = rng.permutation(n)[:ties]
+            Y[where, j] = np.where(Y[where, j] < 0, -near, near)
         got = run_gpu(mp, Y, eta, 1)
         check_against_oracle(got, orc.bilevel(Y, eta, 1), 1)
         assert_columns_in_registers(got["res"])
