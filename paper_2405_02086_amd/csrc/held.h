@@ -254,8 +254,9 @@ __global__ __launch_bounds__(HELD_WG) void held_slab_kernel(const T* Y, T* X, lo
     __syncthreads();
   }
 
-  // 4. tau, by every workgroup for itself (the search of the three-kernel chain: same bits)
-  SearchOut o = search_block<WG, 4, HELD_WG, float>(sm_v, d0, eta, MODE_PROJECT, MLPROJ_OUTER_L1, bs);
+  // 4. tau, by every wavefront for itself (at most 256 slabs; no barriers)
+  static_assert(HELD_POST_WORDS <= 4 * WAVE, "four slabs per lane");
+  SearchOut o = search_wave<4, float>(sm_v, (int)d0, eta, MLPROJ_OUTER_L1);
   if (!complete) o.tau = __longlong_as_double(0x7ff8000000000000LL);   // never reached (see above): make it loud
   const Top top = top_of(o);
   if (piece == 0) {

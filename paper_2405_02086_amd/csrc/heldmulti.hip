@@ -89,14 +89,23 @@ __device__ __forceinline__ void hm_slab_radii(const double* v, double* out, int 
       par = HUGE_VAL;
     } else {
       const double floor_t = (nv - r) / (double)d1;
-      const float guess = -0.75f * (float)(nv / (double)d1) * __logf((float)(r / nv));
+      const float guess = (float)(nv / (double)d1) * 1.25331414f * gauss_z((float)(r * __builtin_amdgcn_rcp(nv)));
       bool first = (double)guess > floor_t;
       par = first ? (double)guess : floor_t;
       unsigned kprev = 0xffffffffu;
+      // (the first of a lane's norms stay in registers: in LDS every step reads them again)
+      constexpr int KEPT = 8;
+      double kept[KEPT];
+#pragma unroll
+      for (int k = 0; k < KEPT; ++k) kept[k] = lane + k * WAVE < d1 ? v[lane + k * WAVE] : 0.0;
       for (;;) {
         double s = 0.0;
         unsigned c = 0;
-        for (int i = lane; i < d1; i += WAVE) {
+#pragma unroll
+        for (int k = 0; k < KEPT; ++k) {
+          if (k * WAVE < d1 && kept[k] > par) { s += kept[k]; ++c; }
+        }
+        for (int i = lane + KEPT * WAVE; i < d1; i += WAVE) {
           const double x = v[i];
           if (x > par) { s += x; ++c; }
         }
@@ -136,6 +145,28 @@ __device__ __forceinline__ void hm_keep_stored(Pack<T, VEC> (&x)[KPF]) {
       __builtin_memcpy(&x[k], w, 16);
     }
   }
+}
+
+// max(d, 0) with the sign of x, d rounded to fp32 and then to the storage type.
+template <typename T>
+__device__ __forceinline__ T round_to_signed(double d, float x) {
+  float f = copysignf(fmaxf((float)d, 0.0f), x);
+  if constexpr (sizeof(T) == 2) asm("" : "+v"(f));   // (see round_to)
+  return (T)f;
+}
+
+// Sum of fp32 values over the lanes of a segment (4 or 16 lanes): for steps that need no more.
+template <int SEG>
+__device__ __forceinline__ float hm_seg_sum_f(float x) {
+  auto step = [&](auto ctrl) { x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, true)); };
+  step(std::integral_constant<int, DPP_SWAP1>());
+  step(std::integral_constant<int, DPP_SWAP2>());
+  if constexpr (SEG == 16) {
+    step(std::integral_constant<int, 0x141>());   // mirror of 8 lanes
+    step(std::integral_constant<int, 0x140>());   // mirror of 16 lanes
+  }
+  static_assert(SEG == 4 || SEG == 16, "segments of a quad or a row");
+  return x;
 }
 
 // above() of l11.h, without its test for an infinite t in the serial part of every step: that t gives a NaN here, and
@@ -290,7 +321,9 @@ __global__ __launch_bounds__(HM_WG) void held_multi_kernel(const void* Yv, void*
   }
 
   // 4. tau, by every workgroup for itself
-  SearchOut o = search_block<WG, HM_MAX_SLABS / WG, HM_WG, double>(sm_w, p.d0, eta, MODE_PROJECT, outer, bs);
+  // (few slabs: every wavefront for itself, without barriers)
+  SearchOut o = p.d0 <= WAVE_SEARCH_MAX ? search_wave<WAVE_SEARCH_CACHE, double>(sm_w, p.d0, eta, outer)
+                                        : search_block<WG, HM_MAX_SLABS / WG, HM_WG, double>(sm_w, p.d0, eta, MODE_PROJECT, outer, bs);
   if (!complete) o.tau = __longlong_as_double(0x7ff8000000000000LL);   // never reached: make it loud
   const Top top = top_of(o);
   if (wg == 0) {
@@ -308,7 +341,11 @@ __global__ __launch_bounds__(HM_WG) void held_multi_kernel(const void* Yv, void*
   }
   __syncthreads();
 
-  // 6. the fibres, from the registers
+  // 6. the fibres, from the registers.  (All loads are over.  Said here once: loads and stores share a counter, and the wait that
+  // the compiler, for want of knowing, puts in front of a round's registers in the searches waits for the stores of the round
+  // before.  256 x 256 x 256 l1,1,1: 41.7 -> 40.7 us; with 4 lanes per fibre it gains nothing and costs up to 2 %.)
+  if constexpr (Q == Q1 && SEG == 16) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+  const double per_element = 1.0 / (double)p.len;
 #pragma unroll
   for (int j = 0; j < ROUNDS; ++j) {
     if (j < p.rounds) {
@@ -319,43 +356,123 @@ __global__ __launch_bounds__(HM_WG) void held_multi_kernel(const void* Yv, void*
       hm_keep_stored(d[j]);
       if constexpr (Q == Q2) par = nv > r ? r / nv : 1.0;
       if constexpr (Q == Q1) {
-        // (the fixed point of fibre_map_cached_kernel, on the elements as fp32: |x| > t is |x| >= above(t))
+        // The fixed point of fibre_map_cached_kernel, on the elements as fp32: |x| > t is |x| >= above(t).  What the search costs is
+        // vector instructions (the memory is idle meanwhile), so the steps far from the root are taken on fp32 sums, without a
+        // quotient in fp64, until a step passes so few entries that the next one hardly passes any; and the last one is known
+        // by no entry lying around it instead of by evaluating there once more.
         bool open = nv > r && r > 0.0 && f < fibres;
-        const double floor_t = open ? (nv - r) / (double)p.len : 0.0;
-        const float guess = open ? -0.75f * (float)(nv / (double)p.len) * __logf((float)(r / nv)) : 0.0f;
-        bool first = (double)guess > floor_t;
-        par = first ? (double)guess : floor_t;
+        const double floor_t = open ? (nv - r) * per_element : 0.0;
         if (nv > r && !(r > 0.0)) par = HUGE_VAL;
-        unsigned kprev = 0xffffffffu;
-        while (__any(open)) {
-          const float ct = hm_above(par);
-          double s = 0.0;
-          unsigned c = 0;
-          hm_keep_stored(d[j]);
+        const float ratio = (float)(r * __builtin_amdgcn_rcp(nv)), rs = (float)r, floor_f = (float)floor_t;
+        float at = open ? fmaxf((float)(nv * per_element) * 1.25331414f * gauss_z(ratio), floor_f) : HUGE_VALF;
+        if constexpr (SEG == 4) {
+          // (16 fibres share a wavefront: what a step costs beside its elements counts little, and the fewest steps win)
+          bool first = (double)at > floor_t;
+          par = open ? (first ? (double)at : floor_t) : par;
+          unsigned kfull = 0u;
+          while (__any(open)) {
+            const float ct = hm_above(par);
+            double s = 0.0;
+            unsigned c = 0;
+            hm_keep_stored(d[j]);
 #pragma unroll
-          for (int k = 0; k < KPF; ++k)
+            for (int k = 0; k < KPF; ++k)
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) {
-              const float h = fabsf((float)d[j][k].e[e]);
-              const bool in = h >= ct;
-              s += (double)(in ? h : 0.0f);
-              c += in ? 1u : 0u;
+              for (int e = 0; e < VEC; ++e) {
+                const float h = fabsf((float)d[j][k].e[e]);
+                const bool in = h >= ct;
+                s += (double)(in ? h : 0.0f);
+                c += in ? 1u : 0u;
+              }
+            s = seg_sum<SEG>(s);
+            c = seg_sum_u<SEG>(c);
+            const double t = (s - r) / (double)c;
+            if (open) {
+              if (first) {
+                kfull = c;
+                par = c > 0u ? fmax(t, floor_t) : floor_t;
+              } else if (c == 0u || c == kfull) {
+                open = false;
+              } else {
+                kfull = c;
+                if (t > par) par = t;
+              }
             }
-          s = seg_sum<SEG>(s);
-          c = seg_sum_u<SEG>(c);
-          const double t = (s - r) / (double)c;
-          if (open) {
-            if (first) {
-              kprev = c > 0u ? c : 0xffffffffu;
-              par = c > 0u ? fmax(t, floor_t) : floor_t;
-            } else if (c == 0u || c == kprev) {
-              open = false;
-            } else {
+            first = false;
+          }
+        } else {
+          float bound = floor_f, margin = 0.0f;
+          bool rough = open;
+          unsigned kprev = 0u;
+          for (int step = 0; step < 6 && __any(rough); ++step) {
+            float s = 0.0f;
+            unsigned c = 0;
+            hm_keep_stored(d[j]);
+  #pragma unroll
+            for (int k = 0; k < KPF; ++k)
+  #pragma unroll
+              for (int e = 0; e < VEC; ++e) {
+                const float h = fabsf((float)d[j][k].e[e]);
+                const bool in = h > at;
+                s += in ? h : 0.0f;
+                c += in ? 1u : 0u;
+              }
+            s = hm_seg_sum_f<SEG>(s);
+            c = seg_sum_u<SEG>(c);
+            if (rough) {
+              const float rc = __builtin_amdgcn_rcpf((float)c), moved = (float)c - (float)kprev;
+              // (from any point the step ends at or left of the root, and 64 fp32 additions are off by less than the margin; a point
+              // beyond every entry says nothing: back towards the bound)
+              if (c > 0u) {
+                margin = 8e-6f * s * rc;
+                at = bound = fmaxf((s - rs) * rc - margin, floor_f);
+                rough = moved * moved > (float)c;
+              } else {
+                at = fmaxf(0.6f * at, floor_f);
+              }
               kprev = c;
-              if (t > par) par = t;
             }
           }
-          first = false;
+          if (open) par = fmax((double)bound, floor_t);
+          // (t is the root if it came from the active set of a point left of it and no entry lies between: the fp32 steps have
+          // left a window (par, end] that holds it more often than not, and the entries of the window show in the same pass)
+          double end = par + (double)(2.0f * margin);
+          bool first = true;
+          unsigned kfull = 0u;
+          while (__any(open)) {
+            const float ct = hm_above(par), ce = hm_above(end);
+            double s = 0.0;
+            unsigned c = 0;
+            unsigned long long between = 0ull;   // lanes with an entry in the window
+            hm_keep_stored(d[j]);
+  #pragma unroll
+            for (int k = 0; k < KPF; ++k)
+  #pragma unroll
+              for (int e = 0; e < VEC; ++e) {
+                const float h = fabsf((float)d[j][k].e[e]);
+                const bool in = h >= ct;
+                s += (double)(in ? h : 0.0f);
+                c += in ? 1u : 0u;
+                between |= __ballot(in) ^ __ballot(h >= ce);
+                asm volatile("" : "+s"(between));   // (at once: put off, the masks of all elements spill)
+              }
+            s = seg_sum<SEG>(s);
+            c = seg_sum_u<SEG>(c);
+            const bool clear = ((between >> (lane & ~(SEG - 1))) & ((1ull << SEG) - 1ull)) == 0ull;
+            if (open) {
+              if (c == 0u || c == kfull) {
+                open = false;
+              } else {
+                const double t = (s - r) / (double)c;
+                const bool inside = clear && t >= par && t <= end;
+                open = !inside && (first || t > par);
+                if (first || t > par) par = fmax(t, floor_t);   // (the first may step back)
+                end = par + (double)(2.0f * margin);
+                kfull = c;
+              }
+            }
+            first = false;
+          }
         }
         hm_keep_stored(d[j]);
       }
@@ -369,7 +486,7 @@ __global__ __launch_bounds__(HM_WG) void held_multi_kernel(const void* Yv, void*
           const float x = (float)d[j][k].e[e];
           if constexpr (Q == QINF) z.e[e] = (T)copysignf(fminf(fabsf(x), rf), x);
           else if constexpr (Q == Q2) z.e[e] = round_to<T>((double)x * par);
-          else z.e[e] = round_to<T>(copysign(fmax(fabs((double)x) - par, 0.0), (double)x));
+          else z.e[e] = round_to_signed<T>((double)fabsf(x) - par, x);
         }
         const int b = f < fibres ? hl.blank(p, k) : VEC;
         if (b == 0) {
