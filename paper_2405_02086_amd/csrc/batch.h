@@ -128,15 +128,16 @@ __global__ __launch_bounds__(WG) void colmap_batch_kernel(BatchItems it, BatchGr
   const Ws ws = bind(b.ws, layout_for(g, b.m, Q));
   const T* Y = static_cast<const T*>(b.Y);
   T* X = static_cast<T*>(b.X);
-  const double eta = Q == Q1 ? -1.0 : b.eta;   // l1,1: tau comes from the record, not from a search here
+  constexpr int SEARCH = Q == Q1 ? 0 : SC;   // l1,1: tau comes from the record, not from a search here
+  const double eta = b.eta;
   const int form = map_form(b.wide != 0, b.m, WIDE);
   const bool wave = RIDE && b.whole != 0;
   if (form == MAP_EVEN)
-    colmap_body<Q, T, WIDE, MAP_EVEN, SC>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid, wave);
+    colmap_body<Q, T, WIDE, MAP_EVEN, SEARCH, MAP_AHEAD>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid, wave);
   else if (form == MAP_RAGGED)
-    colmap_body<Q, T, WIDE, MAP_RAGGED, SC>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid, wave);
+    colmap_body<Q, T, WIDE, MAP_RAGGED, SEARCH, MAP_AHEAD>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid, wave);
   else
-    colmap_body<Q, T, WIDE, MAP_STRIDED, SC>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid, wave);
+    colmap_body<Q, T, WIDE, MAP_STRIDED, SEARCH, MAP_AHEAD>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid, wave);
 }
 
 // Matrices of at most 128 KiB each: the one-kernel form of tiny.h for all of them in one launch

@@ -17,8 +17,9 @@ namespace mlproj {
 // read last there (the ones most likely still cached) are read first here.  For q = 1 the pass before
 // is a listing sweep, which itself runs bottom up after the aggregate pass, so the order is top down
 // (both together: 9001 x 3003 l1,1 148.6 -> 146.3 us; 16384 x 16384 746 -> 742, hardly more than two runs differ).
-// With fused_eta >= 0 every workgroup first runs the threshold search itself (see
-// search_block) and workgroup 0 files the result record; otherwise tau is read from it.
+// SC > 0: every workgroup first runs the threshold search itself (see search_block; SC values of v per thread) and
+// workgroup 0 files the result record; SC = 0: a search kernel ran before and tau is read from it (a build of its own, which
+// the search's registers do not hold back where a CU runs several workgroups).
 // FORM: how a lane reaches its columns (see LaneCols).  MAP_EVEN: 16-byte accesses, m a multiple of
 // VEC; MAP_RAGGED: 16-byte accesses, any m >= VEC; MAP_STRIDED: one element per access.  (The test
 // for the ragged lane at every store costs 1 % where there is none: 35.6 against 35.9 us at 4096 x 4096.)
@@ -39,7 +40,7 @@ __host__ __device__ static inline int map_form(bool wide, long long m, int vec) 
   return MAP_RAGGED;
 }
 
-template <int Q, typename T, int VEC, int FORM, int SC>
+template <int Q, typename T, int VEC, int FORM, int SC, int AHEAD>
 __device__ __forceinline__ void colmap_body(const T* Y, T* X, long long n, long long m,
                                             const Geometry& g, const Ws& ws,
                                             float* __restrict__ u_out,
@@ -72,18 +73,40 @@ __device__ __forceinline__ void colmap_body(const T* Y, T* X, long long n, long 
       if (row < n) lc.load(Y + row * m, dst[r]);
     }
   };
-  // The first block is requested before tau is known, so its latency hides the search.
-  if (col_ok && inside_rows(b)) load_block(b, x);
+  // The first block is requested before tau is known, so its latency hides the search.  AHEAD > 1: that many blocks, the first
+  // behind the search's own loads and the others when those have arrived (asked for ahead of them they hold up the
+  // wavefronts, and with them the search).
+  Pack<T, VEC> ahead[AHEAD > 1 ? AHEAD - 1 : 1][U];
+  auto request_first = [&]() {
+    if (col_ok && inside_rows(b)) load_block(b, x);
+  };
+  auto request_ahead = [&]() {
+#pragma unroll
+    for (int a = 0; a < AHEAD - 1; ++a) {
+      const long long blk = b + (a + 1) * step;
+      if (col_ok && inside_rows(blk)) load_block(blk, ahead[a]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
 
   Top top;
   bool inside;
-  if (fused_eta >= 0.0) {
-    const SearchOut o = wave_search ? search_wave<WAVE_SEARCH_CACHE, double>(ws.v, (int)m, fused_eta, outer)
-                                    : search_block<WG, SC>(ws.v, m, fused_eta, MODE_PROJECT, outer, bs);
+  if constexpr (SC > 0) {
+    SearchOut o;
+    if (wave_search || AHEAD == 1) request_first();
+    if (wave_search) {
+      request_ahead();
+      o = search_wave<WAVE_SEARCH_CACHE, double>(ws.v, (int)m, fused_eta, outer);
+    } else if constexpr (AHEAD > 1) {
+      o = search_block<WG, SC, WG, double>(ws.v, m, fused_eta, MODE_PROJECT, outer, bs, request_first, request_ahead);
+    } else {
+      o = search_block<WG, SC>(ws.v, m, fused_eta, MODE_PROJECT, outer, bs);
+    }
     top = top_of(o);
     inside = o.inside != 0u;
     if (bid == 0 && threadIdx.x == 0) write_result(ws, o, nullptr);
   } else {
+    request_first();
     top = top_of(ws.res);
     inside = ws.res->inside_ball != 0u;
   }
@@ -160,6 +183,32 @@ __device__ __forceinline__ void colmap_body(const T* Y, T* X, long long n, long 
     else return (T)copysignf(fmaxf((fabsf(yv) - th[k]) - tl[k], 0.0f), yv);
   };
 
+  auto store_block = [&](long long blk, const Pack<T, VEC> (&src)[U]) {
+#pragma unroll
+    for (int r = 0; r < U; ++r) {
+      const long long row = blk * MAP_RBLK + wave + (long long)r * WAVES;
+      if (row < n) {
+        Pack<T, VEC> f;
+#pragma unroll
+        for (int k = 0; k < VEC; ++k) f.e[k] = apply((float)src[r].e[k], k);
+        lc.store_nt(X + row * m, f);
+      }
+    }
+  };
+  // The blocks requested under the search; the loads of the pipeline's next one go out ahead of their stores.
+  if constexpr (SC > 0 && AHEAD > 1) {
+    const long long nb = b + AHEAD * step;
+    if (inside_rows(nb)) load_block(nb, y);
+    if (inside_rows(b)) store_block(b, x);
+#pragma unroll
+    for (int a = 0; a < AHEAD - 1; ++a) {
+      const long long blk = b + (a + 1) * step;
+      if (inside_rows(blk)) store_block(blk, ahead[a]);
+    }
+#pragma unroll
+    for (int r = 0; r < U; ++r) x[r] = y[r];
+    b = nb;
+  }
   // Software pipeline: the next block's loads are issued first, then this block is mapped
   // and stored, and only then does the wavefront wait.  On gfx9 loads and stores share one
   // counter, so any wait for a load also waits for every store issued before it: the wait
@@ -169,28 +218,19 @@ __device__ __forceinline__ void colmap_body(const T* Y, T* X, long long n, long 
   for (; inside_rows(b); b += step) {
     const long long nb = b + step;
     if (inside_rows(nb)) load_block(nb, y);
-#pragma unroll
-    for (int r = 0; r < U; ++r) {
-      const long long row = b * MAP_RBLK + wave + (long long)r * WAVES;
-      if (row < n) {
-        Pack<T, VEC> f;
-#pragma unroll
-        for (int k = 0; k < VEC; ++k) f.e[k] = apply((float)x[r].e[k], k);
-        lc.store_nt(X + row * m, f);
-      }
-    }
+    store_block(b, x);
 #pragma unroll
     for (int r = 0; r < U; ++r) x[r] = y[r];
   }
 }
 
-template <int Q, typename T, int VEC, int FORM, int SC = SEARCH_CACHE>
+template <int Q, typename T, int VEC, int FORM, int SC, int AHEAD>
 __global__ __launch_bounds__(WG) void colmap_kernel(const T* Y, T* X, long long n,
                                                     long long m, Geometry g, Ws ws,
                                                     float* __restrict__ u_out,
                                                     unsigned char* __restrict__ mask_out,
                                                     double fused_eta, int outer) {
-  colmap_body<Q, T, VEC, FORM, SC>(Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer, blockIdx.x);
+  colmap_body<Q, T, VEC, FORM, SC, AHEAD>(Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer, blockIdx.x);
 }
 
 }  // namespace mlproj

@@ -492,16 +492,21 @@ static int run_bilevel(const T* Y, T* X, long long n, long long m, float eta,
   if (stages & STAGE_APPLY) {
     mark(stream);
     const int form = map_form(wide, m, WIDE);
-    if (fuse_big && form == MAP_EVEN)   // (more than 4096 columns: wide whatever the alignment)
-      launch((colmap_kernel<Q, T, WIDE, MAP_EVEN, SEARCH_CACHE_BIG>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
-    else if (fuse_big)
-      launch((colmap_kernel<Q, T, WIDE, MAP_RAGGED, SEARCH_CACHE_BIG>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
-    else if (form == MAP_EVEN)
-      launch((colmap_kernel<Q, T, WIDE, MAP_EVEN>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
-    else if (form == MAP_RAGGED)
-      launch((colmap_kernel<Q, T, WIDE, MAP_RAGGED>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
-    else
-      launch((colmap_kernel<Q, T, WIDE, MAP_STRIDED>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
+    auto map = [&](auto f, auto sc) {
+      launch((colmap_kernel<Q, T, WIDE, decltype(f)::value, decltype(sc)::value, 1>), mgrid, block, stream, Y, X, n, m, g, ws, u_out, mask_out, fused_eta, outer);
+    };
+    auto by_form = [&](auto sc) {
+      if (form == MAP_EVEN) map(std::integral_constant<int, MAP_EVEN>(), sc);
+      else if (decltype(sc)::value == SEARCH_CACHE_BIG || form == MAP_RAGGED) map(std::integral_constant<int, MAP_RAGGED>(), sc);   // (more than 4096 columns: wide whatever the alignment)
+      else map(std::integral_constant<int, decltype(sc)::value == SEARCH_CACHE_BIG ? MAP_RAGGED : MAP_STRIDED>(), sc);
+    };
+    if constexpr (Q == Q1) {
+      by_form(std::integral_constant<int, 0>());   // (the search ran with the inner searches)
+    } else {
+      if (fused_eta < 0.0) by_form(std::integral_constant<int, 0>());
+      else if (fuse_big) by_form(std::integral_constant<int, SEARCH_CACHE_BIG>());
+      else by_form(std::integral_constant<int, SEARCH_CACHE>());
+    }
   }
   mark(stream);
   return launch_status();
@@ -1135,7 +1140,7 @@ using namespace mlproj;
 
 extern "C" {
 
-int mlproj_version(void) { return 388; }
+int mlproj_version(void) { return 389; }
 
 const char* mlproj_status_string(int status) {
   switch (status) {
