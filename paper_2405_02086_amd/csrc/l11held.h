@@ -15,17 +15,21 @@ namespace mlproj {
 // lock-step sweeps of l11.h read the whole matrix once per step because a column is strided in
 // memory.  A matrix of at most 4096 rows lets one workgroup hold 16 whole columns instead (one
 // 64-byte run of every row, as the finishing pass does): 512 threads x up to 128 elements.  The
-// workgroup reads its stripe once, runs the fixed point of the finishing pass on registers
-// (no memory traffic per step), and maps and stores from the same registers: after the
-// aggregate pass Y is read once and X written once, whatever the number of steps.
+// workgroup reads its stripe once, finds the thresholds on registers (no memory traffic per
+// step), and maps and stores from the same registers: after the aggregate pass Y is read once
+// and X written once, whatever the number of steps.
+// What bounds it: loads, searches and stores are one chain in every workgroup (4096 x 4096, one per CU: 12 us of loads
+// with the outer search and the first evaluation under them, 9 us of steps, 12 us of stores), and an evaluation
+// of all held entries costs 3 to 4 us there.  So as few of them as possible: the first is at the guess, every further one lists the
+// entries of a window that should hold the root, and among those it is found exactly (two evaluations as a rule instead of
+// three to eight; 4096 x 4096 54.1 -> 50.0 us per call, 2001 x 3003 38.0 -> 33.4).
 //
 // A lane owns VEC = 16 bytes' worth of neighbouring columns (one vector access per row), CW
 // lanes span the stripe, and the thread of row lane r holds rows r, r + RL, r + 2 RL, ...  The
 // partial sums and counts of a column are folded over the row lanes of a 16-lane row on the
 // DPP crossbar (rotations by CW, 2 CW, ... 8), then over the 4 rows of each of the 8
-// wavefronts through LDS by the first wavefront (four lanes per column), always in the same
-// order: the result repeats bit for bit.  The column's owner thread steps its threshold and
-// publishes it.
+// wavefronts through LDS by the 32 lanes that step the column, always in the same order, and
+// the listed entries add up exactly in any order: the result repeats bit for bit.
 constexpr int LH_WG = 512;
 constexpr int LH_COLS = 16;
 constexpr int LH_COLS_NARROW = 8;   // fp32, 4097 to 8192 rows: stripes of 8 columns (32-byte runs), 128 values per thread
@@ -89,7 +93,7 @@ static inline int lh_values(long long n, long long m, bool apart) {
 }
 
 constexpr int LH_LIST = 128;            // window entries kept per column
-constexpr int LH_LIST_SPAN = 48;        // ... and the most a window is laid out for
+constexpr int LH_LIST_SPAN = 40;        // ... and the most a window is laid out for
 constexpr int LH_WINDOWS = 6;           // windows a column tries before it goes on in plain steps
 constexpr int LH_HALF = 32;             // lanes that step one column
 
@@ -195,8 +199,8 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
   // stripe before it (in a row shorter than a stripe the last lanes overlap their neighbours instead;
   // m >= VEC).  The overlap is loaded and summed like the rest.  Lanes of one workgroup that overlap (m < COLS) hold
   // the same values and file the same sums; columns of the stripe before belong to another workgroup, which in place may be
-  // storing them meanwhile: what comes of them reaches no threshold (their owner thread here is none, so it neither
-  // opens nor steps them), no loop exit and no store.  Even rows: a lane past the end shadows the last columns and stores nothing.
+  // storing them meanwhile: what comes of them reaches no threshold (no lanes here own them, so nothing opens or
+  // steps them), no loop exit and no store.  Even rows: a lane past the end shadows the last columns and stores nothing.
   const long long own0 = bid * COLS;                 // first column the workgroup owns
   const long long s0 = EVEN || own0 + COLS <= m ? own0 : (m < COLS ? 0 : m - COLS);   // first column of the stripe
   const long long want = s0 + (long long)cw * VEC;
@@ -221,11 +225,12 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
     }
     __builtin_amdgcn_sched_barrier(0);
   };
-  // The rows are asked for in parts (64 KiB of them per workgroup and part): a wavefront stops at a load that the memory pipeline
-  // has no room for, and with it everything its workgroup has to do meanwhile.  With the search ahead: the first quarter at once, the
-  // rest when the stripe is known to be needed.
-  constexpr int EARLY = SC > 0 ? (ROWS < 8 ? ROWS : 8) : (ROWS >= 4 ? ROWS / 4 : 1);
-  constexpr int MIDDLE = SC > 0 ? (ROWS < 16 ? ROWS : 16) : ROWS;
+  // The rows are asked for in parts: a wavefront stops at a load that the memory pipeline has no room for, and with it
+  // everything its workgroup has to do meanwhile.  With the search inside (rows behind its loads of v / ahead of its rounds too, us): 4096 x
+  // 4096 4 / 12 50.4, 8 / 8 51.0, 8 / 16 50.0, 8 / 24 50.0, all 32 at once 54.6; 2001 x 3003 4 / 12 33.4, 8 / 8 33.7, 8 / 16 34.5.  With
+  // the search ahead: the first quarter at once, the rest when the stripe is known to be needed.
+  constexpr int EARLY = SC > 0 ? (ROWS <= 16 ? 4 : 8) : (ROWS >= 4 ? ROWS / 4 : 1);
+  constexpr int MIDDLE = SC > 0 ? (ROWS <= 8 ? ROWS : ROWS <= 16 ? 12 : 16) : ROWS;
   using R0 = std::integral_constant<int, 0>;
   using RE = std::integral_constant<int, EARLY>;
   using RM = std::integral_constant<int, MIDDLE>;
@@ -292,8 +297,7 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
   Top top;
   bool inside, nothing;
   if constexpr (SC > 0) {
-    // (the search runs under the first half of the stripe: a quarter is requested right behind the search's own
-    // loads, a quarter ahead of its rounds; the column sum ahead of all, since loads return in order)
+    // (the search runs under a part of the stripe; the column sum is requested ahead of all, since loads return in order)
     if (owner) vj = ws.v[jj];
     __builtin_amdgcn_sched_barrier(0);
     const SearchOut o = search_block<LH_WG, SC, LH_WG, double>(ws.v, m, seed_eta, MODE_PROJECT, outer, bs,
@@ -415,17 +419,19 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
     __syncthreads();
     // The window of the next evaluation: (t, hi], or hi = t for a plain step.  With the sum and the count above a
     // point p, and e = S / K - p the mean excess there, entries lie about e / K apart and a Newton step of length d
-    // from p ends about d^2 / (2 e) short of the root.  The window holds twice that and two entries, but no more
-    // than LH_LIST_SPAN entries.
+    // from p ends about d^2 / (2 e) short of the root.  The window holds twice that and two entries; where that comes to
+    // more than LH_LIST_SPAN entries the next step is a plain one (Laplace entries, 4000 x 3000, us: at most 12 entries
+    // 58.3, 24 53.4, 40 53.5, without windows 56.4).
     double hi = HUGE_VAL;
     unsigned kprev = NO_COUNT;
     int windows = 0;
+    bool certain = true;    // t is a lower bound on the root
     auto lay_window = [&](double S, unsigned K, double p) {
       const float rk = __builtin_amdgcn_rcpf((float)K), d = (float)(t - p), e = (float)fma(-(double)K, p, S) * rk, gap = e * rk;
+      const float width = d * d * __builtin_amdgcn_rcpf(e) + 2.0f * gap;
       hi = t;
-      if (K > 0u && e > 0.0f && windows < LH_WINDOWS) {
-        const double end = t + (double)fminf(d * d * __builtin_amdgcn_rcpf(e) + 2.0f * gap, (float)LH_LIST_SPAN * gap);
-        hi = fmin(end, t + t);   // (within a factor 2 the sums of listed entries are exact, in any order)
+      if (K > 0u && e > 0.0f && width <= (float)LH_LIST_SPAN * gap && windows < LH_WINDOWS) {
+        hi = fmin(t + (double)width, t + t);   // (within a factor 2 the sums of listed entries are exact, in any order)
         if (hi > t) ++windows;
         else hi = t;
       }
@@ -448,8 +454,15 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
         // where the radius is small)
         const double g = t;
         lb = fmax(lb, (double)amax - uj);
-        t = K > 0u ? fmax((S - uj) / (double)K, lb) : lb;
-        lay_window(S, K, g);
+        if (K > 0u) {
+          t = fmax((S - uj) / (double)K, lb);
+          lay_window(S, K, g);
+        } else {
+          // the guess lies beyond every entry: on to where entries spread evenly up to a_max would have the root
+          t = fmax(lb, (double)amax - sqrt(2.0 * (double)amax * uj / (double)n));
+          certain = t == lb;
+          hi = t;
+        }
       }
     }
     publish();
@@ -496,7 +509,7 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
       }
       file_sums(s, cnt);
       __syncthreads();
-      if (hc < COLS) {
+      if (__any(open ? 1 : 0)) {   // (a wavefront whose columns are closed has no step to take)
         const double S = half_sum(lds.s[hc][hl]);
         const unsigned K = half_sum_u(lds.k[hc][hl]);
         const unsigned listed = lds.listed[hc];
@@ -547,6 +560,12 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
             windows = LH_WINDOWS;
             hi = t;
           }
+        } else if (open && !certain) {
+          // from any point the step ends at or left of the root
+          const double p = t;
+          certain = true;
+          t = K > 0u ? fmax((S - uj) / (double)K, lb) : lb;
+          lay_window(S, K, p);
         } else if (open) {
           if (K == 0u || K == kprev) {
             open = false;   // t came from this very active set: it is the root
