@@ -30,8 +30,9 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0
 # HBM-side bytes per launch of the map kernel from the rocprofv3 --pmc runs summarised in
 # profiles/ (FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, in KiB), valid for these library versions only.
-TRAFFIC_VERSIONS = (388,)   # the library versions the counters in profiles/ hold for
-TRAFFIC_KIB = {"square_4096": 32972.1 * 1.999 + 65622.5, "square_16384": 524931.1 * 1.999 + 1048631.2,
+# (square_4096 taken at 389; the other two at 388, whose kernels move the same bytes)
+TRAFFIC_VERSIONS = (389, 388)   # the library versions the counters in profiles/ hold for
+TRAFFIC_KIB = {"square_4096": 32985.3 * 1.999 + 65558.6, "square_16384": 524931.1 * 1.999 + 1048631.2,
                "tensor_256x256x256": 32903.1 * 1.999 + 65626.1}
 INFINITY_CACHE_BYTES = 256 * 1024 * 1024
 
