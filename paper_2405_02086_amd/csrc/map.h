@@ -75,7 +75,8 @@ __device__ __forceinline__ void colmap_body(const T* Y, T* X, long long n, long 
   };
   // The first block is requested before tau is known, so its latency hides the search.  AHEAD > 1: that many blocks, the first
   // behind the search's own loads and the others when those have arrived (asked for ahead of them they hold up the
-  // wavefronts, and with them the search).
+  // wavefronts, and with them the search).  Batches take MAP_AHEAD = 4: 16 x (1024 x 1024) 41.1 -> 38.9 us per call; single calls, one
+  // workgroup per CU and a band of rows that should stay narrow, one block: 4096 x 4096 35.0 with 1, 35.2 with 2, 35.6 us with 4.
   Pack<T, VEC> ahead[AHEAD > 1 ? AHEAD - 1 : 1][U];
   auto request_first = [&]() {
     if (col_ok && inside_rows(b)) load_block(b, x);
