@@ -345,7 +345,8 @@ __global__ __launch_bounds__(HM_WG) void held_multi_kernel(const void* Yv, void*
   // the compiler, for want of knowing, puts in front of a round's registers in the searches waits for the stores of the round
   // before.  256 x 256 x 256 l1,1,1: 41.7 -> 40.7 us; with 4 lanes per fibre it gains nothing and costs up to 2 %.)
   if constexpr (Q == Q1 && SEG == 16) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
-  const double per_element = 1.0 / (double)p.len;
+  // (a little less than 1 / len: the all-active bound (nv - r) / len must not be rounded to the right of the root)
+  const double per_element = (1.0 - 0x1p-51) / (double)p.len;
 #pragma unroll
   for (int j = 0; j < ROUNDS; ++j) {
     if (j < p.rounds) {
@@ -363,7 +364,9 @@ __global__ __launch_bounds__(HM_WG) void held_multi_kernel(const void* Yv, void*
         bool open = nv > r && r > 0.0 && f < fibres;
         const double floor_t = open ? (nv - r) * per_element : 0.0;
         if (nv > r && !(r > 0.0)) par = HUGE_VAL;
-        const float ratio = (float)(r * __builtin_amdgcn_rcp(nv)), rs = (float)r, floor_f = (float)floor_t;
+        // (floor_f rounded down: rounded up it may reach the entries of a fibre in which all are equal, and a search that starts there sees
+        // none above it and ends: 256 x 256 x 256 ones at a radius of 0.1 came out as zeros)
+        const float ratio = (float)(r * __builtin_amdgcn_rcp(nv)), rs = (float)r, floor_f = float_at_or_below(floor_t);
         float at = open ? fmaxf((float)(nv * per_element) * 1.25331414f * gauss_z(ratio), floor_f) : HUGE_VALF;
         if constexpr (SEG == 4) {
           // (16 fibres share a wavefront: what a step costs beside its elements counts little, and the fewest steps win)
@@ -421,10 +424,10 @@ __global__ __launch_bounds__(HM_WG) void held_multi_kernel(const void* Yv, void*
             c = seg_sum_u<SEG>(c);
             if (rough) {
               const float rc = __builtin_amdgcn_rcpf((float)c), moved = (float)c - (float)kprev;
-              // (from any point the step ends at or left of the root, and 64 fp32 additions are off by less than the margin; a point
-              // beyond every entry says nothing: back towards the bound)
+              // (from any point the step ends at or left of the root, and 64 fp32 additions are off by less than the margin, subnormal
+              // sums included; a point beyond every entry says nothing: back towards the bound)
               if (c > 0u) {
-                margin = 8e-6f * s * rc;
+                margin = fmaf(8e-6f * s, rc, 1e-43f);
                 at = bound = fmaxf((s - rs) * rc - margin, floor_f);
                 rough = moved * moved > (float)c;
               } else {

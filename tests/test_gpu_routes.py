@@ -274,6 +274,59 @@ def test_multilevel_in_one_pass_on_16_bit_storage(mp, storage, taken, shape, nor
     assert torch.equal(mp.multilevel_proj_stored(Yd, norms, eta, X=Yd), X)
 
 
+# Fibres whose entries are equal or nearly so, at radii far below an fp32 unit of them: every layout of the one-pass kernel (4 lanes; 16 with 4, 8 and
+# 16 chunks each), ragged last chunks, and the chain.
+FLAT = [("f32", True, (20, 16, 100)), ("f32", True, (20, 16, 129)), ("f32", True, (20, 8, 256)), ("f32", True, (20, 8, 511)), ("f32", True, (200, 30, 1001)),
+        ("f32", True, (256, 256, 256)), ("f32", True, (256, 64, 1024)), ("f32", False, (3, 4, 1500)), ("bf16", True, (20, 30, 512)), ("bf16", True, (200, 30, 1001)),
+        ("f16", True, (20, 8, 512)), ("f16", True, (250, 32, 1024)), ("f16", False, (3, 4, 2000))]
+
+
+def assert_near(X, want, tol, storage):
+    """Every entry within tol of the wanted value, as the storage type rounds the ends of that range."""
+    got = X.float().cpu().numpy()
+    assert np.all(got >= orc.round_to_storage((want - tol).astype(np.float32), storage))
+    assert np.all(got <= orc.round_to_storage((want + tol).astype(np.float32), storage))
+
+
+@pytest.mark.parametrize("storage,taken,shape", FLAT)
+def test_multilevel_l1_of_constant_fibres(mp, storage, taken, shape):
+    """All magnitudes a: every entry keeps eta / (number of entries) and its sign, whatever the radius.  A threshold is a difference of
+    64-bit sums (at most 128 additions to one, three levels): 512 units of 2^-53 relative to the norm, 512 x 2^-53 / share relative to the result."""
+    assert one_pass(mp, storage, shape, [1, 1]) == taken
+    gen = torch.Generator(device="cuda").manual_seed(shape[2])
+    signs = torch.randint(0, 2, shape, generator=gen, device="cuda").mul_(2).sub_(1)
+    for a in (1.0, 0.703125, 24576.0):
+        Y = (signs if a != 1.0 else torch.ones_like(signs)).to(getattr(torch, STORE_DTYPES[storage])) * a
+        for share in (0.25, 1e-3, 2e-8, 1e-10):
+            eta = float(np.float32(share * a * Y.numel()))
+            want = Y.sign().float().cpu().numpy().astype(np.float64) * (eta / Y.numel())
+            tol = (2.0 ** -22 + 512 * 2.0 ** -53 / share) * (eta / Y.numel())
+            assert_near(mp.multilevel_proj_stored(Y, [1, 1], eta), want, tol, storage)
+
+
+@pytest.mark.parametrize("kind", ["tied", "close", "heavy"])
+@pytest.mark.parametrize("storage,taken,shape", [c for c in FLAT if c[2][0] <= 20])
+def test_multilevel_l1_of_fibres_hard_to_search(mp, storage, taken, shape, kind):
+    """Two values a few storage units apart, values in steps of one unit, and a few entries of a Cauchy sample far above the rest, at small radii, against
+    the oracle; the bound as for constant fibres, absolute: a fibre whose other entries are dropped has the norm's rounding in one of them."""
+    assert one_pass(mp, storage, shape, [1, 1]) == taken
+    rng = np.random.default_rng(list(shape) + [len(kind)])
+    unit = {"f32": 2.0 ** -23, "bf16": 2.0 ** -7, "f16": 2.0 ** -10}[storage]
+    if kind == "tied":
+        Y = 1.0 + 4 * unit * rng.integers(0, 2, shape)
+    elif kind == "close":
+        Y = 1.0 + unit * rng.integers(0, 9, shape)
+    else:
+        Y = np.clip(np.abs(rng.standard_cauchy(shape)), 1e-3, 6e4)
+    Y = orc.round_to_storage((Y * rng.choice([-1.0, 1.0], shape)).astype(np.float32), storage)
+    Yd = torch.from_numpy(Y).cuda().to(getattr(torch, STORE_DTYPES[storage]))
+    for share in (0.02, 1e-4, 1e-7):
+        eta = float(np.float32(share * nested_norm(Y, [1, 1])))
+        ref = orc.multilevel(Y, [1, 1], eta)
+        want = ref["U"][0]
+        assert_near(mp.multilevel_proj_stored(Yd, [1, 1], eta), want, 2.0 ** -22 * np.abs(want) + 512 * 2.0 ** -53 * ref["w"].max(), storage)
+
+
 def test_multilevel_in_one_pass_in_a_graph(mp):
     """Replays of a captured call, eager calls on other contents between them."""
     assert one_pass(mp, "f32", (200, 40, 60), [1, 1])
