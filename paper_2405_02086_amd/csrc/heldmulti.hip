@@ -78,7 +78,9 @@ __device__ __forceinline__ double hm_slab_norm(const double* v, int d1, int q2) 
 }
 
 // The radii of a slab's d1 fibres, by one wavefront: its fibre norms v (q2-norm nv) projected onto the
-// q2-ball of radius r (the map of fibre.h, see fibre_map_cached_kernel for the starting point).
+// q2-ball of radius r (the map and the steps of fibre_map_cached_kernel, from the threshold Gaussian entries would have).  The norms are
+// read from LDS in every step: eight of them per lane in registers cost small tensors more than they gave large ones (2048 x 2 x 50 l1,1,1
+// 14.3 / 13.7 us, 256 x 256 x 256 39.4 / 39.1).
 __device__ __forceinline__ void hm_slab_radii(const double* v, double* out, int d1, int q2, double nv, double r) {
   const int lane = threadIdx.x & (WAVE - 1);
   double par = 0.0;
@@ -93,19 +95,10 @@ __device__ __forceinline__ void hm_slab_radii(const double* v, double* out, int 
       bool first = (double)guess > floor_t;
       par = first ? (double)guess : floor_t;
       unsigned kprev = 0xffffffffu;
-      // (the first of a lane's norms stay in registers: in LDS every step reads them again)
-      constexpr int KEPT = 8;
-      double kept[KEPT];
-#pragma unroll
-      for (int k = 0; k < KEPT; ++k) kept[k] = lane + k * WAVE < d1 ? v[lane + k * WAVE] : 0.0;
       for (;;) {
         double s = 0.0;
         unsigned c = 0;
-#pragma unroll
-        for (int k = 0; k < KEPT; ++k) {
-          if (k * WAVE < d1 && kept[k] > par) { s += kept[k]; ++c; }
-        }
-        for (int i = lane + KEPT * WAVE; i < d1; i += WAVE) {
+        for (int i = lane; i < d1; i += WAVE) {
           const double x = v[i];
           if (x > par) { s += x; ++c; }
         }
