@@ -340,159 +340,176 @@ __global__ __launch_bounds__(HM_WG) void held_multi_kernel(const void* Yv, void*
   if constexpr (Q == Q1 && SEG == 16) __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
   // (a little less than 1 / len: the all-active bound (nv - r) / len must not be rounded to the right of the root)
   const double per_element = (1.0 - 0x1p-51) / (double)p.len;
+  // With 16 lanes per fibre the rounds go through the code in two passes, the second half of the registers moved to the first in
+  // between: unrolled as a whole the two loops of the search, once per round, come to 90 KB, more than the instruction
+  // cache, and a call that follows other kernels fetches them anew (256 x 256 x 256 l1,1,1 behind a product, a copy and an l1,1
+  // projection 70 us, in two passes 61, repeated 39.3 / 38.9; what both replaced 64, repeated 43.8).
+  constexpr int PASS = Q == Q1 && SEG == 16 && ROUNDS >= 4 ? ROUNDS / 2 : ROUNDS;
+#pragma unroll 1
+  for (int j0 = 0;;) {
 #pragma unroll
-  for (int j = 0; j < ROUNDS; ++j) {
-    if (j < p.rounds) {
-      const int f = j * NSEG + seg;
-      const int fc = f < fibres ? f : fibres - 1;
-      const double nv = sm_v[fc], r = sm_r[fc];
-      double par = 0.0;
-      hm_keep_stored(d[j]);
-      if constexpr (Q == Q2) par = nv > r ? r / nv : 1.0;
-      if constexpr (Q == Q1) {
-        // The fixed point of fibre_map_cached_kernel, on the elements as fp32: |x| > t is |x| >= above(t).  What the search costs is
-        // vector instructions (the memory is idle meanwhile), so the steps far from the root are taken on fp32 sums, without a
-        // quotient in fp64, until a step passes so few entries that the next one hardly passes any; and the last one is known
-        // by no entry lying around it instead of by evaluating there once more.
-        bool open = nv > r && r > 0.0 && f < fibres;
-        const double floor_t = open ? (nv - r) * per_element : 0.0;
-        if (nv > r && !(r > 0.0)) par = HUGE_VAL;
-        // (floor_f rounded down: rounded up it may reach the entries of a fibre in which all are equal, and a search that starts there sees
-        // none above it and ends: 256 x 256 x 256 ones at a radius of 0.1 came out as zeros)
-        const float ratio = (float)(r * __builtin_amdgcn_rcp(nv)), rs = (float)r, floor_f = float_at_or_below(floor_t);
-        float at = open ? fmaxf((float)(nv * per_element) * 1.25331414f * gauss_z(ratio), floor_f) : HUGE_VALF;
-        if constexpr (SEG == 4) {
-          // (16 fibres share a wavefront: what a step costs beside its elements counts little, and the fewest steps win)
-          bool first = (double)at > floor_t;
-          par = open ? (first ? (double)at : floor_t) : par;
-          unsigned kfull = 0u;
-          while (__any(open)) {
-            const float ct = hm_above(par);
-            double s = 0.0;
-            unsigned c = 0;
-            hm_keep_stored(d[j]);
-#pragma unroll
-            for (int k = 0; k < KPF; ++k)
-#pragma unroll
-              for (int e = 0; e < VEC; ++e) {
-                const float h = fabsf((float)d[j][k].e[e]);
-                const bool in = h >= ct;
-                s += (double)(in ? h : 0.0f);
-                c += in ? 1u : 0u;
-              }
-            s = seg_sum<SEG>(s);
-            c = seg_sum_u<SEG>(c);
-            const double t = (s - r) / (double)c;
-            if (open) {
-              if (first) {
-                kfull = c;
-                par = c > 0u ? fmax(t, floor_t) : floor_t;
-              } else if (c == 0u || c == kfull) {
-                open = false;
-              } else {
-                kfull = c;
-                if (t > par) par = t;
-              }
-            }
-            first = false;
-          }
-        } else {
-          float bound = floor_f, margin = 0.0f;
-          bool rough = open;
-          unsigned kprev = 0u;
-          for (int step = 0; step < 6 && __any(rough); ++step) {
-            float s = 0.0f;
-            unsigned c = 0;
-            hm_keep_stored(d[j]);
-  #pragma unroll
-            for (int k = 0; k < KPF; ++k)
-  #pragma unroll
-              for (int e = 0; e < VEC; ++e) {
-                const float h = fabsf((float)d[j][k].e[e]);
-                const bool in = h > at;
-                s += in ? h : 0.0f;
-                c += in ? 1u : 0u;
-              }
-            s = hm_seg_sum_f<SEG>(s);
-            c = seg_sum_u<SEG>(c);
-            if (rough) {
-              const float rc = __builtin_amdgcn_rcpf((float)c), moved = (float)c - (float)kprev;
-              // (from any point the step ends at or left of the root, and 64 fp32 additions are off by less than the margin, subnormal
-              // sums included; a point beyond every entry says nothing: back towards the bound)
-              if (c > 0u) {
-                margin = fmaf(8e-6f * s, rc, 1e-43f);
-                at = bound = fmaxf((s - rs) * rc - margin, floor_f);
-                rough = moved * moved > (float)c;
-              } else {
-                at = fmaxf(0.6f * at, floor_f);
-              }
-              kprev = c;
-            }
-          }
-          if (open) par = fmax((double)bound, floor_t);
-          // (t is the root if it came from the active set of a point left of it and no entry lies between: the fp32 steps have
-          // left a window (par, end] that holds it more often than not, and the entries of the window show in the same pass)
-          double end = par + (double)(2.0f * margin);
-          bool first = true;
-          unsigned kfull = 0u;
-          while (__any(open)) {
-            const float ct = hm_above(par), ce = hm_above(end);
-            double s = 0.0;
-            unsigned c = 0;
-            unsigned long long between = 0ull;   // lanes with an entry in the window
-            hm_keep_stored(d[j]);
-  #pragma unroll
-            for (int k = 0; k < KPF; ++k)
-  #pragma unroll
-              for (int e = 0; e < VEC; ++e) {
-                const float h = fabsf((float)d[j][k].e[e]);
-                const bool in = h >= ct;
-                s += (double)(in ? h : 0.0f);
-                c += in ? 1u : 0u;
-                between |= __ballot(in) ^ __ballot(h >= ce);
-                asm volatile("" : "+s"(between));   // (at once: put off, the masks of all elements spill)
-              }
-            s = seg_sum<SEG>(s);
-            c = seg_sum_u<SEG>(c);
-            const bool clear = ((between >> (lane & ~(SEG - 1))) & ((1ull << SEG) - 1ull)) == 0ull;
-            if (open) {
-              if (c == 0u || c == kfull) {
-                open = false;
-              } else {
-                const double t = (s - r) / (double)c;
-                const bool inside = clear && t >= par && t <= end;
-                open = !inside && (first || t > par);
-                if (first || t > par) par = fmax(t, floor_t);   // (the first may step back)
-                end = par + (double)(2.0f * margin);
-                kfull = c;
-              }
-            }
-            first = false;
-          }
-        }
+    for (int j = 0; j < PASS; ++j) {
+      if (j0 + j < p.rounds) {
+        const int f = (j0 + j) * NSEG + seg;
+        const int fc = f < fibres ? f : fibres - 1;
+        const double nv = sm_v[fc], r = sm_r[fc];
+        double par = 0.0;
         hm_keep_stored(d[j]);
-      }
-      const float rf = (float)r;
-      T* out = X + origin + (long long)fc * p.len;
+        if constexpr (Q == Q2) par = nv > r ? r / nv : 1.0;
+        if constexpr (Q == Q1) {
+          // The fixed point of fibre_map_cached_kernel, on the elements as fp32: |x| > t is |x| >= above(t).  What the search costs is
+          // vector instructions (the memory is idle meanwhile), so the steps far from the root are taken on fp32 sums, without a
+          // quotient in fp64, until a step passes so few entries that the next one hardly passes any; and the last one is known
+          // by no entry lying around it instead of by evaluating there once more.
+          bool open = nv > r && r > 0.0 && f < fibres;
+          const double floor_t = open ? (nv - r) * per_element : 0.0;
+          if (nv > r && !(r > 0.0)) par = HUGE_VAL;
+          // (floor_f rounded down: rounded up it may reach the entries of a fibre in which all are equal, and a search that starts there sees
+          // none above it and ends: 256 x 256 x 256 ones at a radius of 0.1 came out as zeros)
+          const float ratio = (float)(r * __builtin_amdgcn_rcp(nv)), rs = (float)r, floor_f = float_at_or_below(floor_t);
+          float at = open ? fmaxf((float)(nv * per_element) * 1.25331414f * gauss_z(ratio), floor_f) : HUGE_VALF;
+          if constexpr (SEG == 4 || KPF == 16) {
+            // (16 fibres share a wavefront: what a step costs beside its elements counts little, and the fewest steps win.  16 chunks per lane
+            // leave no registers, and their code no cache, for both loops: 200 x 30 x 1001 l1,1,1 24.9 / 23.9 us with this one alone,
+            // 256 x 64 x 1024 35.9 / 36.7, behind other kernels 65.7 / 63.3)
+            bool first = (double)at > floor_t;
+            par = open ? (first ? (double)at : floor_t) : par;
+            unsigned kfull = 0u;
+            while (__any(open)) {
+              const float ct = hm_above(par);
+              double s = 0.0;
+              unsigned c = 0;
+              hm_keep_stored(d[j]);
 #pragma unroll
-      for (int k = 0; k < KPF; ++k) {
-        Pack<T, VEC> z;
+              for (int k = 0; k < KPF; ++k)
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          const float x = (float)d[j][k].e[e];
-          if constexpr (Q == QINF) z.e[e] = (T)copysignf(fminf(fabsf(x), rf), x);
-          else if constexpr (Q == Q2) z.e[e] = round_to<T>((double)x * par);
-          else z.e[e] = round_to_signed<T>((double)fabsf(x) - par, x);
+                for (int e = 0; e < VEC; ++e) {
+                  const float h = fabsf((float)d[j][k].e[e]);
+                  const bool in = h >= ct;
+                  s += (double)(in ? h : 0.0f);
+                  c += in ? 1u : 0u;
+                }
+              s = seg_sum<SEG>(s);
+              c = seg_sum_u<SEG>(c);
+              const double t = (s - r) / (double)c;
+              if (open) {
+                if (first) {
+                  kfull = c;
+                  par = c > 0u ? fmax(t, floor_t) : floor_t;
+                } else if (c == 0u || c == kfull) {
+                  open = false;
+                } else {
+                  kfull = c;
+                  if (t > par) par = t;
+                }
+              }
+              first = false;
+            }
+          } else {
+            float bound = floor_f, margin = 0.0f;
+            bool rough = open;
+            unsigned kprev = 0u;
+            for (int step = 0; step < 6 && __any(rough); ++step) {
+              float s = 0.0f;
+              unsigned c = 0;
+              hm_keep_stored(d[j]);
+#pragma unroll
+              for (int k = 0; k < KPF; ++k)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) {
+                  const float h = fabsf((float)d[j][k].e[e]);
+                  const bool in = h > at;
+                  s += in ? h : 0.0f;
+                  c += in ? 1u : 0u;
+                }
+              s = hm_seg_sum_f<SEG>(s);
+              c = seg_sum_u<SEG>(c);
+              if (rough) {
+                const float rc = __builtin_amdgcn_rcpf((float)c), moved = (float)c - (float)kprev;
+                // (from any point the step ends at or left of the root, and 64 fp32 additions are off by less than the margin, subnormal
+                // sums included; a point beyond every entry says nothing: back towards the bound)
+                if (c > 0u) {
+                  margin = fmaf(8e-6f * s, rc, 1e-43f);
+                  at = bound = fmaxf((s - rs) * rc - margin, floor_f);
+                  rough = moved * moved > (float)c;
+                } else {
+                  at = fmaxf(0.6f * at, floor_f);
+                }
+                kprev = c;
+              }
+            }
+            if (open) par = fmax((double)bound, floor_t);
+            // (t is the root if it came from the active set of a point left of it and no entry lies between: the fp32 steps have
+            // left a window (par, end] that holds it more often than not, and the entries of the window show in the same pass)
+            double end = par + (double)(2.0f * margin);
+            bool first = true;
+            unsigned kfull = 0u;
+            while (__any(open)) {
+              const float ct = hm_above(par), ce = hm_above(end);
+              double s = 0.0;
+              unsigned c = 0;
+              unsigned long long between = 0ull;   // lanes with an entry in the window
+              hm_keep_stored(d[j]);
+#pragma unroll
+              for (int k = 0; k < KPF; ++k)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) {
+                  const float h = fabsf((float)d[j][k].e[e]);
+                  const bool in = h >= ct;
+                  s += (double)(in ? h : 0.0f);
+                  c += in ? 1u : 0u;
+                  between |= __ballot(in) ^ __ballot(h >= ce);
+                  asm volatile("" : "+s"(between));   // (at once: put off, the masks of all elements spill)
+                }
+              s = seg_sum<SEG>(s);
+              c = seg_sum_u<SEG>(c);
+              const bool clear = ((between >> (lane & ~(SEG - 1))) & ((1ull << SEG) - 1ull)) == 0ull;
+              if (open) {
+                if (c == 0u || c == kfull) {
+                  open = false;
+                } else {
+                  const double t = (s - r) / (double)c;
+                  const bool inside = clear && t >= par && t <= end;
+                  open = !inside && (first || t > par);
+                  if (first || t > par) par = fmax(t, floor_t);   // (the first may step back)
+                  end = par + (double)(2.0f * margin);
+                  kfull = c;
+                }
+              }
+              first = false;
+            }
+          }
+          hm_keep_stored(d[j]);
         }
-        const int b = f < fibres ? hl.blank(p, k) : VEC;
-        if (b == 0) {
-          store_pack(out + hl.at(p, k), z);
-        } else if (b < VEC) {
+        const float rf = (float)r;
+        T* out = X + origin + (long long)fc * p.len;
 #pragma unroll
-          for (int e = 0; e < VEC; ++e)
-            if (e >= b) store_one_nt(out + hl.at(p, k) + e, z.e[e]);
+        for (int k = 0; k < KPF; ++k) {
+          Pack<T, VEC> z;
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) {
+            const float x = (float)d[j][k].e[e];
+            if constexpr (Q == QINF) z.e[e] = (T)copysignf(fminf(fabsf(x), rf), x);
+            else if constexpr (Q == Q2) z.e[e] = round_to<T>((double)x * par);
+            else z.e[e] = round_to_signed<T>((double)fabsf(x) - par, x);
+          }
+          const int b = f < fibres ? hl.blank(p, k) : VEC;
+          if (b == 0) {
+            store_pack(out + hl.at(p, k), z);
+          } else if (b < VEC) {
+#pragma unroll
+            for (int e = 0; e < VEC; ++e)
+              if (e >= b) store_one_nt(out + hl.at(p, k) + e, z.e[e]);
+          }
         }
       }
+    }
+    j0 += PASS;
+    if (PASS == ROUNDS || j0 >= p.rounds) break;
+#pragma unroll
+    for (int j = 0; j < PASS && PASS + j < ROUNDS; ++j) {
+#pragma unroll
+      for (int k = 0; k < KPF; ++k) d[j][k] = d[PASS + j][k];
     }
   }
 }
