@@ -85,6 +85,16 @@ static inline void plan_batch_map(int count, const long long* tiles, const long 
   for (int i = 0; i < count; ++i) plan->groups[i] = (int)cdiv(cdiv(rows[i], MAP_RBLK), lo);
 }
 
+// Row blocks that a map workgroup of a batch requests under its search (see colmap_body).  Every one costs 16 registers in
+// fp32 and 32 on 16-bit storage, and the plan above counts on two workgroups per CU whatever the number of columns and on
+// three up to 4096: as many as leave those.  One / four blocks, us: l1,inf fp32 16 x (1024 x 1024) 41.2 / 38.8, 4 x (512 x 6000) 35.7 / 33.5;
+// bf16 28.0 / 29.5, 26.1 / 38.8 (one workgroup per CU).  l1,2 fp32 beyond 4096 columns has room for three: 4 x (512 x 6000)
+// 35.0 / 33.9 with three / 37.8 with four, 16 x (1024 x 1024) 41.2 / 40.2 / 39.8; bf16 8 x (10000 x 256) 41.0 / 65.7.
+template <int Q, typename T>
+constexpr int map_ahead() {
+  return sizeof(T) == 2 ? 1 : Q == QINF ? 4 : 3;
+}
+
 // The problem a workgroup belongs to, and its number within that problem.
 __device__ __forceinline__ int batch_find(const BatchGrid& gr, int count, long long& bid) {
   int p = 0;
@@ -129,15 +139,16 @@ __global__ __launch_bounds__(WG) void colmap_batch_kernel(BatchItems it, BatchGr
   const T* Y = static_cast<const T*>(b.Y);
   T* X = static_cast<T*>(b.X);
   constexpr int SEARCH = Q == Q1 ? 0 : SC;   // l1,1: tau comes from the record, not from a search here
+  constexpr int AHEAD = map_ahead<Q, T>();
   const double eta = b.eta;
   const int form = map_form(b.wide != 0, b.m, WIDE);
   const bool wave = RIDE && b.whole != 0;
   if (form == MAP_EVEN)
-    colmap_body<Q, T, WIDE, MAP_EVEN, SEARCH, MAP_AHEAD>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid, wave);
+    colmap_body<Q, T, WIDE, MAP_EVEN, SEARCH, AHEAD>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid, wave);
   else if (form == MAP_RAGGED)
-    colmap_body<Q, T, WIDE, MAP_RAGGED, SEARCH, MAP_AHEAD>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid, wave);
+    colmap_body<Q, T, WIDE, MAP_RAGGED, SEARCH, AHEAD>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid, wave);
   else
-    colmap_body<Q, T, WIDE, MAP_STRIDED, SEARCH, MAP_AHEAD>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid, wave);
+    colmap_body<Q, T, WIDE, MAP_STRIDED, SEARCH, AHEAD>(Y, X, b.n, b.m, g, ws, b.u_out, b.mask_out, eta, outer, bid, wave);
 }
 
 // Matrices of at most 128 KiB each: the one-kernel form of tiny.h for all of them in one launch

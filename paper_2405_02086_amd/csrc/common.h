@@ -30,7 +30,6 @@ constexpr unsigned NO_COUNT = 0xffffffffu;
 constexpr int QINF = MLPROJ_L1INF, Q1 = MLPROJ_L11, Q2 = MLPROJ_L12;
 constexpr int MODE_PROJECT = 0, MODE_NORM = 1;
 constexpr int MAP_UNROLL = 4;            // rows in flight per wavefront in the map pass (x2: pipelined)
-constexpr int MAP_AHEAD = 4;             // ... and blocks requested while the workgroup searches the outer threshold
 constexpr int MAP_RBLK = WAVES * MAP_UNROLL;
 constexpr long long TARGET_WGS = 512;    // workgroups of a read-only pass on 256 CUs (2 per CU)
 constexpr long long TARGET_WGS_MAP = 256;  // workgroups of the read+write pass (1 per CU)

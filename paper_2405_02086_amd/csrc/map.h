@@ -75,8 +75,8 @@ __device__ __forceinline__ void colmap_body(const T* Y, T* X, long long n, long 
   };
   // The first block is requested before tau is known, so its latency hides the search.  AHEAD > 1: that many blocks, the first
   // behind the search's own loads and the others when those have arrived (asked for ahead of them they hold up the
-  // wavefronts, and with them the search).  Batches take MAP_AHEAD = 4: 16 x (1024 x 1024) 41.1 -> 38.9 us per call; single calls, one
-  // workgroup per CU and a band of rows that should stay narrow, one block: 4096 x 4096 35.0 with 1, 35.2 with 2, 35.6 us with 4.
+  // wavefronts, and with them the search).  Batches: see map_ahead.  Single calls, one workgroup per CU and a band of
+  // rows that should stay narrow, take one block: 4096 x 4096 35.0 with 1, 35.2 with 2, 35.6 us with 4.
   Pack<T, VEC> ahead[AHEAD > 1 ? AHEAD - 1 : 1][U];
   auto request_first = [&]() {
     if (col_ok && inside_rows(b)) load_block(b, x);
@@ -94,14 +94,13 @@ __device__ __forceinline__ void colmap_body(const T* Y, T* X, long long n, long 
   bool inside;
   if constexpr (SC > 0) {
     SearchOut o;
-    if (wave_search || AHEAD == 1) request_first();
-    if (wave_search) {
-      request_ahead();
-      o = search_wave<WAVE_SEARCH_CACHE, double>(ws.v, (int)m, fused_eta, outer);
-    } else if constexpr (AHEAD > 1) {
-      o = search_block<WG, SC, WG, double>(ws.v, m, fused_eta, MODE_PROJECT, outer, bs, request_first, request_ahead);
+    if constexpr (AHEAD > 1) {
+      o = wave_search ? search_wave<WAVE_SEARCH_CACHE, double>(ws.v, (int)m, fused_eta, outer, request_first, request_ahead)
+                      : search_block<WG, SC, WG, double>(ws.v, m, fused_eta, MODE_PROJECT, outer, bs, request_first, request_ahead);
     } else {
-      o = search_block<WG, SC>(ws.v, m, fused_eta, MODE_PROJECT, outer, bs);
+      request_first();
+      o = wave_search ? search_wave<WAVE_SEARCH_CACHE, double>(ws.v, (int)m, fused_eta, outer)
+                      : search_block<WG, SC>(ws.v, m, fused_eta, MODE_PROJECT, outer, bs);
     }
     top = top_of(o);
     inside = o.inside != 0u;

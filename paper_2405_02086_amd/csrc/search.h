@@ -228,8 +228,10 @@ __device__ __forceinline__ SearchOut search_block(const VT* __restrict__ v, long
 // same bits (they may differ from search_block's in the last bit of a sum: another order).
 constexpr int WAVE_SEARCH_CACHE = 8;
 constexpr int WAVE_SEARCH_MAX = WAVE * WAVE_SEARCH_CACHE;   // groups up to which the one-kernel form searches this way
-template <int CACHE, typename VT>
-__device__ __forceinline__ SearchOut search_wave(const VT* v, int ngroups, double eta, int outer) {
+// after_loads, after_sums: as for search_block.
+template <int CACHE, typename VT, typename AfterLoads = NothingAfterLoads, typename AfterSums = NothingAfterLoads>
+__device__ __forceinline__ SearchOut search_wave(const VT* v, int ngroups, double eta, int outer,
+                                                 AfterLoads after_loads = AfterLoads(), AfterSums after_sums = AfterSums()) {
   const int lane = threadIdx.x & (WAVE - 1);
   double vr[CACHE];
   double a = 0.0, mx = 0.0;
@@ -237,12 +239,17 @@ __device__ __forceinline__ SearchOut search_wave(const VT* v, int ngroups, doubl
   for (int k = 0; k < CACHE; ++k) {
     const int i = lane + k * WAVE;
     vr[k] = i < ngroups ? (double)v[i] : 0.0;   // 0 is never active
+  }
+  after_loads();
+#pragma unroll
+  for (int k = 0; k < CACHE; ++k) {
     a += vr[k];
     mx = fmax(mx, vr[k]);
   }
   SearchOut o;
   o.total = wave_sum(a);
   o.vmax = wave_max(mx);
+  after_sums();
   o.norm = o.total;
   o.tau = 0.0;
   o.scale = 1.0;

@@ -3,6 +3,8 @@ header declares, sizes workspaces sanely, and rejects bad arguments before enque
 import ctypes
 import os
 import re
+import shutil
+import subprocess
 
 import pytest
 
@@ -394,3 +396,31 @@ def test_multilevel_route_argument_checks(lib):
     f = lib.mlproj_multilevel_one_pass
     assert f(3, 1, 4, 4, 4, 256) == -6 and f(0, 3, 4, 4, 4, 256) == -6
     assert f(0, 1, 0, 4, 4, 256) == -2 and f(0, 1, 4, 4, 4, 0) == -2 and f(0, 1, 1 << 30, 1 << 30, 1, 256) == -3
+
+
+def kernel_resources(tmp_path):
+    """Registers and LDS of every kernel in the built library, as its code objects' metadata states them."""
+    tools = "/opt/rocm/llvm/bin/"
+    copy = shutil.copy(binding.LIB_PATH, tmp_path)
+    subprocess.run([tools + "llvm-objdump", "--offloading", copy], check=True, capture_output=True)
+    found = {}
+    for name in os.listdir(tmp_path):
+        if "gfx950" not in name:
+            continue
+        notes = subprocess.run([tools + "llvm-readelf", "--notes", os.path.join(tmp_path, name)], check=True, capture_output=True, text=True).stdout
+        for entry in notes.split("- .agpr_count:")[1:]:
+            kernel = re.search(r"\.name:\s+(\S+)", entry).group(1)
+            found[kernel] = {k: int(re.search(r"\.%s:\s+(\d+)" % k, entry).group(1)) for k in ("vgpr_count", "vgpr_spill_count", "group_segment_fixed_size")}
+    return found
+
+
+def test_batch_map_workgroups_fit_as_planned(lib, tmp_path):
+    """The map launch of a batch is planned for at least two workgroups per CU (one wavefront of each on every SIMD: 512 registers between
+    them), three where no matrix has more than 4096 columns: the blocks requested under the search must leave room for them."""
+    builds = {k: r for k, r in kernel_resources(tmp_path).items() if "colmap_batch_kernel" in k}
+    assert len(builds) >= 18
+    for kernel, r in builds.items():
+        search = int(re.search(r"colmap_batch_kernelILi\dE\w+?Li(\d+)E", kernel).group(1))
+        registers = -(-r["vgpr_count"] // 8) * 8
+        assert 512 // registers >= (3 if search <= 16 else 2), (kernel, r)
+        assert r["vgpr_spill_count"] == 0, (kernel, r)
