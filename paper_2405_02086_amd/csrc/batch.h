@@ -248,8 +248,8 @@ __global__ __launch_bounds__(FIN_WG) void l11_finish_batch_kernel(BatchItems it,
 // l1,1 problems of at most 4096 rows after their aggregate pass: the columns-in-registers kernel
 // of l11held.h, every workgroup running the outer search of its own problem.  NV: the values per
 // thread the tallest problem of the launch needs.  EVEN as in l11_held_body, when it holds for every
-// problem of the launch.  (Both bodies in one kernel: the two-per-CU builds spill 42 to 48 registers
-// instead of 19 to 29, every build holds the LDS twice; 8 x (2048 x 2048) fp32 136 against 132 us.  A launch each
+// problem of the launch.  (Both bodies in one kernel: the two-per-CU builds spilled 42 to 48 registers
+// instead of 19 to 29, every build held the LDS twice; 8 x (2048 x 2048) fp32 136 against 132 us.  A launch each
 // for the even and the ragged problems of a mixed batch: 300x257 + 3 x (64x64) + 1000x512 40 against 25 us.)
 // SC and COLS as in l11_held_body: the values of v per thread of the search (0: the record is read, see
 // search_batch_kernel), and the columns of a stripe.
@@ -263,7 +263,7 @@ __global__ __launch_bounds__(LH_WG, lh_min_waves(NV, PACKED)) void l11_held_batc
   const Geometry g = plan_columns(b.n, b.m, WIDE, Q1);
   const Ws ws = bind(b.ws, layout_for(g, b.m, Q1));
   const long long stripes = (long long)(gr.first[p + 1] - gr.first[p]);
-  l11_held_body<T, NV, SC, COLS, EVEN>(static_cast<const T*>(b.Y), static_cast<T*>(b.X), b.n, b.m, ws, b.u_out,
+  l11_held_body<T, NV, SC, COLS, EVEN, lh_windows(sizeof(T), PACKED)>(static_cast<const T*>(b.Y), static_cast<T*>(b.X), b.n, b.m, ws, b.u_out,
                                        b.mask_out, SC > 0 ? b.eta : -1.0, outer, stripe_of_workgroup(bid, stripes));
 }
 

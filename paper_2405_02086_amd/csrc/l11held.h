@@ -175,13 +175,23 @@ __device__ __forceinline__ float half_max(float x) {
   return max_abs(__uint_as_float(r.even), __uint_as_float(r.odd));
 }
 
+// Whether a build lists windows or takes plain steps only.  A window saves one to three evaluations; it costs a comparison and two
+// lane masks per value in every evaluation, and the listing.  Not with two workgroups of 64 values per CU on 16-bit storage, bound by
+// instructions, where registers spill (20 to 30 with windows, 12 to 28 without) and eight columns of listing share a row.
+// Windows / plain steps / the form before both, us at a radius of 0.2 norms, bf16: 2000 x 10000 Gaussian 63.1 / 64.8 / 63.8, Laplace 76.7 / 70.8 / 70.9; 2001 x
+// 15003 93.0 / 91.7 / 90.1 and 109 / 100 / 100; 2048 x 8192 72.5 / 69.4 / 76.6 and 79.1 / 74.0 / 80.4; 1500 x 5000 42.8 / 44.9 / 44.5 and 50.8 / 48.9 /
+// 48.5; 8 x (2048 x 2048) in a batch 113 / 112 / 108 and 120 / 113 / 112.  (Sums of 16-bit entries within a factor 2^33 are exact
+// in 64 bits: either way a column ends with the same threshold.)
+constexpr bool lh_windows(int elem_bytes, bool packed) { return !(elem_bytes == 2 && packed); }
+
 // NV: values per thread (rows per thread x VEC).  SC > 0: every workgroup runs the outer search
 // itself (SC values of v per thread), workgroup 0 files the result record; SC = 0: a search
 // kernel ran before and the record is read.  X may alias Y: a thread writes only elements it has read, and
 // what it reads beside them (see below) goes nowhere.
+// WINDOWS: see lh_windows.
 // EVEN: every stripe's runs lie on whole 64-byte sectors of X (lh_even_rows); otherwise rows may start
 // anywhere.  (Two builds: with the ragged form's tests and stores beside it the even one lost 1 to 2 %.)
-template <typename T, int NV, int SC, int COLS, bool EVEN>
+template <typename T, int NV, int SC, int COLS, bool EVEN, bool WINDOWS>
 __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, long long m, const Ws& ws,
                                               float* __restrict__ u_out, unsigned char* __restrict__ mask_out,
                                               double seed_eta, int outer, long long bid) {
@@ -427,9 +437,10 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
     int windows = 0;
     bool certain = true;    // t is a lower bound on the root
     auto lay_window = [&](double S, unsigned K, double p) {
+      hi = t;
+      if constexpr (!WINDOWS) return;
       const float rk = __builtin_amdgcn_rcpf((float)K), d = (float)(t - p), e = (float)fma(-(double)K, p, S) * rk, gap = e * rk;
       const float width = d * d * __builtin_amdgcn_rcpf(e) + 2.0f * gap;
-      hi = t;
       if (K > 0u && e > 0.0f && width <= (float)LH_LIST_SPAN * gap && windows < LH_WINDOWS) {
         hi = fmin(t + (double)width, t + t);   // (within a factor 2 the sums of listed entries are exact, in any order)
         if (hi > t) ++windows;
@@ -487,12 +498,14 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
           const bool in = h >= ch[k];
           s[k] += (double)(in ? h : 0.0f);
           cnt[k] += in ? 1u : 0u;
-          listed[k] = __ballot(h >= cl[k]) & ~__ballot(in);
-          any |= listed[k];
+          if constexpr (WINDOWS) {
+            listed[k] = __ballot(h >= cl[k]) & ~__ballot(in);
+            any |= listed[k];
+          }
         }
 #pragma unroll
         for (int k = 0; k < VEC; ++k) asm volatile("" : "+v"(s[k]), "+v"(cnt[k]));   // (the sums are not put off beyond the branch)
-        if (any != 0ull) {   // (one entry in some hundreds)
+        if (WINDOWS && any != 0ull) {   // (one entry in some hundreds)
           unsigned found = 0u;
 #pragma unroll
           for (int k = 0; k < VEC; ++k) found |= __builtin_amdgcn_inverse_ballot_w64(listed[k]) ? 1u << k : 0u;
@@ -513,7 +526,7 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
         const double S = half_sum(lds.s[hc][hl]);
         const unsigned K = half_sum_u(lds.k[hc][hl]);
         const unsigned listed = lds.listed[hc];
-        const bool window = open && hi > t;
+        const bool window = WINDOWS && open && hi > t;
         const bool solve = window && listed <= (unsigned)LH_LIST;
         double tn = t;
         // Inside the window: the fixed point over the listed entries and what lies above them, from the bound t.
@@ -525,7 +538,7 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
         }
         bool going = solve;
         unsigned kk = NO_COUNT;
-        while (__any(going ? 1 : 0)) {
+        while (WINDOWS && __any(going ? 1 : 0)) {
           const float c = above(t);
           double ls = 0.0;
           unsigned lk = 0u;
@@ -598,7 +611,7 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
 }
 
 // Registers: 32 values per thread leave room for two workgroups per CU, 128 for one.  64 fit two
-// only with some twenty registers spilled, which pays when there are more stripes than CUs (the
+// only with twelve to 28 registers spilled on 16-bit storage (fp32: none to four), which pays when there are more stripes than CUs (the
 // second workgroup's loads and stores run under the first one's arithmetic: 42 against 52 us at
 // 2048 x 8192) and costs when every stripe has a CU to itself (27 against 23 us at 2048 x 2048):
 // PACKED picks the two-per-CU build.
@@ -608,7 +621,7 @@ template <typename T, int NV, int SC, bool EVEN, bool PACKED = false, int COLS =
 __global__ __launch_bounds__(LH_WG, lh_min_waves(NV, PACKED)) void l11_held_kernel(
     const T* Y, T* X, long long n, long long m, Ws ws, float* __restrict__ u_out,
     unsigned char* __restrict__ mask_out, double seed_eta, int outer) {
-  l11_held_body<T, NV, SC, COLS, EVEN>(Y, X, n, m, ws, u_out, mask_out, seed_eta, outer,
+  l11_held_body<T, NV, SC, COLS, EVEN, lh_windows(sizeof(T), PACKED)>(Y, X, n, m, ws, u_out, mask_out, seed_eta, outer,
                                  stripe_of_workgroup(blockIdx.x, gridDim.x));
 }
 

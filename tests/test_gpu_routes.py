@@ -154,6 +154,28 @@ def test_l11_leaves_large_ragged_matrices_to_the_grid(mp, held, shape, inplace):
         assert torch.equal(Xb, X)
 
 
+@pytest.mark.parametrize("kind", ["normal", "heavy", "tied"])
+@pytest.mark.parametrize("storage", ["bf16", "f16"])
+def test_l11_batches_of_plain_steps_give_the_bits_of_calls_with_windows(mp, storage, kind):
+    """16-bit matrices of 1025 to 2048 rows: together more stripes than CUs, stepped without windows; each for itself fewer, with
+    windows.  Entries of one scale, over twelve decimal orders (f16: eight), and on a grid of a few values."""
+    rng = np.random.default_rng(len(kind))
+    Yd, etas = [], []
+    for n, m in ((1100, 2048), (2048, 2040), (1025, 3001)):
+        Y = rng.standard_normal((n, m))
+        if kind == "heavy":
+            Y = np.sign(Y) * 10.0 ** rng.uniform(*((-8, 4) if storage == "bf16" else (-4, 4)), (n, m))
+        elif kind == "tied":
+            Y = np.round(3 * Y) / 4
+        Y = orc.round_to_storage(Y.astype(np.float32), storage)
+        Yd.append(torch.from_numpy(Y).cuda().to(getattr(torch, STORE_DTYPES[storage])))
+        etas.append(eta_for(Y, 1, {"normal": 0.2, "heavy": 0.9, "tied": 0.02}[kind]))
+    for Y, eta, X in zip(Yd, etas, mp.bilevel_proj_batch(Yd, etas, 1)):
+        assert torch.equal(mp.bilevel_proj_stored(Y, eta, 1), X)
+        Yh = Y.float().cpu().numpy()
+        check_stored(run_stored(mp, Yh, eta, 1, storage), orc.bilevel_stored(Yh, eta, 1, storage), 1, storage)
+
+
 @pytest.mark.parametrize("shape", [(200, 5001), (256, 5120), (5000, 101), (6000, 48), (1000, 77), (2048, 64), (9000, 40)])
 def test_l11_batches_share_their_launches(mp, shape):
     """Six matrices take the launches of two, whatever form of the l1,1 kernels they go to (16 x (5000 x 101): 84 us, 650 one
