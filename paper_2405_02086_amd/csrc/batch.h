@@ -271,7 +271,7 @@ __global__ __launch_bounds__(LH_WG, lh_min_waves(NV, PACKED)) void l11_held_batc
 // single call (search_kernel, same bits).
 template <typename T>
 __global__ __launch_bounds__(WG) void search_batch_kernel(BatchItems it, int outer) {
-  __shared__ PairScratch<WG / WAVE> s;
+  __shared__ SearchScratch<WG / WAVE> s;
   const BatchItem& b = it.item[blockIdx.x];
   const Geometry g = plan_columns(b.n, b.m, 16 / (int)sizeof(T), Q1);
   const Ws ws = bind(b.ws, layout_for(g, b.m, Q1));

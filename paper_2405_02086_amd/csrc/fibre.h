@@ -201,7 +201,7 @@ template <bool TOP>
 __device__ __forceinline__ Top top_prologue(const TopFuse& tf, long long nf) {
   Top top{0.0, 1.0, HUGE_VAL};
   if constexpr (TOP) {
-    __shared__ PairScratch<WAVES> bs;
+    __shared__ SearchScratch<WAVES> bs;
     const SearchOut o = search_block<WG, SEARCH_CACHE>(tf.ws.v, nf, tf.eta, MODE_PROJECT, tf.outer, bs);
     top = top_of(o);
     if (blockIdx.x == 0 && threadIdx.x == 0) write_result(tf.ws, o, nullptr);

@@ -192,7 +192,6 @@ __global__ __launch_bounds__(HELD_WG) void held_slab_kernel(const T* Y, T* X, lo
                 "one polling lane, one cleared word and one workspace word per piece");
   __shared__ float sm_v[HELD_MAX_WGS];       // the aggregate w_a of every slab (exact in fp32)
   __shared__ float sm_w[HELD_WAVES];
-  __shared__ PairScratch<HELD_WAVES> bs;
   __shared__ unsigned char sm_missing[HELD_MAX_WGS];
   __shared__ unsigned sm_any;
 

@@ -182,7 +182,7 @@ __global__ __launch_bounds__(HM_WG) void held_multi_kernel(const void* Yv, void*
   __shared__ double sm_v[HM_MAX_FIBRES];   // fibre norms
   __shared__ double sm_r[HM_MAX_FIBRES];   // ... their radii (a helper's scratch before that)
   __shared__ double sm_w[HM_MAX_SLABS];    // slab norms, of the whole tensor
-  __shared__ PairScratch<HM_WAVES> bs;
+  __shared__ SearchScratch<HM_WAVES> bs;
   __shared__ unsigned char sm_missing[HM_MAX_WGS], sm_list[HM_MAX_WGS];
   static_assert(HM_MAX_WGS <= 256, "a workgroup's number fits a byte");
   __shared__ unsigned sm_any;

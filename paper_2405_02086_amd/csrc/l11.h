@@ -325,7 +325,7 @@ __device__ __forceinline__ double l11_guess(double vj, double uj, long long n, d
 template <int SC>
 __device__ __forceinline__ void l11_init_body(long long n, long long m, const Ws& ws,
                                               double fused_eta, int outer, long long bid) {
-  __shared__ PairScratch<WAVES> bs;
+  __shared__ SearchScratch<WAVES> bs;
   Top top;
   bool nothing_to_do;
   if (fused_eta >= 0.0) {
@@ -612,7 +612,7 @@ __device__ __forceinline__ void l11_finish_body(const T* __restrict__ Y, long lo
                                                 int outer = MLPROJ_OUTER_L1) {
   __shared__ double sm_s[FIN_WAVES][FIN_COLS];
   __shared__ unsigned sm_k[FIN_WAVES][FIN_COLS];
-  __shared__ PairScratch<FIN_WAVES> bs;
+  __shared__ SearchScratch<FIN_WAVES> bs;
   mlproj_result* res = ws.res;
   const int c = threadIdx.x % FIN_COLS;
   const int r = threadIdx.x / FIN_COLS;

@@ -162,7 +162,7 @@ __global__ __launch_bounds__(WG) void l11_init_grid_kernel(long long n, long lon
                                                            double fused_eta, int outer,
                                                            const float* __restrict__ scale,
                                                            const float* __restrict__ gpart) {
-  __shared__ PairScratch<WAVES> bs;
+  __shared__ SearchScratch<WAVES> bs;
   __shared__ BlockScratch<WAVES> cs;
   Top top;
   bool nothing_to_do;

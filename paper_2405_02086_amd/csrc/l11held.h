@@ -199,7 +199,7 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
   constexpr int VEC = Sh::VEC, CW = Sh::CW, RL = Sh::RL;
   constexpr int ROWS = NV / VEC;
   __shared__ LhLds lds;
-  __shared__ PairScratch<LH_WAVES> bs;
+  __shared__ SearchScratch<LH_WAVES> bs;
   const int tid = threadIdx.x;
   const int lane = tid & (WAVE - 1);
   const int wave = tid / WAVE;

@@ -49,7 +49,7 @@ __device__ __forceinline__ void colmap_body(const T* Y, T* X, long long n, long 
                                             bool wave_search = false) {
   constexpr int TILE_W = WAVE * VEC;
   constexpr int U = MAP_UNROLL;
-  __shared__ PairScratch<WAVES> bs;
+  __shared__ SearchScratch<WAVES> bs;
   const int lane = threadIdx.x & (WAVE - 1);
   const int wave = threadIdx.x / WAVE;
   const long long t = bid % g.tiles;

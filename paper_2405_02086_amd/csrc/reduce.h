@@ -117,7 +117,6 @@ struct PairScratch {
   double a[2][NW];
   double b[NW];
   unsigned u[2][NW];
-  double top[NW * WAVE];   // every thread's largest value (see subset_bound)
 };
 // (AT_ONCE: how many waves' pairs are fetched together; fewer where registers are short)
 template <int NW, int AT_ONCE = NW>

@@ -88,6 +88,11 @@ __device__ __forceinline__ double subset_bound(const double* top, double tau, do
   return fmax(tau, at - 1e-12 * vmax);
 }
 
+template <int NW>
+struct SearchScratch : PairScratch<NW> {
+  double top[NW * WAVE];   // every thread's largest value (see subset_bound)
+};
+
 // NTHREADS > NT: a larger workgroup runs the search of an NT-thread one; the threads beyond
 // NT hold nothing and add zeros, so the result has the bits the NT-thread workgroup gets.
 // VT: the type v is stored in where the search reads it (fp64 in the workspace; fp32 for exact
@@ -104,7 +109,7 @@ template <int NT, int CACHE = SEARCH_CACHE, int NTHREADS = NT, typename VT = dou
           typename AfterSums = NothingAfterLoads>
 __device__ __forceinline__ SearchOut search_block(const VT* __restrict__ v, long long ngroups,
                                                   double eta, int mode, int outer,
-                                                  PairScratch<NTHREADS / WAVE>& s,
+                                                  SearchScratch<NTHREADS / WAVE>& s,
                                                   AfterLoads after_loads = AfterLoads(),
                                                   AfterSums after_sums = AfterSums()) {
   static_assert(NTHREADS >= NT && NTHREADS % WAVE == 0, "whole wavefronts, at least NT threads");
@@ -333,7 +338,7 @@ __global__ __launch_bounds__(NT) void search_kernel(Ws ws, long long ngroups, do
                                                     int only_as_fallback,
                                                     double* __restrict__ radii,
                                                     float* __restrict__ u_out) {
-  __shared__ PairScratch<NT / WAVE> s;
+  __shared__ SearchScratch<NT / WAVE> s;
   if (only_as_fallback && ws.flags[1] == 0u) return;
   const SearchOut o = search_block<NT, CACHE>(ws.v, ngroups, eta, mode, outer, s);
   if (threadIdx.x <= MAX_INNER_SWEEPS) ws.pending[threadIdx.x] = 0u;

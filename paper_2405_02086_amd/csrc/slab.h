@@ -50,7 +50,7 @@ __global__ __launch_bounds__(WG) void slabmap_kernel(const T* Y, T* X, long long
                                                      float* __restrict__ u_out,
                                                      unsigned char* __restrict__ mask_out,
                                                      double fused_eta) {
-  __shared__ PairScratch<WAVES> bs;
+  __shared__ SearchScratch<WAVES> bs;
   const long long a = d0 - 1 - blockIdx.x / g.groups;
   const long long c = blockIdx.x % g.groups;
   const long long lo = c * g.span;

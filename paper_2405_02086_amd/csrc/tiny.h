@@ -73,12 +73,12 @@ __device__ __forceinline__ void tiny_body(const T* Y, T* X, long long n,
                                           bool whole) {
   using Acc = typename AccOf<Q>::type;
   __shared__ alignas(16) Acc sm_part[TINY_WG * VEC];   // [row lane][column]
-  __shared__ PairScratch<TINY_WAVES> bs;
+  __shared__ SearchScratch<TINY_WAVES> bs;
   // v (zero beyond column m) takes the place of row lane 0 of the partials, in their type (fp32
   // maxima are exact, sums stay fp64): column c of that row is read by the one thread that then
-  // writes v_c, and the other rows lie behind it.  So the body's LDS is at most 32 KiB.
+  // writes v_c, and the other rows lie behind it.  The partials are 8 to 32 KiB (q = 2 on 16-bit storage), the search's scratch 4.3.
   Acc* const sm_v = sm_part;
-  static_assert(sizeof(Acc) * TINY_WG * VEC + sizeof(PairScratch<TINY_WAVES>) <= 49152,
+  static_assert(sizeof(Acc) * TINY_WG * VEC + sizeof(SearchScratch<TINY_WAVES>) <= 37 * 1024,
                 "tiny_body: the partial aggregates of this (q, storage type) need more LDS than planned");
   const int rl = TINY_WG / cw;
   const int tc = threadIdx.x % cw;
