@@ -578,16 +578,18 @@ static int run_trilevel(const T* Y, T* X, long long d0, long long d1, long long 
   mark(stream);
   launch((reduce_kernel<QINF>), rgrid, rblock, stream, ws.partial, d0, g, parts, ws.v, v_out, ws.flags);
   const bool fuse = d0 <= FUSED_SEARCH_MAX;
-  const double fused_eta = fuse ? (double)eta : -1.0;
   if (!fuse) {
     mark(stream);
     launch_search(ws, d0, (double)eta, MODE_PROJECT, MLPROJ_OUTER_L1, nullptr, stream);
   }
   mark(stream);
-  if (vec == WIDE)
-    launch((slabmap_kernel<T, WIDE>), grid, block, stream, Y, X, d0, len, g, ws, u_out, mask_out, fused_eta);
-  else
-    launch((slabmap_kernel<T, 1>), grid, block, stream, Y, X, d0, len, g, ws, u_out, mask_out, fused_eta);
+  auto map = [&](auto vecs) {
+    constexpr int V = decltype(vecs)::value;
+    if (fuse) launch((slabmap_kernel<T, V, true>), grid, block, stream, Y, X, d0, len, g, ws, u_out, mask_out, (double)eta);
+    else launch((slabmap_kernel<T, V, false>), grid, block, stream, Y, X, d0, len, g, ws, u_out, mask_out, -1.0);
+  };
+  if (vec == WIDE) map(std::integral_constant<int, WIDE>());
+  else map(std::integral_constant<int, 1>());
   mark(stream);
   return launch_status();
 }
@@ -1140,7 +1142,7 @@ using namespace mlproj;
 
 extern "C" {
 
-int mlproj_version(void) { return 389; }
+int mlproj_version(void) { return 390; }
 
 const char* mlproj_status_string(int status) {
   switch (status) {

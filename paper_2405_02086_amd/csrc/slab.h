@@ -44,19 +44,23 @@ __global__ __launch_bounds__(WG) void slabagg_kernel(const T* __restrict__ Y, lo
 
 // X_abc = sign(Y_abc) min(|Y_abc|, u_a).  The appendix form clips each fibre to
 // U2_ab = min(V_ab, u_a); since |Y_abc| <= V_ab the two clips give the same value.
-template <typename T, int VEC>
+// FUSED: every workgroup searches tau itself (see search_block); otherwise a search kernel ran before and the record is read.
+// What bounds it is loads in flight, eight workgroups per CU, so the two are builds of their own (with the search's registers in the one that
+// reads the record 153165 x 16 x 25 took 221 us and takes 206), and the search is the one without the start from the threads' largest values, which
+// fits 64 registers (seven workgroups with it: 843 x 8 x 80 15.6 against 14.8, 393 x 132 x 33 16.6 / 15.9; held to 64, it spills: 16.5, 17.5).
+template <typename T, int VEC, bool FUSED>
 __global__ __launch_bounds__(WG) void slabmap_kernel(const T* Y, T* X, long long d0,
                                                      long long len, Geometry g, Ws ws,
                                                      float* __restrict__ u_out,
                                                      unsigned char* __restrict__ mask_out,
                                                      double fused_eta) {
-  __shared__ SearchScratch<WAVES> bs;
   const long long a = d0 - 1 - blockIdx.x / g.groups;
   const long long c = blockIdx.x % g.groups;
   const long long lo = c * g.span;
   const long long hi = (lo + g.span < len) ? lo + g.span : len;
   Top top;
-  if (fused_eta >= 0.0) {
+  if constexpr (FUSED) {
+    __shared__ PairScratch<WAVES> bs;
     const SearchOut o = search_block<WG>(ws.v, d0, fused_eta, MODE_PROJECT, MLPROJ_OUTER_L1, bs);
     top = top_of(o);
     if (blockIdx.x == 0 && threadIdx.x == 0) write_result(ws, o, nullptr);
