@@ -61,12 +61,14 @@ static inline void hm_layout(long long nvec, int* seg, int* kpf) {
 // elements or not, and a segment's streamed stores leave partly written 64-byte sectors where a fibre is no
 // whole number of them.  The lines below were drawn on 4900 tensors of random sizes, radii and distributions on an
 // MI355X (256 CUs): a class of tensors takes the one pass where its median is ahead of the chain's and its worst
-// close to it.  What they send here takes 0.84 of the chain's time (geometric mean; 2.3 % of it is behind
-// by more than 2 %), what they keep away would have taken 1.11.  Chain / one pass, us, some of either kind:
-//   taken    256^3 l1,2,2 39.1 / 30.3, l1,1,1 46.2 / 43.7; 6 x 71 x 64 l1,1,inf 15.8 / 12.7; 1000 x 128 x 81
-//            l1,1,2 138 / 59; 256 x 64 x 1024 l1,2,2 42.8 / 37.3 (spilled registers and all, see below)
-//   refused  1 x 64 x 1000 l1,2,2 10.6 / 18.9 (one workgroup); 64 x 64 x 1000 l1,2,2 15.9 / 20.9; 1000 x 128 x 72
-//            l1,inf,2 32.0 / 37.1 (sectors, idle slots); 2000 x 256 x 15 l1,1,1 50.7 / 57.2; 4 x 512 x 8 bf16 l1,1,1 17.7 / 26.5
+// close to it.  What they sent here took 0.84 of the chain's time (geometric mean; 2.3 % of it was behind
+// by more than 2 %), what they kept away would have taken 1.11.  The l1 searches of the fibres have become cheaper since, so a few of the l1 classes
+// kept away would be level or ahead by now.  Chain / one pass, us, some of either kind (norms after the outer one innermost first):
+//   taken    256^3 l1,2,2 39.1 / 29.5, l1,1,1 46.4 / 39.0; 6 x 71 x 64 l1,1,inf 14.1 / 10.3; 1000 x 128 x 81
+//            l1,1,2 112 / 56; 256 x 64 x 1024 l1,2,2 39.3 / 33.7 (spilled registers and all, see below), l1,1,1 47.0 / 36.7; 200 x 30 x 1001 l1,1,1 37.4 / 24.0
+//   refused  1 x 64 x 1000 l1,2,2 14.2 / 19.0 (one workgroup); 64 x 64 x 1000 l1,2,2 15.3 / 21.2; 1000 x 128 x 72
+//            l1,2,inf 31.9 / 37.1 (sectors, idle slots); 2000 x 256 x 15 l1,1,1 48.5 / 51.7; 4 x 512 x 8 bf16 l1,1,1 18.7 / 27.1;
+//            but 1000 x 128 x 81 l1,2,1 59.7 / 56.6, 64 x 64 x 500 l1,1,1 17.9 / 17.6
 // q1: norm of the fibres; fibres, rounds: of a workgroup; cus: compute units.
 static inline bool hm_pays(int q1, int elem_bytes, long long len, long long nvec, int seg, int kpf, long long fibres,
                            long long rounds, long long nwg, int cus) {

@@ -315,8 +315,15 @@ __global__ __launch_bounds__(WG) void l11_filter_kernel(const T* __restrict__ Y,
 // search_block) and workgroup 0 files the result record and clears the sweep counters, which
 // takes the one-workgroup search kernel off the critical path; otherwise the record is read.
 // The guess for a kept column (see above) and the all-active lower bound.
-__device__ __forceinline__ double l11_guess(double vj, double uj, long long n, double& floor_t) {
-  const float z = gauss_z((float)(uj * __builtin_amdgcn_rcp(vj)));
+// z_most, in standard deviations: a column whose radius is next to nothing has its root beyond all but a few of its entries, and an evaluation
+// beyond all of them says nothing.  l11_reach: where about twelve of n Gaussian entries lie beyond (2.5 at 1000, 3.2 at 9000, 4.4 at 10^6), for guesses
+// that a whole sweep is spent on.  (600 columns of 9000 rows, every third with a share of 1e-4: without it six sweeps and eight columns
+// left over, with it three; 5632 x 10656 bf16 under the weighted ball, few such columns, 236 / 181 us.)
+__device__ __forceinline__ float l11_reach(long long n) {
+  return sqrtf(1.38629436f * __builtin_amdgcn_logf(fmaxf((float)n * (1.0f / 12.0f), 1.2f))) - 0.42f;   // (v_log_f32: base 2)
+}
+__device__ __forceinline__ double l11_guess(double vj, double uj, long long n, double& floor_t, float z_most) {
+  const float z = fminf(gauss_z((float)(uj * __builtin_amdgcn_rcp(vj))), z_most);
   const double sigma = (vj / (double)n) * 1.2533141373155001;   // sqrt(pi/2)
   floor_t = fmax((vj - uj) / (double)n, 0.0);
   return fmax(sigma * (double)z, floor_t);  // never below the all-active bound
@@ -347,7 +354,7 @@ __device__ __forceinline__ void l11_init_body(long long n, long long m, const Ws
   const double vj = ws.v[j];
   const double uj = radius_of(ws, j, vj, top);
   double tj = HUGE_VAL, floor_t = HUGE_VAL;
-  if (uj > 0.0) tj = l11_guess(vj, uj, n, floor_t);
+  if (uj > 0.0) tj = l11_guess(vj, uj, n, floor_t, l11_reach(n));
   ws.tauj[j] = tj;
   ws.tlo[j] = tj;
   ws.lb[j] = floor_t;
@@ -656,7 +663,7 @@ __device__ __forceinline__ void l11_finish_body(const T* __restrict__ Y, long lo
   bool first = sweeps == 0;
   if (seeded) {
     lb = 0.0;
-    t = mine ? l11_guess(ws.v[jj], uj, n, lb) : 0.0;
+    t = mine ? l11_guess(ws.v[jj], uj, n, lb, HUGE_VALF) : 0.0;
   } else {
     lb = ws.lb[jj];
     t = first ? ws.tauj[jj] : lb;

@@ -185,7 +185,7 @@ __global__ __launch_bounds__(WG) void l11_init_grid_kernel(long long n, long lon
     double lo = HUGE_VAL, hi = HUGE_VAL, floor_t = HUGE_VAL;
     if (uj > 0.0) {
       open = 1u;
-      const double guess = l11_guess(vj, uj, n, floor_t);
+      const double guess = l11_guess(vj, uj, n, floor_t, l11_reach(n));
       lo = hi = guess;
       // fold the column's grid partials (fp64: the counts are exact)
       const long long tl = j / g.tile_w, c = j % g.tile_w;

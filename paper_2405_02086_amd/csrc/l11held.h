@@ -22,7 +22,7 @@ namespace mlproj {
 // with the outer search and the first evaluation under them, 9 us of steps, 12 us of stores), and an evaluation
 // of all held entries costs 3 to 4 us there.  So as few of them as possible: the first is at the guess, every further one lists the
 // entries of a window that should hold the root, and among those it is found exactly (two evaluations as a rule instead of
-// three to eight; 4096 x 4096 54.1 -> 50.0 us per call, 2001 x 3003 38.0 -> 33.4).
+// three to eight; 4096 x 4096 54.1 -> 49.7 us per call, 2001 x 3003 38.0 -> 33.3).
 //
 // A lane owns VEC = 16 bytes' worth of neighbouring columns (one vector access per row), CW
 // lanes span the stripe, and the thread of row lane r holds rows r, r + RL, r + 2 RL, ...  The
@@ -237,7 +237,8 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
   };
   // The rows are asked for in parts: a wavefront stops at a load that the memory pipeline has no room for, and with it
   // everything its workgroup has to do meanwhile.  With the search inside (rows behind its loads of v / ahead of its rounds too, us): 4096 x
-  // 4096 4 / 12 50.4, 8 / 8 51.0, 8 / 16 50.0, 8 / 24 50.0, all 32 at once 54.6; 2001 x 3003 4 / 12 33.4, 8 / 8 33.7, 8 / 16 34.5.  With
+  // 4096 4 / 12 50.4, 8 / 8 51.0, 8 / 16 50.0, 8 / 24 50.0, all 32 at once 54.6; 2001 x 3003 4 / 12 33.4, 8 / 8 33.7, 8 / 16 34.5.  (Eleven shapes of 500 to 8192 rows, fp32 and bf16: 4 / 4 everywhere is
+  // within 2 %, but 1500 x 3000 28.2 / 27.7, 8192 x 1024 60.1 / 57.0 and the other way 3500 x 3501 49.0 / 49.8, 6000 x 2000 77.2 / 78.5.)  With
   // the search ahead: the first quarter at once, the rest when the stripe is known to be needed.
   constexpr int EARLY = SC > 0 ? (ROWS <= 16 ? 4 : 8) : (ROWS >= 4 ? ROWS / 4 : 1);
   constexpr int MIDDLE = SC > 0 ? (ROWS <= 8 ? ROWS : ROWS <= 16 ? 12 : 16) : ROWS;
@@ -358,7 +359,7 @@ __device__ __forceinline__ void l11_held_body(const T* Y, T* X, long long n, lon
   }
   // (the starting guess only now: with the search ahead, the rest of the stripe is on its way)
   // a dropped column maps to zero: threshold +inf; inside the ball nothing moves: threshold 0
-  t = mine ? l11_guess(vj, uj, n, lb) : (inside ? 0.0 : HUGE_VAL);   // (the same for a column somebody else owns)
+  t = mine ? l11_guess(vj, uj, n, lb, HUGE_VALF) : (inside ? 0.0 : HUGE_VAL);   // (the same for a column somebody else owns)
 
   float held[ROWS][VEC];
   auto widen_row = [&](int u) {

@@ -424,3 +424,11 @@ def test_batch_map_workgroups_fit_as_planned(lib, tmp_path):
         registers = -(-r["vgpr_count"] // 8) * 8
         assert 512 // registers >= (3 if search <= 16 else 2), (kernel, r)
         assert r["vgpr_spill_count"] == 0, (kernel, r)
+
+
+def test_slab_map_workgroups_fit_as_planned(lib, tmp_path):
+    """The map pass of the tri-level chain lives of eight workgroups of 256 threads per CU, with and without the search inside."""
+    builds = {k: r for k, r in kernel_resources(tmp_path).items() if "slabmap_kernel" in k}
+    assert len(builds) == 12
+    for kernel, r in builds.items():
+        assert r["vgpr_count"] <= 64 and r["vgpr_spill_count"] == 0, (kernel, r)

@@ -5,7 +5,7 @@ import pytest
 
 from oracle import mlproj_oracle as orc
 from test_gpu_parity import (ATOL, QNAME, RTOL, STORE_DTYPES, check_against_oracle, check_multi, check_stored, eta_for, nested_norm,  # noqa: F401
-                             run_gpu, run_multi, run_stored, stored_input, mp)
+                             run_gpu, run_multi, run_stored, run_weighted, stored_input, mp)
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -116,6 +116,28 @@ def test_l11_batches_give_the_bits_of_the_single_calls(mp, shapes, storage):
     mp.bilevel_proj_batch(Zs, etas, 1, Xs=Zs, mask_outs=masks)
     for Z, X, mask in zip(Zs, Xs, masks):
         assert torch.equal(Z, X) and torch.equal(mask.bool() | (X != 0).any(0), mask.bool())
+
+
+@pytest.mark.parametrize("storage", ["f32", "bf16"])
+@pytest.mark.parametrize("n", [9000, 20000])
+def test_l11_columns_with_next_to_no_radius_cost_no_further_sweeps(mp, n, storage):
+    """Every third column keeps a share of 1e-4 of its norm: its root lies beyond all but one or two of its Gaussian entries.  The guess stays
+    left of the largest, so one sweep more than for ordinary columns closes them (a first step, then a window)."""
+    rng = np.random.default_rng(n)
+    Y = rng.standard_normal((n, 600)).astype(np.float32)
+    Y[:, ::3] *= 0.5
+    Y = orc.round_to_storage(Y, storage)
+    v = np.abs(Y.astype(np.float64)).sum(0)
+    tau = 0.6 * v.max()
+    sweeps = []
+    for share in (0.5, 1e-4):
+        w = np.ones(600, np.float32)
+        w[::3] = v[::3] * (1.0 - share) / tau
+        eta = float(np.float32((w * np.maximum(v - w * tau, 0.0)).sum()))
+        got = run_weighted(mp, Y, eta, 1, storage, w)
+        sweeps.append(got["res"]["inner_sweeps"])
+        check_stored(got, orc.bilevel_stored(Y, eta, 1, storage, p=("w1", w)), 1, storage)
+    assert 0 < sweeps[0] and sweeps[1] <= sweeps[0] + 1, sweeps
 
 
 @pytest.mark.parametrize("family", ["gaussian", "cauchy", "misleading_head"])
