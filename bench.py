@@ -29,11 +29,10 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 # HBM-side bytes per launch of the map kernel from the rocprofv3 --pmc runs summarised in
-# profiles/ (FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, in KiB), valid for these library versions only.
-# (square_4096 taken at 389; the other two at 388, whose kernels move the same bytes)
-TRAFFIC_VERSIONS = (389, 388)   # the library versions the counters in profiles/ hold for
-TRAFFIC_KIB = {"square_4096": 32985.3 * 1.999 + 65558.6, "square_16384": 524931.1 * 1.999 + 1048631.2,
-               "tensor_256x256x256": 32903.1 * 1.999 + 65626.1}
+# profiles/ (FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, in KiB), valid for this library version only.
+TRAFFIC_VERSION = 390   # the library version the counters in profiles/ were taken with
+TRAFFIC_KIB = {"square_4096": 32980.6 * 1.999 + 65567.0, "square_16384": 524929.1 * 1.999 + 1048625.8,
+               "tensor_256x256x256": 32900.4 * 1.999 + 65630.3}
 INFINITY_CACHE_BYTES = 256 * 1024 * 1024
 
 
@@ -576,13 +575,13 @@ def main():
         # (inner searches and soft-threshold), not the plain map pass
         dom = "l11_held (inner searches + map from registers)"
     traffic_ok = (args.workload in TRAFFIC_KIB and args.variant == "l1inf"
-                  and mp.lib().mlproj_version() in TRAFFIC_VERSIONS)
+                  and mp.lib().mlproj_version() == TRAFFIC_VERSION)
     roofline = {
         "bound": "hbm", "kernel": "%s (%s; 8 B/element: reads Y, writes X)" % (dom, what),
         "achieved": 8.0 * elems / dom_ms / 1e6, "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "frac": 8.0 * elems / dom_ms / 1e6 / HBM_PEAK_GBS,
         "traffic": TRAFFIC_KIB[args.workload] * 1024.0 if traffic_ok else None,
-        "traffic_source": "profiles/ (rocprofv3 --pmc, taken with library version %d)" % TRAFFIC_VERSIONS[0] if traffic_ok else None,
+        "traffic_source": "profiles/ (rocprofv3 --pmc, taken with library version %d)" % TRAFFIC_VERSION if traffic_ok else None,
         "algorithmic_bytes": 8.0 * elems,
         "kernel_ms": dom_ms,
         "all_kernels_ms": {k: round(v, 5) for k, v in kms.items()},

@@ -18,8 +18,8 @@ namespace mlproj {
 // workgroup reads its stripe once, finds the thresholds on registers (no memory traffic per
 // step), and maps and stores from the same registers: after the aggregate pass Y is read once
 // and X written once, whatever the number of steps.
-// What bounds it: loads, searches and stores are one chain in every workgroup (4096 x 4096, one per CU: 12 us of loads
-// with the outer search and the first evaluation under them, 9 us of steps, 12 us of stores), and an evaluation
+// What bounds it: loads, searches and stores are one chain in every workgroup (4096 x 4096, one per CU, time stamps: 13 us of loads
+// with the outer search and the first evaluation under them, 8 us of steps, 11 us of stores), and an evaluation
 // of all held entries costs 3 to 4 us there.  So as few of them as possible: the first is at the guess, every further one lists the
 // entries of a window that should hold the root, and among those it is found exactly (two evaluations as a rule instead of
 // three to eight; 4096 x 4096 54.1 -> 49.7 us per call, 2001 x 3003 38.0 -> 33.3).
