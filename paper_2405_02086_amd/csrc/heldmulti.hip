@@ -78,9 +78,10 @@ __device__ __forceinline__ double hm_slab_norm(const double* v, int d1, int q2) 
 }
 
 // The radii of a slab's d1 fibres, by one wavefront: its fibre norms v (q2-norm nv) projected onto the
-// q2-ball of radius r (the map and the steps of fibre_map_cached_kernel, from the threshold Gaussian entries would have).  The norms are
-// read from LDS in every step: eight of them per lane in registers cost small tensors more than they gave large ones (2048 x 2 x 50 l1,1,1
-// 14.3 / 13.7 us, 256 x 256 x 256 39.4 / 39.1).
+// q2-ball of radius r (the map and the steps of fibre_map_cached_kernel, from the threshold Gaussian entries would have).  Up to
+// 2 * WAVE norms are read from LDS in every step; of more a lane keeps its first eight in registers (same order, same bits).  All in registers / all in
+// LDS / by this rule, us: 2048 x 2 x 50 l1,1,1 14.5 / 13.9 / 14.2, 1000 x 20 x 77 17.4 / 17.1 / 17.2; 39 x 265 x 11 l1,inf,1 12.7 / 13.1 / 12.8, 200 x 600 x 16 14.3 /
+// 15.8 / 14.4, 250 x 1000 x 24 l1,2,1 28.2 / 29.4 / 28.6.
 __device__ __forceinline__ void hm_slab_radii(const double* v, double* out, int d1, int q2, double nv, double r) {
   const int lane = threadIdx.x & (WAVE - 1);
   double par = 0.0;
@@ -95,26 +96,46 @@ __device__ __forceinline__ void hm_slab_radii(const double* v, double* out, int 
       bool first = (double)guess > floor_t;
       par = first ? (double)guess : floor_t;
       unsigned kprev = 0xffffffffu;
-      for (;;) {
-        double s = 0.0;
-        unsigned c = 0;
-        for (int i = lane; i < d1; i += WAVE) {
+      auto search = [&](auto add_above) {
+        for (;;) {
+          double s = 0.0;
+          unsigned c = 0;
+          add_above(s, c);
+          s = wave_sum(s);
+          c = wave_sum_u(c);
+          if (first) {
+            kprev = c > 0u ? c : 0xffffffffu;
+            par = c > 0u ? fmax((s - r) / (double)c, floor_t) : floor_t;
+            first = false;
+          } else if (c == 0u || c == kprev) {
+            break;
+          } else {
+            kprev = c;
+            const double t = (s - r) / (double)c;
+            if (t > par) par = t;
+          }
+        }
+      };
+      auto from_lds = [&](int begin, double& s, unsigned& c) {
+        for (int i = begin + lane; i < d1; i += WAVE) {
           const double x = v[i];
           if (x > par) { s += x; ++c; }
         }
-        s = wave_sum(s);
-        c = wave_sum_u(c);
-        if (first) {
-          kprev = c > 0u ? c : 0xffffffffu;
-          par = c > 0u ? fmax((s - r) / (double)c, floor_t) : floor_t;
-          first = false;
-        } else if (c == 0u || c == kprev) {
-          break;
-        } else {
-          kprev = c;
-          const double t = (s - r) / (double)c;
-          if (t > par) par = t;
-        }
+      };
+      if (d1 <= 2 * WAVE) {
+        search([&](double& s, unsigned& c) { from_lds(0, s, c); });
+      } else {
+        constexpr int KEPT = 8;
+        double kept[KEPT];
+#pragma unroll
+        for (int k = 0; k < KEPT; ++k) kept[k] = lane + k * WAVE < d1 ? v[lane + k * WAVE] : 0.0;   // (0 is never above a threshold)
+        search([&](double& s, unsigned& c) {
+#pragma unroll
+          for (int k = 0; k < KEPT; ++k) {
+            if (k * WAVE < d1 && kept[k] > par) { s += kept[k]; ++c; }
+          }
+          from_lds(KEPT * WAVE, s, c);
+        });
       }
     }
   }
